@@ -56,7 +56,23 @@ constexpr MfmaForm kSlimShortForm = {kMfmaSlimShort, 1, 4, 1, 256, 2, {1.9f, 2.6
 constexpr MfmaForm kBigForm = {kMfmaBig, 4, 2, 2, 256, 1, {}, {}};   // (taken by rule, see choose_mfma)
 constexpr float kWorkgroupStart = 5.0f;   // us before a workgroup's first step and after its last
 constexpr int kCUs = 256;
-constexpr long long kChunkRecordBytes = 512ll << 20;   // what a prefill chunk's records may take (see choose_mfma)
+
+// What a plan's records may take: 512 MB, or what one round of 128-row workgroups, or `rows` query rows with a single key
+// split, leave if that is more.  (Without a limit a plan took gigabytes for a few per cent: 8 x 100 tokens over 16384
+// keys of an 80-layer model 4.7 GB in 64 splits.)
+long long record_limit(const krul_shape_t *s, long long rows)
+{
+    const long long most = rows > 128ll * kCUs ? rows : 128ll * kCUs, floor = 512ll << 20;
+    return most * s->n_layers * 16 > floor ? most * s->n_layers * 16 : floor;
+}
+// us that records take to be written and read back.  A few of them are still in the caches when they are read and cost
+// next to nothing (117 tokens over 566 keys of 32 heads: 57 us with 10 MB, 66 with the plan that leaves 6), except beside a
+// prefill chunk's uneven splits.
+double record_time(long long bytes, bool chunk)
+{
+    const double free_bytes = chunk ? 0.0 : 32.0 * (1 << 20);
+    return fmax(0.0, (double)bytes - free_bytes) / 5e6;
+}
 
 // Whether the records and the head values of a plan fit the scratch area of krul_pair_similarity_static.
 bool fits_static(const krul_shape_t *s, long long records)
@@ -87,6 +103,7 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys)
 {
     const long long B = s->batch, L = s->n_layers, Hkv = s->n_kv_heads, S = s->n_hist, Tq = s->n_query;
     const long long Rk = s->n_q_heads / Hkv * Tq, d = s->head_dim;
+    const long long limit = record_limit(s, B * Hkv * ceil_div(Rk, 128) * 128);
     const bool single = (s->flags & KRUL_FLAG_SINGLE_SPLIT) != 0, causal = (s->flags & KRUL_FLAG_CAUSAL) != 0;
     const auto splits = [&](const MfmaForm &f, long long want, long long chunks) {
         const long long tiles = ceil_div(S, f.kt), n = want < 1 || single ? 1 : (want < tiles ? want : tiles);
@@ -107,13 +124,14 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys)
         const MfmaForm &f = big ? kBigForm : kWideForm;
         const long long nrt = ceil_div(Rk, f.rows()), want = ceil_div(kCUs, B * Hkv * nrt);
         // (Not a prefill chunk on keys in place whose records at one tile per split stay small: see below.)
-        const bool chunk = causal && !plain_keys && Tq > f.rows() && B * Hkv * nrt * tiles * L * f.rows() * 16 <= kChunkRecordBytes;
+        const bool chunk = causal && !plain_keys && Tq > f.rows() && B * Hkv * nrt * tiles * L * f.rows() * 16 <= limit;
         if (big || (nrt % 8 == 0 && tiles >= 16 && want <= 4 && !chunk))
             return splits(f, want < 4 && tiles >= 16 && nrt % 8 == 0 ? 4 : want, 1);
     }
 
     MfmaChoice best = {nullptr, 0, 0, 0};
     double best_t = 0.0;
+    long long best_bytes = 0;
     bool best_fits = false;
     const auto consider = [&](const MfmaForm &f, long long want, long long chunks) {
         const MfmaChoice c = splits(f, want, chunks);
@@ -122,14 +140,16 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys)
         const double slots = (double)kCUs * f.resident, n_wg = (double)(n_splits_all * chunks);
         const double steps = (double)(c.tiles_per_split * (ceil_div(L - 1, chunks) + 1));
         const double layers_read = (double)(L - 1 + chunks);
-        double t_steps = ceil(n_wg / slots) * (steps * f.step[d > 64] + kWorkgroupStart), t_records = 0.0;
-        if (causal && Tq > f.rows()) {
+        const long long record_bytes = n_splits_all * L * f.rows() * 16;
+        double t_steps = ceil(n_wg / slots) * (steps * f.step[d > 64] + kWorkgroupStart);
+        const bool chunk = causal && Tq > f.rows();
+        if (chunk) {
             // The tiles right of a row tile's diagonal are not walked and splits without a tile left stop at once.  Row
             // tiles see S - Tq/2 + rows/2 keys on average.  Splits of one tile are alike and come in rounds; longer
             // ones differ, so the last of them run beside idle CUs for about half a split.  One tile per split
             // measured best or near it (32/8 heads of 128, against the plan without this: 651 tokens over 1623 keys 721
             // -> 564 us, 1888 over 2707 2450 -> 1890, 700 over 16000 5990 -> 4990; 512 over 3575, where two splits make
-            // one even round, 777 against 799) but pays for its records.
+            // one even round, 777 against 799).
             const double tiles_seen = fmin((double)ceil_div(S, f.kt), ((double)S - 0.5 * (double)(Tq - f.rows())) / f.kt + 0.5);
             const double live = (double)(B * Hkv * nrt * chunks) * (c.n_split > 1 ? fmin((double)c.n_split, tiles_seen / (double)c.tiles_per_split + (c.tiles_per_split > 1 ? 0.5 : 0.0)) : 1.0);
             const double tile_steps = (double)(ceil_div(L - 1, chunks) + 1) * f.step[d > 64];
@@ -140,34 +160,35 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys)
             // (the short forms over several tiles: 4 x 200 tokens over 300 keys of 32 heads 264 us, 229 in 256-key tiles)
             if (c.tiles_per_split > 1 && f.kt <= 128) t_steps *= 1.2;
             if (chunks > 1) t_steps *= 1.25;   // (600 tokens over 700 keys: 247 us in two chunks, 241 in one)
-            t_records = (double)(n_splits_all * L * f.rows()) * 16.0 / 5e6;
         }
         // (idle places draw no keys: the stream is up to 15 % slower)
         const double bytes = (double)(B * d * 2) * (double)(Hkv * S + s->n_q_heads * Tq) * layers_read;
         const double t_stream = bytes / (f.stream[d > 64] * 1e6 * fmin(1.0, 0.85 + 0.15 * n_wg / slots)) + kWorkgroupStart;
         // (slim tiles have next to nothing to do but wait for keys; the others' steps hide most of the stream)
-        const double t = fmax(t_steps, t_stream) + t_records + (Rk > 32 ? 0.1 * fmin(t_steps, t_stream) : 0.0);
+        const double t = fmax(t_steps, t_stream) + record_time(record_bytes, chunk) + (Rk > 32 ? 0.1 * fmin(t_steps, t_stream) : 0.0);
         // A plan whose workspace fits krul_pair_similarity_static's area wins over one whose does not: that call
-        // takes every shape that has one, and gives the same bits as the call with a workspace.  (It takes dense keys only;
-        // a prefill chunk on keys in place may keep up to 512 MB of records.)
-        const bool in_place_chunk = !plain_keys && causal && Tq > f.rows();
-        if (in_place_chunk && best.form && n_splits_all * L * f.rows() * 16 > kChunkRecordBytes) return;
-        const bool fits = in_place_chunk || fits_static(s, n_splits_all * L * f.rows());
-        if (!best.form || (fits && !best_fits) || (fits == best_fits && t < best_t)) {
+        // takes every shape that has one, and gives the same bits as the call with a workspace.  (It takes dense keys only.)
+        // Then the fastest within the limit on records; where none is, the one with the fewest.
+        const bool fits = (!plain_keys && chunk) || fits_static(s, n_splits_all * L * f.rows());
+        const bool better = record_bytes <= limit ? best_bytes > limit || t < best_t : best_bytes > limit && record_bytes < best_bytes;
+        if (!best.form || (fits && !best_fits) || (fits == best_fits && better)) {
             best = c;
             best_t = t;
+            best_bytes = record_bytes;
             best_fits = fits;
         }
     };
     const auto consider_form = [&](const MfmaForm &f) {
         const long long tiles = ceil_div(S, f.kt), nrt = ceil_div(Rk, f.rows()), units = B * Hkv * nrt;
         const long long slots = (long long)kCUs * f.resident;
-        // Splits of several tiles for a round, two or three -- not where the stream of keys is the bound: a split of
+        // Splits of several tiles for a round, or up to eight (seven rounds of 8 x 100 tokens over 16384 keys of an 80-layer model
+        // come out even, one to three do not: 30.5 ms against 34.6; a prefill chunk's splits are uneven by themselves: up to
+        // three) -- not where the stream of keys is the bound: a split of
         // several tiles parks its running records in memory between tiles, and that cost a quarter of the bandwidth
         // (a decode step over 131072 tokens: 57 % of 8 TB/s against 74 % with one tile per split) -- then one tile per
         // split and the layers in chunks.
         if (Rk > 64)
-            for (int r = 1; r <= 3 && slots * r / units < tiles; ++r) consider(f, slots * r / units, 1);
+            for (int r = 1; r <= (causal && Tq > f.rows() ? 3 : 8) && slots * r / units < tiles; ++r) consider(f, slots * r / units, 1);
         const long long most = tiles < 1024 ? tiles : 1024;
         consider(f, most, 1);
         if (most < tiles || single || &f == &kSlimDeepForm) return;   // (the deep ring takes too long to fill for a piece of the chain)
@@ -231,10 +252,12 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys)
         y.variant = kF32;
         y.wr = y.wk = y.rb = 1;
         const long long tiles = ceil_div(S, 128), ks = ceil_div(s->head_dim, 16);
-        long long best_ns = 1, best_nl = 1;
+        const int rb_most = Rk > 32 && s->head_dim <= 128 ? 2 : 1;
+        const long long limit = record_limit(s, B * Hkv * ceil_div(Rk, 32 * rb_most) * 32 * rb_most);
+        long long best_ns = 1, best_nl = 1, best_bytes = 0;
         double best_t = 0.0;
         bool best_fits = false;
-        for (int rb = 1; rb <= (Rk > 32 && s->head_dim <= 128 ? 2 : 1); ++rb) {
+        for (int rb = 1; rb <= rb_most; ++rb) {
             const long long nrt = ceil_div(Rk, 32 * rb), units = B * Hkv * nrt;
             // us per step for one workgroup a CU and for two, measured at head_dim 128
             const double step1 = rb == 1 ? 2.2 : 3.2, step2 = (rb == 1 ? 2.9 : 4.4) * (0.3 + 0.7 * (double)ks / 8.0);
@@ -242,13 +265,17 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys)
                 const long long tps = ceil_div(tiles, ns);
                 if ((s->flags & KRUL_FLAG_SINGLE_SPLIT) && ns > 1) return;
                 const double n = (double)(units * ceil_div(tiles, tps) * nl), steps = (double)(tps * (ceil_div(L - 1, nl) + 1));
-                const double t = n <= kCUs ? steps * fmin(step1, step2) + 4.0 : ceil(n / (2 * kCUs)) * (steps * step2 + 4.0);
-                const bool fits = fits_static(s, units * ceil_div(tiles, tps) * L * 32 * rb);   // (preferred, as in choose_mfma)
-                if (best_t == 0.0 || (fits && !best_fits) || (fits == best_fits && t < best_t)) {
+                const long long records_n = units * ceil_div(tiles, tps) * L * 32 * rb, bytes = records_n * 16;
+                const double t = (n <= kCUs ? steps * fmin(step1, step2) + 4.0 : ceil(n / (2 * kCUs)) * (steps * step2 + 4.0)) +
+                                 record_time(bytes, false);
+                const bool fits = fits_static(s, records_n);   // (preferred, then the limit on records, as in choose_mfma)
+                const bool better = bytes <= limit ? best_bytes > limit || t < best_t : best_bytes > limit && bytes < best_bytes;
+                if (best_t == 0.0 || (fits && !best_fits) || (fits == best_fits && better)) {
                     y.rb = rb;
                     best_ns = ceil_div(tiles, tps);
                     best_nl = nl;
                     best_t = t;
+                    best_bytes = bytes;
                     best_fits = fits;
                 }
             };
