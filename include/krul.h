@@ -106,12 +106,13 @@ int krul_pair_similarity(const krul_shape_t *shape, const void *q, const void *k
 /*
  * krul_pair_similarity for callers that cannot provide a workspace because they cannot allocate device
  * memory where they stand: code recorded into a HIP graph, tight serving loops, harnesses that forbid
- * hipMalloc.  Same arguments without the workspace, same results bit for bit.  The scratch memory is a
- * fixed area of KRUL_STATIC_SCRATCH_BYTES that the library's code object holds on every GPU it is loaded
+ * hipMalloc.  Same arguments without the workspace, and the same results: bit for bit where
+ * krul_pair_similarity_workspace() is at most KRUL_STATIC_SCRATCH_BYTES; where it is more the call with a workspace may
+ * split the keys otherwise, and the results agree to rounding.  The scratch memory is a fixed area of KRUL_STATIC_SCRATCH_BYTES that the library's code object holds on every GPU it is loaded
  * on until the process ends; the call allocates nothing and frees nothing.
  *
- *   - Shapes whose plan on dense keys needs more than KRUL_STATIC_SCRATCH_BYTES (krul_pair_similarity_workspace() is never
- *     less than what it needs) are refused with KRUL_ESCRATCH (nothing enqueued).  40 MiB holds every few-query and decode-step shape of the
+ *   - Shapes of which no way to split the work fits KRUL_STATIC_SCRATCH_BYTES are refused with KRUL_ESCRATCH (nothing
+ *     enqueued).  40 MiB holds every few-query and decode-step shape of the
  *     Llama-3-8B kind (64 query tokens over 4096 keys: 16 MiB; one token over 131072 keys: 32 MiB); the
  *     many-query shapes need hundreds of MiB and take krul_pair_similarity with a workspace.
  *   - The stream must belong to the CURRENT device.  The first call on a device looks up the area's

@@ -74,12 +74,12 @@ double record_time(long long bytes, bool chunk)
     return fmax(0.0, (double)bytes - free_bytes) / 5e6;
 }
 
-// Whether the records and the head values of a plan fit the scratch area of krul_pair_similarity_static.
-bool fits_static(const krul_shape_t *s, long long records)
+// What the scratch area of krul_pair_similarity_static leaves for records beside the head values (whole multiples of
+// kAlign; not positive: nothing).
+long long static_limit(const krul_shape_t *s)
 {
-    return round_up((size_t)records * sizeof(float4), kAlign) +
-               2 * round_up((size_t)s->batch * (s->n_layers - 1) * s->n_q_heads * sizeof(float), kAlign) <=
-           (size_t)KRUL_STATIC_SCRATCH_BYTES;
+    return (long long)KRUL_STATIC_SCRATCH_BYTES -
+           2 * (long long)round_up((size_t)s->batch * (s->n_layers - 1) * s->n_q_heads * sizeof(float), kAlign);
 }
 
 struct MfmaChoice {
@@ -99,11 +99,15 @@ struct MfmaChoice {
 //     empty (3 x 40 tokens over 3000 keys 404 -> 297 us);
 //   - for more than 64 rows the 64-row shape where 128-row tiles would leave much of the last one empty (the same
 //     example in 64-row tiles: 253 us).
-MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys)
+//
+// in_static: for krul_pair_similarity_static.  Its limit on records is the library's own area, so it takes the plan of the
+// call with a workspace where that fits, and the fastest that fits where it does not.  (Preferred in every call, such
+// plans cost 2 x 129 tokens over 7967 keys of an 80-layer model a third of its speed: 144 workgroups on 256 CUs.)
+MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static)
 {
     const long long B = s->batch, L = s->n_layers, Hkv = s->n_kv_heads, S = s->n_hist, Tq = s->n_query;
     const long long Rk = s->n_q_heads / Hkv * Tq, d = s->head_dim;
-    const long long limit = record_limit(s, B * Hkv * ceil_div(Rk, 128) * 128);
+    const long long limit = in_static ? static_limit(s) : record_limit(s, B * Hkv * ceil_div(Rk, 128) * 128);
     const bool single = (s->flags & KRUL_FLAG_SINGLE_SPLIT) != 0, causal = (s->flags & KRUL_FLAG_CAUSAL) != 0;
     const auto splits = [&](const MfmaForm &f, long long want, long long chunks) {
         const long long tiles = ceil_div(S, f.kt), n = want < 1 || single ? 1 : (want < tiles ? want : tiles);
@@ -132,7 +136,6 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys)
     MfmaChoice best = {nullptr, 0, 0, 0};
     double best_t = 0.0;
     long long best_bytes = 0;
-    bool best_fits = false;
     const auto consider = [&](const MfmaForm &f, long long want, long long chunks) {
         const MfmaChoice c = splits(f, want, chunks);
         if (chunks > 1 && c.tiles_per_split > 1) return;
@@ -166,16 +169,11 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys)
         const double t_stream = bytes / (f.stream[d > 64] * 1e6 * fmin(1.0, 0.85 + 0.15 * n_wg / slots)) + kWorkgroupStart;
         // (slim tiles have next to nothing to do but wait for keys; the others' steps hide most of the stream)
         const double t = fmax(t_steps, t_stream) + record_time(record_bytes, chunk) + (Rk > 32 ? 0.1 * fmin(t_steps, t_stream) : 0.0);
-        // A plan whose workspace fits krul_pair_similarity_static's area wins over one whose does not: that call
-        // takes every shape that has one, and gives the same bits as the call with a workspace.  (It takes dense keys only.)
-        // Then the fastest within the limit on records; where none is, the one with the fewest.
-        const bool fits = (!plain_keys && chunk) || fits_static(s, n_splits_all * L * f.rows());
-        const bool better = record_bytes <= limit ? best_bytes > limit || t < best_t : best_bytes > limit && record_bytes < best_bytes;
-        if (!best.form || (fits && !best_fits) || (fits == best_fits && better)) {
+        // The fastest within the limit on records; where none is, the one with the fewest.
+        if (!best.form || (record_bytes <= limit ? best_bytes > limit || t < best_t : best_bytes > limit && record_bytes < best_bytes)) {
             best = c;
             best_t = t;
             best_bytes = record_bytes;
-            best_fits = fits;
         }
     };
     const auto consider_form = [&](const MfmaForm &f) {
@@ -214,7 +212,7 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys)
 
 }  // namespace
 
-int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys)
+int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bool in_static)
 {
     const int rc = check_shape(s);
     if (rc != KRUL_OK) return rc;
@@ -234,7 +232,7 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys)
                       !(s->flags & KRUL_FLAG_GENERIC_KERNEL);
     long long n_wg, records;
     if (mfma) {
-        const MfmaChoice ch = choose_mfma(s, want_ir, plain_keys);
+        const MfmaChoice ch = choose_mfma(s, want_ir, plain_keys, in_static);
         const MfmaForm &f = *ch.form;
         y.variant = f.variant;
         y.wr = f.wr;
@@ -253,10 +251,9 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys)
         y.wr = y.wk = y.rb = 1;
         const long long tiles = ceil_div(S, 128), ks = ceil_div(s->head_dim, 16);
         const int rb_most = Rk > 32 && s->head_dim <= 128 ? 2 : 1;
-        const long long limit = record_limit(s, B * Hkv * ceil_div(Rk, 32 * rb_most) * 32 * rb_most);
+        const long long limit = in_static ? static_limit(s) : record_limit(s, B * Hkv * ceil_div(Rk, 32 * rb_most) * 32 * rb_most);
         long long best_ns = 1, best_nl = 1, best_bytes = 0;
         double best_t = 0.0;
-        bool best_fits = false;
         for (int rb = 1; rb <= rb_most; ++rb) {
             const long long nrt = ceil_div(Rk, 32 * rb), units = B * Hkv * nrt;
             // us per step for one workgroup a CU and for two, measured at head_dim 128
@@ -265,18 +262,15 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys)
                 const long long tps = ceil_div(tiles, ns);
                 if ((s->flags & KRUL_FLAG_SINGLE_SPLIT) && ns > 1) return;
                 const double n = (double)(units * ceil_div(tiles, tps) * nl), steps = (double)(tps * (ceil_div(L - 1, nl) + 1));
-                const long long records_n = units * ceil_div(tiles, tps) * L * 32 * rb, bytes = records_n * 16;
+                const long long bytes = units * ceil_div(tiles, tps) * L * 32 * rb * 16;
                 const double t = (n <= kCUs ? steps * fmin(step1, step2) + 4.0 : ceil(n / (2 * kCUs)) * (steps * step2 + 4.0)) +
                                  record_time(bytes, false);
-                const bool fits = fits_static(s, records_n);   // (preferred, then the limit on records, as in choose_mfma)
-                const bool better = bytes <= limit ? best_bytes > limit || t < best_t : best_bytes > limit && bytes < best_bytes;
-                if (best_t == 0.0 || (fits && !best_fits) || (fits == best_fits && better)) {
+                if (best_t == 0.0 || (bytes <= limit ? best_bytes > limit || t < best_t : best_bytes > limit && bytes < best_bytes)) {   // (as in choose_mfma)
                     y.rb = rb;
                     best_ns = ceil_div(tiles, tps);
                     best_nl = nl;
                     best_t = t;
                     best_bytes = bytes;
-                    best_fits = fits;
                 }
             };
             for (long long nl = 1; nl <= L - 1 && nl <= 31; ++nl) {
@@ -410,10 +404,10 @@ int run_similarity(const krul_shape_t *shape, const void *q, const void *k, floa
                    uint8_t *eligible, void *workspace, size_t workspace_bytes, void *stream,
                    void *event_begin, void *event_end, bool accumulate = false,
                    const krul_k_layout_t *kl = nullptr, const krul_k_pages_t *kp = nullptr,
-                   const SelectArgs *sel = nullptr)
+                   const SelectArgs *sel = nullptr, bool in_static = false)
 {
     Plan pl;
-    const int rc = make_plan(shape, &pl, ir, k != nullptr && !kl && !kp);
+    const int rc = make_plan(shape, &pl, ir, k != nullptr && !kl && !kp, in_static);
     if (rc != KRUL_OK) return rc;
     if (!q || (accumulate ? !head_score : !pair_score)) return KRUL_EINVAL;
     if (ir && (shape->flags & KRUL_FLAG_CAUSAL)) return KRUL_EUNSUPPORTED;
@@ -574,7 +568,7 @@ int krul_pair_similarity_static(const krul_shape_t *shape, const void *q, const 
                                 float *pair_score, float *head_score, float *pair_dist, void *stream)
 {
     Plan pl;
-    const int rc = make_plan(shape, &pl, false, true);
+    const int rc = make_plan(shape, &pl, false, true, true);
     if (rc != KRUL_OK) return rc;
     if (pl.total_bytes > (size_t)KRUL_STATIC_SCRATCH_BYTES) return KRUL_ESCRATCH;
     void *ptr = nullptr;
@@ -583,7 +577,7 @@ int krul_pair_similarity_static(const krul_shape_t *shape, const void *q, const 
     // Nothing in the area has to start at zero: every record the finalize kernels read is written by the
     // similarity kernel of the same call first.
     return run_similarity(shape, q, k, pair_score, head_score, pair_dist, false, 0.f, nullptr, nullptr,
-                          ptr, (size_t)KRUL_STATIC_SCRATCH_BYTES, stream, nullptr, nullptr);
+                          ptr, (size_t)KRUL_STATIC_SCRATCH_BYTES, stream, nullptr, nullptr, false, nullptr, nullptr, nullptr, true);
 }
 
 int krul_pair_similarity_strided(const krul_shape_t *shape, const void *q, const krul_k_layout_t *k_layout,

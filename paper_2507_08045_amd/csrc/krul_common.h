@@ -70,7 +70,8 @@ struct Plan {
 // krul_status_t.
 // plain_keys: the keys are dense and no mask or Initial-Recent test is asked for -- what the many-query kernel
 // (kMfmaBig) takes; the plan (and so the workspace) may differ with it.
-int make_plan(const krul_shape_t *s, Plan *plan, bool want_ir = false, bool plain_keys = false);
+// in_static: a plan for the scratch area of krul_pair_similarity_static, if there is one that fits it.
+int make_plan(const krul_shape_t *s, Plan *plan, bool want_ir = false, bool plain_keys = false, bool in_static = false);
 
 struct SimParams {
     const void *q;

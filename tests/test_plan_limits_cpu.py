@@ -49,3 +49,12 @@ def test_named_workspaces():
         return kr.workspace_bytes(kr.KrulShape(B, L, Hq, Hkv, 128, S, Tq, kr.KRUL_BF16, 0.0, 0))
     assert need(8, 80, 64, 8, 16384, 100) < 400 << 20
     assert need(1, 80, 64, 8, 32768, 700) < 520 << 20
+
+
+def test_plans_do_not_obey_the_static_areas_size():
+    """A call with a workspace fills the chip whether or not its plan would fit krul_pair_similarity_static's 40 MB."""
+    def plan(B, L, Hq, Hkv, S, Tq):
+        return kr.plan(kr.KrulShape(B, L, Hq, Hkv, 128, S, Tq, kr.KRUL_BF16, 0.0, 0))
+    assert plan(2, 80, 64, 8, 7967, 129)["n_workgroups"] >= 256      # (not one key split in 144)
+    assert plan(8, 80, 64, 8, 16384, 16)["form"] == 1                # 128 x 256: 5.28 ms, in 64 x 512 tiles 5.55
+    assert plan(2, 32, 32, 8, 204, 1249)["form"] == 1                # 128 x 256: 334 us, in 64 x 128 tiles 420
