@@ -230,7 +230,8 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
     // zero-padded to the next of the two inside LDS)
     const bool mfma = (s->dtype == KRUL_BF16 || s->dtype == KRUL_F16) && s->head_dim <= 128 &&
                       !(s->flags & KRUL_FLAG_GENERIC_KERNEL);
-    long long n_wg, records;
+    bool generic = (s->flags & KRUL_FLAG_GENERIC_KERNEL) != 0;
+    long long n_wg = 0, records = 0;
     if (mfma) {
         const MfmaChoice ch = choose_mfma(s, want_ir, plain_keys, in_static);
         const MfmaForm &f = *ch.form;
@@ -245,7 +246,7 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
         const long long n_splits_all = B * Hkv * y.n_row_tiles * ch.n_split;
         n_wg = n_splits_all * ch.n_chunks;
         records = n_splits_all * L * f.rows();
-    } else if (!(s->flags & KRUL_FLAG_GENERIC_KERNEL)) {
+    } else if (!generic) {
         // float32 inputs and larger heads: tiles of 32 or 64 rows x 128 keys
         y.variant = kF32;
         y.wr = y.wk = y.rb = 1;
@@ -291,7 +292,11 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
         n_wg = units * best_ns;
         records = n_wg * L * 32 * y.rb;
         n_wg *= best_nl;
-    } else {
+        // The portable kernel keeps records of the rows there are, without the padding to 32: what fits the static area with
+        // it alone (one token of many conversations with a kv head per query head) runs, slower.
+        generic = in_static && best_bytes > limit;
+    }
+    if (generic) {
         y.variant = kGeneric;
         y.wr = y.wk = y.rb = 1;
         y.n_row_tiles = 1;

@@ -58,3 +58,13 @@ def test_plans_do_not_obey_the_static_areas_size():
     assert plan(2, 80, 64, 8, 7967, 129)["n_workgroups"] >= 256      # (not one key split in 144)
     assert plan(8, 80, 64, 8, 16384, 16)["form"] == 1                # 128 x 256: 5.28 ms, in 64 x 512 tiles 5.55
     assert plan(2, 32, 32, 8, 204, 1249)["form"] == 1                # 128 x 256: 334 us, in 64 x 128 tiles 420
+
+
+def test_static_call_takes_what_the_portable_kernel_fits():
+    """64 conversations x one token of 40 heads, 80 layers: 5 MB of records without the float32 kernel's padding to 32 rows, 105
+    MB with it.  (The queries are misaligned: past the plan the call is refused before any GPU work.)"""
+    import ctypes
+    shp = kr.KrulShape(64, 80, 40, 40, 128, 1000, 1, kr.KRUL_F32, 0.0, 0)
+    vp = ctypes.c_void_p
+    rc = kr.lib().krul_pair_similarity_static(ctypes.byref(shp), vp(0x1008), vp(0x2000), vp(0x3000), None, None, None)
+    assert rc in (kr.KRUL_EINVAL, kr.KRUL_ELAUNCH), rc   # (without a GPU the scratch area is not found)

@@ -57,3 +57,19 @@ def test_static_scratch_refuses_large_shapes():
     with pytest.raises(kr.KrulError) as ei:
         kr.pair_similarity_static(q, k, _outs(B, L, Hq))
     assert ei.value.status == kr.KRUL_ESCRATCH
+
+
+def test_static_scratch_with_many_conversations_in_float32(oracle):
+    """One token of many conversations, a kv head per query head: padded to the float32 kernel's 32 rows the records would not fit; the
+    portable kernel's do."""
+    import gpu_util as G
+    import paper_2507_08045_amd as kr
+    w = workloads.make("na-portable", B=40, L=80, Hq=40, Hkv=40, d=8, S=9, Tq=1, dtype="f32", rho_k=0.7, seed=74)
+    q, k = G.to_device(w)
+    assert w.B * w.Hkv * w.L * 32 * 16 > kr.KRUL_STATIC_SCRATCH_BYTES
+    o = _outs(w.B, w.L, w.Hq)
+    kr.pair_similarity_static(q, k, o)
+    torch.cuda.synchronize()
+    want = oracle.pair_similarity(w.q, w.k)
+    for name in ("pair_score", "head_score", "pair_dist"):
+        G.assert_close(o[name].cpu().numpy(), want[name], 5e-6, f"static, portable kernel: {name}")   # float32 sums of 8 and 9 terms
