@@ -4,9 +4,11 @@
 // Float32 logits on the bfloat16 matrix cores.  v_mfma_f32_32x32x2_f32 runs at 1/16 of the 16-bit rate and, measured,
 // shares its unit with the vector instructions (two of them per MFMA: 155 -> 135 TFLOP/s, nothing overlaps).  Instead
 // each operand is split into three bfloat16 of 8 bits each -- x = h + m + l, exactly: 24 bits -- and a product is
-// hh + (hm + mh + mm + hl + lh), six bfloat16 MFMAs with float32 sums.  What is left out (ml + lm + ll) is at most
-// 2^-23 of the product; the sum over 128 elements in float32 arithmetic rounds by several times that.  (One row
-// block to a wave: the large terms and the small ones have an accumulator each.)
+// hh + (hm + mh + mm + hl + lh), six bfloat16 MFMAs with float32 sums.  What is left out is ml + lm + ll.  h is x cut off
+// after 8 bits (nothing overflows), m the rest rounded to 8 bits, so l has either sign: |m| <= 2^-7 and |l| <= 2^-16 for x in
+// [1, 2), and the products of 1 <= x, y < 2 miss at most 2^-22, as often too much as too little.  (With m cut off as well
+// |l| reaches 2^-15, always with x's sign: every product came out too small, by up to 2^-21.)  The sum over 128 elements in float32
+// arithmetic rounds by several times that.  (One row block to a wave: the large terms and the small ones have an accumulator each.)
 //
 // What bounds it.  32 keys x 32 rows at head_dim 128 are 48 MFMAs of 32 cycles; splitting the keys takes 352 vector
 // instructions per 32 keys of a wave, the exponentials, the share in the query rows' split and the sums some 250 per
@@ -33,6 +35,8 @@ namespace {
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 constexpr int kWaves = 4, kThreads = kWaves * 64, kTileKeys = kWaves * 32;
@@ -46,13 +50,14 @@ template <> struct Elem8<float> {
     __device__ void split_pair(int i, u32x4 (&o)[3]) const   // elements 2i and 2i + 1
     {
         float x = i < 2 ? a[2 * i] : b[2 * i - 4], y = i < 2 ? a[2 * i + 1] : b[2 * i - 3];
-#pragma unroll
-        for (int pl = 0; pl < 3; ++pl) {
-            const unsigned ux = __float_as_uint(x), uy = __float_as_uint(y);
-            o[pl][i] = __builtin_amdgcn_perm(uy, ux, 0x07060302);   // the upper halves: the leading 8 bits
-            x -= __uint_as_float(ux & 0xFFFF0000u);                 // (exact)
-            y -= __uint_as_float(uy & 0xFFFF0000u);
-        }
+        const auto upper_halves = [](float u, float v) { return __builtin_amdgcn_perm(__float_as_uint(v), __float_as_uint(u), 0x07060302); };
+        o[0][i] = upper_halves(x, y);
+        x -= __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);   // (exact)
+        y -= __uint_as_float(__float_as_uint(y) & 0xFFFF0000u);
+        o[1][i] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{x, y}), bf16x2));   // (to nearest)
+        x -= __uint_as_float(o[1][i] << 16);                      // (exact, and of 8 bits)
+        y -= __uint_as_float(o[1][i] & 0xFFFF0000u);
+        o[2][i] = upper_halves(x, y);
     }
 };
 template <> struct Elem8<uint16_t> {

@@ -68,3 +68,27 @@ def test_causal_whole_prompt_f32(oracle):
     q, k = G.to_device(w)
     got, want = G.gpu_scores(q, k, flags=kr.KRUL_FLAG_CAUSAL), oracle.pair_similarity(w.q, w.k, causal=True)
     G.assert_close(got["head_score"], want["head_score"], TOL32, "causal head_score")
+
+
+def test_logits_are_not_biased():
+    """Elements whose third plane would always have the operand's sign if the planes were cut off instead of rounded: every product
+    then misses 2^-21 of itself, and the logit of eight of them four units of its last place.  Rounding alone -- the small terms' sum, its
+    addition to the large one's, the scaling, half a unit each at most -- can move the difference of the two logits by less than half of that."""
+    import math
+    import paper_2507_08045_amd as kr
+    x = 1.0 + 2.0 ** -7 - 2.0 ** -23
+    scale = 2.0 ** 17
+    q = torch.full((1, 2, 1, 1, 8), x, device="cuda")
+    k = torch.ones((1, 2, 1, 2, 8), device="cuda")
+    k[0, 0, 0, 0] = x                                     # layer 0, key 0: eight products x * x
+    k[0, 0, 0, 1, :4] = 1.0 + 2.0 ** -6                   # key 1: a sum close to it of products without a third plane
+    k[0, 1, 0, 1] = -1.0                                  # layer 1: all weight on key 0
+    out = kr.pair_similarity(q, k, scale=scale)
+    torch.cuda.synchronize()
+    cos = out["pair_score"].item()                        # of (p0, 1 - p0) and (1, 0)
+    log2_ratio = math.log2(cos / math.sqrt(1.0 - cos * cos))
+    c = scale * math.log2(math.e)
+    want = c * 8 * x * (x - 1.0 - 2.0 ** -7)
+    ulp = 2.0 ** -20                                      # of a logit between 8 and 16
+    rounding = 2 * c * ulp * 0.5 + 2 * 0.5 * 2.0 ** -3    # (two logits: the addition, and the scaled value between 2^20 and 2^21)
+    assert abs(log2_ratio - want) <= rounding + 1e-3, (log2_ratio, want, rounding)
