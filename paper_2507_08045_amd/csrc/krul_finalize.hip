@@ -33,7 +33,8 @@ __device__ inline float block_sum(float v, float *red)
 }
 
 // Running merge of partial records of one row for a layer pair (a = layer l, b = l+1):
-// exponents Ma, Mb; Z and N2 of both layers and the cross term C, all relative to them.
+// exponents Ma, Mb; Z and N2 of both layers and the cross term C, all relative to them.  (exp2f, not the bare instruction: a
+// sum all of whose terms lie 2^126 to 2^149 below the row's largest exponential is subnormal, not zero.)
 struct RowAcc {
     float Ma, Za, Na, Mb, Zb, Nb, C;
 };
@@ -41,8 +42,8 @@ struct RowAcc {
 __device__ inline void merge_into(RowAcc &r, float ma, float za, float na, float mb, float zb, float nb, float c)
 {
     const float Ma = fmaxf(r.Ma, ma), Mb = fmaxf(r.Mb, mb);
-    const float fa0 = __builtin_amdgcn_exp2f(r.Ma - Ma), fa1 = __builtin_amdgcn_exp2f(ma - Ma);
-    const float fb0 = __builtin_amdgcn_exp2f(r.Mb - Mb), fb1 = __builtin_amdgcn_exp2f(mb - Mb);
+    const float fa0 = exp2f(r.Ma - Ma), fa1 = exp2f(ma - Ma);
+    const float fb0 = exp2f(r.Mb - Mb), fb1 = exp2f(mb - Mb);
     r.Za = r.Za * fa0 + za * fa1;
     r.Na = r.Na * (fa0 * fa0) + na * (fa1 * fa1);
     r.Zb = r.Zb * fb0 + zb * fb1;
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
                     for (int i = 0; i < kBatch; ++i) {
                         if (p0 + i * p.G >= P) continue;
                         const float Mn = fmaxf(M, am[i]);
-                        const float f0 = __builtin_amdgcn_exp2f(M - Mn), f1 = __builtin_amdgcn_exp2f(am[i] - Mn);
+                        const float f0 = exp2f(M - Mn), f1 = exp2f(am[i] - Mn);
                         Z = Z * f0 + az[i] * f1;
                         I = I * f0 + ai[i] * f1;
                         M = Mn;
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
             for (int off = 32; off >= RW; off >>= 1) {
                 const float m2 = __shfl_xor(M, off, 64), z2 = __shfl_xor(Z, off, 64), i2 = __shfl_xor(I, off, 64);
                 const float Mn = fmaxf(M, m2);
-                const float f0 = __builtin_amdgcn_exp2f(M - Mn), f1 = __builtin_amdgcn_exp2f(m2 - Mn);
+                const float f0 = exp2f(M - Mn), f1 = exp2f(m2 - Mn);
                 Z = Z * f0 + z2 * f1;
                 I = I * f0 + i2 * f1;
                 M = Mn;
