@@ -83,6 +83,7 @@ struct HeadsArgs {
     int want_dist, accumulate;
     int n_items;   // (conversation, pair, head) triples; the (conversation, layer, head) triples of the layer test follow
     int n_all;
+    int first;     // of this launch
     float *head_cos, *head_dist, *head_ir;
 };
 
@@ -121,7 +122,7 @@ template <bool PER_WAVE, bool IR>
 __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
 {
     __shared__ float red[kThreads / 64];
-    int item = PER_WAVE ? blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6) : blockIdx.x;
+    int item = p.first + (PER_WAVE ? blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6) : blockIdx.x);
     if (PER_WAVE && item >= p.n_all) return;   // (a whole wave: no barrier follows in this form)
     const bool first = (PER_WAVE ? threadIdx.x & 63 : threadIdx.x) == 0;
     const int P = p.lay.partials;
@@ -218,7 +219,8 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
 }
 
 struct PairsArgs {
-    int n_pairs, n_layers;   // of all conversations; n_layers 0 without the layer test
+    unsigned n_pairs, n_layers;   // of all conversations; n_layers 0 without the layer test
+    unsigned first;               // of this launch
     int Hq;
     float scale;             // of the head values: 1 for means, 1/tokens for running sums
     const float *head_cos, *head_dist, *head_ir;
@@ -233,7 +235,7 @@ struct PairsArgs {
 // test, with the test against gamma
 __global__ __launch_bounds__(kThreads) void finalize_pairs_kernel(PairsArgs a)
 {
-    int i = (blockIdx.x * kThreads + threadIdx.x) >> 5;
+    unsigned i = a.first + blockIdx.x * (kThreads / 32) + (threadIdx.x >> 5);
     const int lane = threadIdx.x & 31;
     if (i >= a.n_pairs + a.n_layers) return;   // (a whole half-wave)
     if (i >= a.n_pairs) {
@@ -254,10 +256,30 @@ __global__ __launch_bounds__(kThreads) void finalize_pairs_kernel(PairsArgs a)
     }
 }
 
-hipError_t launch_pairs(const PairsArgs &a, hipStream_t st)
+constexpr int kMostBlocks = 1 << 22;   // of a launch: HIP numbers at most 2^32 threads
+
+hipError_t launch_pairs(PairsArgs a, hipStream_t st)
 {
-    hipLaunchKernelGGL(finalize_pairs_kernel, dim3((a.n_pairs + a.n_layers + 7) / 8), dim3(kThreads), 0, st, a);
+    constexpr unsigned per_block = kThreads / 32, step = (unsigned)kMostBlocks * per_block;
+    const unsigned n = a.n_pairs + a.n_layers;
+    for (a.first = 0; a.first < n; a.first += step) {
+        const unsigned here = n - a.first < step ? n - a.first : step;
+        hipLaunchKernelGGL(finalize_pairs_kernel, dim3((here + per_block - 1) / per_block), dim3(kThreads), 0, st, a);
+    }
     return hipGetLastError();
+}
+
+template <bool PER_WAVE>
+void launch_heads(HeadsArgs p, bool ir, hipStream_t st)
+{
+    constexpr int per_block = PER_WAVE ? kThreads / 64 : 1, step = kMostBlocks * per_block;
+    for (long long first = 0; first < p.n_all; first += step) {
+        p.first = (int)first;
+        const long long here = p.n_all - first < step ? p.n_all - first : step;
+        const dim3 grid((unsigned)((here + per_block - 1) / per_block));
+        if (ir) hipLaunchKernelGGL((finalize_heads_kernel<PER_WAVE, true>), grid, dim3(kThreads), 0, st, p);
+        else hipLaunchKernelGGL((finalize_heads_kernel<PER_WAVE, false>), grid, dim3(kThreads), 0, st, p);
+    }
 }
 
 }  // namespace
@@ -286,14 +308,11 @@ hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, i
     p.G = 1;
     if (Tq <= 8) {   // few rows: a wave per head, G lanes per row with G * Tq <= 64
         while (p.G * 2 * Tq <= 64 && p.G < lay.partials) p.G <<= 1;
-        const dim3 grid((p.n_all + kThreads / 64 - 1) / (kThreads / 64));
-        if (ir) hipLaunchKernelGGL((finalize_heads_kernel<true, true>), grid, dim3(kThreads), 0, st, p);
-        else hipLaunchKernelGGL((finalize_heads_kernel<true, false>), grid, dim3(kThreads), 0, st, p);
+        launch_heads<true>(p, ir != nullptr, st);
     } else {
         // lanes per row: enough to keep a workgroup's 256 threads busy, at most one per partial
         while (p.G < 64 && p.G * Tq < kThreads && p.G < lay.partials) p.G <<= 1;
-        if (ir) hipLaunchKernelGGL((finalize_heads_kernel<false, true>), dim3(p.n_all), dim3(kThreads), 0, st, p);
-        else hipLaunchKernelGGL((finalize_heads_kernel<false, false>), dim3(p.n_all), dim3(kThreads), 0, st, p);
+        launch_heads<false>(p, ir != nullptr, st);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || accumulate || !pair_cos) return e;   // (no pair scores asked for: the caller forms them)

@@ -25,3 +25,32 @@ def test_mass_far_below_the_largest_exponential(dtype):
     # 2^-149 is 5e-6 of it, and the exponent of a float32 near 130 is known to 2^-17: 1e-4 covers both
     assert torch.all(torch.abs(got / want - 1) <= 1e-4), (got, want)
     assert out["eligible"].cpu().tolist() == [[1, 1]]
+
+
+def test_more_pairs_than_one_launch_numbers():
+    """2^27 pairs and a few: 32 threads for each are more than the 2^32 that a launch can number."""
+    import paper_2507_08045_amd as kr
+    batch, pairs = 2 ** 25 + 1, 4
+    sums = torch.arange(batch * pairs, dtype=torch.int32, device="cuda").remainder_(8191).float().view(batch, pairs, 1)
+    out = kr.pair_scores_from_sums(sums, 2.0)
+    torch.cuda.synchronize()
+    assert torch.equal(out["pair_score"], sums.view(batch, pairs) * 0.5)   # (one head, a power of two: exact)
+
+
+def test_more_heads_than_one_launch_numbers():
+    """Scores and the layer test in one launch: 3 * 5.9 million (layer or pair, head) values are more than 2^24 workgroups."""
+    import paper_2507_08045_amd as kr
+    B, Hq, S, Tq, d = 92001, 64, 4, 9, 8
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q = torch.randn((B, 2, Hq, Tq, d), generator=gen, device="cuda").bfloat16()
+    k = torch.randn((B, 2, 1, S, d), generator=gen, device="cuda").bfloat16()
+    out = kr.pair_similarity_ir(q, k, 0.5)
+    torch.cuda.synchronize()
+    x = torch.matmul(q.float().view(B, 2, Hq * Tq, d), k.float().view(B, 2, S, d).transpose(-1, -2).contiguous()) / math.sqrt(d)
+    p = torch.softmax(x, -1).view(B, 2, Hq, Tq, S)
+    a, r = p[:, 0], p[:, 1]
+    cos = ((a * r).sum(-1) / torch.sqrt((a * a).sum(-1) * (r * r).sum(-1))).mean(-1)
+    mass = p[..., 3].mean((-1, -2))   # T_recent of four keys; T_initial is empty
+    # float32 on both sides, sums of 4 keys and 9 rows
+    assert torch.max(torch.abs(out["head_score"][:, 0] - cos)) <= 1e-5
+    assert torch.max(torch.abs(out["ir_mass"] - mass)) <= 1e-5
