@@ -221,7 +221,8 @@ int krul_pair_similarity_paged(const krul_shape_t *shape, const void *q, const k
  *   head_sum       [B][L-1][Hq] float  device, required, read and written (+=)
  *   head_dist_sum  [B][L-1][Hq] float  device, may be NULL
  *   n_tokens       rows accumulated per head so far (> 0)
- *   pair_score [B][L-1] required; head_score [B][L-1][Hq], pair_dist [B][L-1] may be NULL
+ *   pair_score [B][L-1] required; head_score [B][L-1][Hq], pair_dist [B][L-1] may be NULL;
+ *   head_score may be head_sum (every sum is read before its scaled value is written)
  *   (pair_dist needs head_dist_sum)
  * Calls on one stream are ordered; concurrent calls that share sums race.  Errors as for
  * krul_pair_similarity.

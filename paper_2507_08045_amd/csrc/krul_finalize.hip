@@ -224,7 +224,7 @@ struct PairsArgs {
     int Hq;
     float scale;             // of the head values: 1 for means, 1/tokens for running sums
     const float *head_cos, *head_dist, *head_ir;
-    float *head_out;         // head_cos * scale, or null
+    float *head_out;         // head_cos * scale, or null; may be head_cos
     float *pair_cos, *pair_dist;
     float gamma;
     float *ir_mass;
@@ -246,9 +246,8 @@ __global__ __launch_bounds__(kThreads) void finalize_pairs_kernel(PairsArgs a)
         if (a.eligible) a.eligible[i] = m >= a.gamma ? 1 : 0;   // below gamma: not an Initial-Recent layer, set aside
         return;
     }
-    if (a.head_out)
-        for (int h = lane; h < a.Hq; h += 32) a.head_out[(size_t)i * a.Hq + h] = a.head_cos[(size_t)i * a.Hq + h] * a.scale;
-    const float cs = pair_average(a.head_cos + (size_t)i * a.Hq, a.Hq, a.scale, lane);
+    const float cs = pair_average(a.head_cos + (size_t)i * a.Hq, a.Hq, a.scale, lane,
+                                  a.head_out ? a.head_out + (size_t)i * a.Hq : nullptr);
     if (lane == 0) a.pair_cos[i] = cs;
     if (a.pair_dist) {
         const float ds = pair_average(a.head_dist + (size_t)i * a.Hq, a.Hq, a.scale, lane);

@@ -17,10 +17,15 @@ namespace krul {
 
 // Average of a pair's Hq head values (times scale) by the 32 lanes of a half-wave: lane k takes heads k, k + 32, ... in
 // order, a butterfly adds the lanes' sums.  The one order in which heads are averaged, whichever kernel does it.
-__device__ inline float pair_average(const float *head, int Hq, float scale, int lane)
+// out: the scaled values go there, if anywhere; it may be head (every value is read once).
+__device__ inline float pair_average(const float *head, int Hq, float scale, int lane, float *out = nullptr)
 {
     float s = 0.f;
-    for (int h = lane; h < Hq; h += 32) s += head[h] * scale;
+    for (int h = lane; h < Hq; h += 32) {
+        const float v = head[h] * scale;
+        if (out) out[h] = v;
+        s += v;
+    }
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o, 32);
     return s / (float)Hq;

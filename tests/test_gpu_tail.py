@@ -1,4 +1,5 @@
 """GPU tests of the kernels behind the similarity kernel -- merged records, averages over heads -- at the ends of their ranges."""
+import ctypes
 import math
 
 import pytest
@@ -54,3 +55,17 @@ def test_more_heads_than_one_launch_numbers():
     # float32 on both sides, sums of 4 keys and 9 rows
     assert torch.max(torch.abs(out["head_score"][:, 0] - cos)) <= 1e-5
     assert torch.max(torch.abs(out["ir_mass"] - mass)) <= 1e-5
+
+
+def test_head_scores_in_the_place_of_their_sums():
+    """krul_pair_scores_from_sums with head_score = head_sum: every sum is read once, before its scaled value takes its place."""
+    import paper_2507_08045_amd as kr
+    B, NP, Hq = 3, 5, 70
+    sums = torch.rand((B, NP, Hq), generator=torch.Generator().manual_seed(1)).cuda() * 7.0
+    want = kr.pair_scores_from_sums(sums, 7.0)
+    vp, pair = ctypes.c_void_p, torch.empty((B, NP), device="cuda")
+    rc = kr.lib().krul_pair_scores_from_sums(vp(sums.data_ptr()), None, B, NP + 1, Hq, 7.0, vp(pair.data_ptr()), vp(sums.data_ptr()), None,
+                                             vp(torch.cuda.current_stream().cuda_stream))
+    assert rc == kr.KRUL_OK
+    torch.cuda.synchronize()
+    assert torch.equal(pair, want["pair_score"]) and torch.equal(sums, want["head_score"])
