@@ -559,19 +559,19 @@ __global__ __launch_bounds__(WV * 64) void ap_gram_kernel(APParams p, int ksp, i
 // anew when a lane's sum over a block passes kDirectLimit (a jump of about 20 times the largest so far; 16 keys as large as the
 // largest stay below it).  The rows' Gram matrices are then brought to the new exponents.  The binary16 copies are rounded once (the
 // three-kernel way: again by the factor of their key split), nothing above 2^-22 of a row's largest is a subnormal, and Z is the sum of
-// what is stored, so a row's weights add up to one whatever the rounding: cosines of 2000 keys are within 4e-7 rms of float64
-// (three kernels: 1.1e-6), with 2 % heavy tokens 4e-7 (2.0e-6); distances 6e-7 and 3e-7 of themselves (3.4e-6, 2.2e-6).
+// what is stored, so a row's weights add up to one whatever the rounding.  Errors against float64, geometric means over 30 calls of 24 to
+// 32 layers drawn over the calls' sizes, a third with 2 % heavy tokens (three kernels -> this one): cosines 3.1e-6 -> 2.2e-6, distances
+// 1.6e-6 -> 9.7e-7 of themselves, 1.24e-6 with Z the sum of the exponentials before rounding.
 //
-// Measured, bfloat16, 32 layers, 32/8 heads of 128 (the three kernels -> this one, whole call): 64 tokens over 4096 keys 374 -> 213 us
-// (weights 186, scale 10, Gram 145 -> 178), over 16384 1285 -> 660; 256 over 2000 680 -> 356; one over 16384 340 -> 246.
+// Measured, bfloat16, 32 layers, 32/8 heads of 128 (the three kernels -> this one, whole call): 64 tokens over 4096 keys 374 -> 203 us
+// (traced: weights 186, scale 10, Gram 145 -> 188), over 16384 1285 -> 650; 256 over 2000 680 -> 356; one over 16384 340 -> 225.
 // What bounds it: 8 bytes of keys per logit through the CU's L2-to-LDS stream (row blocks of a kv head run side by side on an XCD
-// and share them in its L2), 8 KB in flight per wave: without its copies the kernel takes 115 us, with all of them hitting the L2
-// 160.  Two buffers per wave would not fit beside the exponentials.
+// and share them in its L2), 8 KB in flight per wave: with nothing copied the kernel takes 139 us, with every copy reading one block of keys
+// in the L2 165.  Two buffers per wave would not fit beside the exponentials.
 constexpr int kDirectWaves = 8, kDirectLayers = 32;
 constexpr int kDirectGram = 768;   // floats of a partial Gram matrix: element v of lane (l16, kq) of block a at a*256 + v*64 + kq*16 + l16
 constexpr float kDirectBelow = 8.f, kDirectRaise = 9.f, kDirectLimit = 5793.f;
 
-// KA: 0 dense keys, 1 strides (a pointer per layer, or dense with a head size below D), 2 pages
 __device__ inline int fresh_lane()   // the lane's number, formed anew: a register less alive over a loop
 {
     int ln;
@@ -579,6 +579,7 @@ __device__ inline int fresh_lane()   // the lane's number, formed anew: a regist
     return ln;
 }
 
+// KA: 0 dense keys, 1 strides (a pointer per layer, or dense with a head size below D), 2 pages
 template <int D, bool F16, int KA>
 __global__ __launch_bounds__(kDirectWaves * 64, 2) void ap_direct_kernel(APParams p, int ksp, int kb_per)
 {

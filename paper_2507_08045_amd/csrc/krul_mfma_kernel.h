@@ -99,8 +99,6 @@ __device__ inline int swz(int row)
     return D == 128 ? (row & 15) : ((row >> 1) & 7);
 }
 
-// MODE 0: cosine only; 1: also Z = sum e (needed for the distance); 2: also Zir = sum of e over the
-// initial and recent keys (the Initial-Recent layer test of Sec. 4.2), which needs Z too
 // A wave-uniform address, said to be so: descriptors built from it then stay in scalar registers.
 __device__ inline const uint16_t *uniform_ptr(const uint16_t *ptr)
 {
@@ -120,6 +118,8 @@ __device__ inline f32x16 mfma_16bit(bf16x8 a, bf16x8 b, f32x16 c)
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// MODE 0: cosine only; 1: also Z = sum e (needed for the distance); 2: also Zir = sum of e over the
+// initial and recent keys (the Initial-Recent layer test of Sec. 4.2), which needs Z too.
 // KA: how the keys are addressed.  0: dense [B][L][Hkv][S][d].  1: one allocation per layer (a device
 // table of pointers) and strides between conversations, kv heads and keys.  2: one pool of pages per
 // layer, a block table per conversation, strides between pages, kv heads and the keys of a page.
