@@ -52,7 +52,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 constexpr float kLazy = 16.0f;
 constexpr float kBig = 4294967296.0f;   // 2^(2*kLazy): bound on a block's sum of squared exponentials
 
-template <int D_, int WR_, int WK_, int KBW_, int NC_>
+template <int D_, int WR_, int WK_, int KBW_, int NC_, int KS_ = D_ / 16>
 struct Cfg {
     static constexpr int D = D_, WR = WR_, WK = WK_, KBW = KBW_;
     static constexpr int NC = NC_;                 // chunks per key tile = ring slots
@@ -63,7 +63,7 @@ struct Cfg {
     static constexpr int CH = WK * KBW * 32;       // keys per chunk
     static constexpr int KT = CH * NC;             // keys per tile
     static constexpr int NBLK = NC * KBW;          // 32-key blocks per wave per tile
-    static constexpr int KS = D / 16;              // MFMA k-steps per 32x32 block
+    static constexpr int KS = KS_;                 // MFMA k-steps per 32x32 block: the head size they cover may be below D
     static constexpr int PPR = D / 8;              // 16-byte pieces per row
     static constexpr int RPI = 64 / PPR;           // rows covered by one 1 KB wave-instruction
     static constexpr int SLOT_BYTES = CH * D * 2;
@@ -559,13 +559,12 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
                     float bz = 0.f, bn = 0.f, bd = 0.f;
                     {
                         const float negm = -mcur;
-                        constexpr int VPK = 16 / KS;
 #pragma unroll
                         for (int ks = 0; ks < KS; ++ks) {
                             nx = mfma_16bit<F16>(aop[ks], qf[ks], nx);
                             asm volatile("" : "+v"(nx));
 #pragma unroll
-                            for (int v = ks * VPK; v < (ks + 1) * VPK; ++v) {
+                            for (int v = ks * 16 / KS; v < (ks + 1) * 16 / KS; ++v) {
                                 ev[v] = __builtin_amdgcn_exp2f(fmaf(x[v], cs, negm));
                                 if (WZ) bz += ev[v];
                                 bn = fmaf(ev[v], ev[v], bn);
@@ -683,7 +682,8 @@ hipError_t launch_cfg_t(const SimParams &p, int n_workgroups, hipStream_t st)
     if (p.block_table) return launch_mode<C, 2, F16>(p, n_workgroups, st);   // keys in pages
     // keys in per-layer allocations, with strides -- or dense, with a head size below the kernel's
     if (p.k_tab || p.d != C::D) return launch_mode<C, 1, F16>(p, n_workgroups, st);
-    return launch_mode<C, 0, F16>(p, n_workgroups, st);
+    if constexpr (C::KS * 16 == C::D) return launch_mode<C, 0, F16>(p, n_workgroups, st);
+    return hipErrorInvalidValue;
 }
 
 template <class C>
