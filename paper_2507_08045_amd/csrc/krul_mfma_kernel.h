@@ -606,10 +606,14 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
                         if (kb0 + 32 <= p.ir_init_end || kb0 >= p.ir_recent_begin) {
                             tzir += bz;
                         } else if (!(kb0 >= p.ir_init_end && kb0 + 32 <= p.ir_recent_begin)) {
-                            float bir = 0.f;   // element v of this lane is key kb0 + 8*(v/4) + 4*half + v%4
+                            // element v of this lane is key lane_key + 8*(v/4) + v%4 (opaque: the bounds of a tile's 64 keys a
+                            // lane would else be formed once, in scalar registers that there are not)
+                            float bir = 0.f;
+                            int lane_key = kb0 + 4 * half;
+                            asm volatile("" : "+v"(lane_key));
 #pragma unroll
                             for (int v = 0; v < 16; ++v) {
-                                const int key = kb0 + 8 * (v >> 2) + 4 * half + (v & 3);
+                                const int key = lane_key + 8 * (v >> 2) + (v & 3);
                                 if (key < p.ir_init_end || key >= p.ir_recent_begin) bir += ev[v];
                             }
                             tzir += bir;
