@@ -1264,11 +1264,22 @@ void ap_layout(const krul_shape_t *s, int nrg, APPlan *pl)
     if (ksp > ksp_max) ksp = ksp_max;
     if (ksp > 64) ksp = 64;
     if (pl->direct) {
-        // a round of one workgroup per CU, counted over the whole problem (so that the sums do not depend on the batch)
-        const long long blocks = (long long)s->batch * s->n_kv_heads * pl->NRB;
-        ksp = (256 + blocks - 1) / blocks;
-        if (ksp > pl->NKB) ksp = pl->NKB;
-        if (ksp > 128) ksp = 128;   // (the row kernel holds every partial's exponents in LDS)
+        // As many key splits as fill some number of rounds of one workgroup per CU: the number that takes the least by the time
+        // of a key block (5.9 us for 32 layers of 128), of a workgroup's start and end, and of the partial matrices' way
+        // through memory.  (One round or the next above: 72 tokens over 4096 keys, 72 row blocks, 4 splits in two rounds, the
+        // second nearly empty.)  Counted over the whole problem, so that the sums do not depend on the batch.
+        const long long blocks = (long long)s->batch * s->n_kv_heads * pl->NRB, most = pl->NKB < 128 ? pl->NKB : 128;   // (the row kernel holds every partial's exponents in LDS)
+        const double t_kb = 5.9 * (double)((s->n_layers + 7) / 8) / 4.0 * (s->head_dim > 64 ? 1.0 : 0.63);
+        double best = 0.0;
+        for (long long r = (blocks + 255) / 256, r_end = r + 8; r < r_end; ++r) {
+            const long long n = 256 * r / blocks < most ? 256 * r / blocks : most, kb = (pl->NKB + n - 1) / n;
+            const double t = (double)r * ((double)kb * t_kb + 8.0) + 0.04 * (double)(blocks * n);
+            if (best == 0.0 || t < best) {
+                best = t;
+                ksp = n;
+            }
+            if (n == most) break;
+        }
     }
     pl->kb_per = (int)((pl->NKB + ksp - 1) / ksp);
     pl->ksp = (pl->NKB + pl->kb_per - 1) / pl->kb_per;
@@ -1301,17 +1312,20 @@ int ap_plan(const krul_shape_t *s, size_t max_bytes, APPlan *pl)
     const long long g = s->n_q_heads / s->n_kv_heads, Rk = g * s->n_query;
     if (Rk > INT32_MAX || (long long)s->batch * s->n_q_heads * s->n_query > INT32_MAX) return KRUL_EUNSUPPORTED;
     if (s->n_hist * (long long)s->head_dim * 4 >= (1ll << 31)) return KRUL_EUNSUPPORTED;
+    pl->mfma = (s->dtype == KRUL_BF16 || s->dtype == KRUL_F16) && s->head_dim <= 128 &&
+               !(s->flags & KRUL_FLAG_GENERIC_KERNEL);
+    pl->direct = pl->mfma && s->n_layers <= kDirectLayers;
     const long long NRB = (Rk + 31) / 32;   // 32-row blocks per unit
-    pl->NW = NRB >= 6 ? 8 : (NRB >= 3 ? 4 : (int)NRB);
+    // Row blocks to a group.  ap_direct_kernel takes them singly, so that there are no workgroups without rows: they are
+    // handed to an XCD's shader engines in turn, and with 9 of 16 of them at work (72 tokens) one engine in four
+    // had nine to run on its eight CUs where the others had six.
+    pl->NW = pl->direct ? 1 : NRB >= 6 ? 8 : (NRB >= 3 ? 4 : (int)NRB);
     pl->NRB = (int)NRB;
     pl->NRG = (int)((NRB + pl->NW - 1) / pl->NW);
     pl->NKB = (s->n_hist + 31) / 32;
     const long long total = (long long)s->batch * s->n_kv_heads * pl->NRG;
     if (total * pl->NW * 32 > INT32_MAX / 4) return KRUL_EUNSUPPORTED;
     pl->total_rg = (int)total;
-    pl->mfma = (s->dtype == KRUL_BF16 || s->dtype == KRUL_F16) && s->head_dim <= 128 &&
-               !(s->flags & KRUL_FLAG_GENERIC_KERNEL);
-    pl->direct = pl->mfma && s->n_layers <= kDirectLayers;
     // key splits of the weights kernel: one per kKeysPerSplit keys (the portable kernel does not split)
     if (pl->mfma) {
         pl->kps = kKeysPerSplit;
