@@ -73,6 +73,7 @@ struct APParams {
     int tpw;            // key splits that one weights-kernel workgroup walks
     int grg0, nrg;      // this batch: global row groups [grg0, grg0 + nrg)
     int want_dist;
+    int classes;        // of a head's rows, by token index (a power of two)
     unsigned char *dump;   // [kDumpBlocks][2 KB]
     unsigned char *E;   // [nrg*NW][NKB][L][32][64 bytes]; e = 2^(x - m) with m of the row, layer and key split
     float *rowM;        // [nrg*NW*32][nsplit][L]  reference exponent m; then the factor 2^(m - largest m of the row, layer)
@@ -81,7 +82,7 @@ struct APParams {
     float *Gpart;       // [nrg*NW*32][ksp][NACC*1024] partial Gram matrices, result-register order
     float *row_cos;     // [nrg*NW*32][L*L]  (entries i > j)
     float *row_dist;    // same, or unused
-    float *head_cos;    // [B][Hq][kClasses][L*L] running sums over the rows of a head, by class of token index
+    float *head_cos;    // [B][Hq][classes][L*L] running sums over the rows of a head, by class of token index
     float *head_dist;
 };
 
@@ -870,87 +871,34 @@ __global__ __launch_bounds__(kDirectWaves * 64, 2) void ap_direct_kernel(APParam
 
 // 4. One workgroup per row of the batch: the row's partial Gram matrices are added in order and
 // cos_ij, dist_ij are written for i > j.
-// DIRECT: the partials come from ap_direct_kernel, each at exponents of its own (rowM, rowZ [row][ksp][L]): they are brought
-// to the row's largest first.
-template <bool DIRECT>
 __global__ __launch_bounds__(kThreads) void ap_row_final_kernel(APParams p, int ksp)
 {
     extern __shared__ float sm_rf[];
     const int L = p.L, NB = (L + 31) / 32, NACC = NB * (NB + 1) / 2;
     float *Gs = sm_rf;                 // [NACC*1024]
-    float *Zs = Gs + (DIRECT ? kDirectGram : NACC * 1024);   // [L]: 1 / Z of the layer
+    float *Zs = Gs + NACC * 1024;      // [L]: 1 / Z of the layer
     const int rowl = blockIdx.x, rbl = rowl >> 5, row32 = rowl & 31;
     const int grb = p.grg0 * p.NW + rbl;
     const int rb = grb % (p.NRG * p.NW);
     if (rb * 32 + row32 >= p.Rk) return;
     const int tid = threadIdx.x;
-    const float *gp = p.Gpart + (size_t)rowl * ksp * (DIRECT ? kDirectGram : NACC * 1024);
-    if constexpr (DIRECT) {
-        float *fac = Zs + 32;         // [ksp][32] factor of (partial, layer); first its exponent
-        float *zp = fac + ksp * 32;   // [ksp][32]
-        const float4 *g4 = reinterpret_cast<const float4 *>(gp) + min(tid, kDirectGram / 4 - 1);
-        float4 t[4];   // the first partials are asked for before the exponents are here
+    const float *gp = p.Gpart + (size_t)rowl * ksp * (NACC * 1024);
+    for (int i = tid; i < NACC * 1024; i += kThreads) {
+        float g = 0.f;
+        int y = 0;
+        for (; y + 8 <= ksp; y += 8) {   // eight loads in flight, added in order
+            float t[8];
 #pragma unroll
-        for (int k2 = 0; k2 < 4; ++k2) t[k2] = g4[(size_t)min(k2, ksp - 1) * (kDirectGram / 4)];
-        for (int y = tid >> 5; y < ksp; y += kThreads / 32) {
-            const int l = tid & 31;
-            fac[y * 32 + l] = l < L ? p.rowM[((size_t)rowl * ksp + y) * L + l] : 0.f;
-            zp[y * 32 + l] = l < L ? p.rowZ[((size_t)rowl * ksp + y) * L + l] : 0.f;
-        }
-        __syncthreads();
-        if (tid < 32) {   // (columns of layers that do not exist: 0)
-            const bool ok = tid < L;
-            float M = kMInit, zt = 0.f;
-            if (ok)
-                for (int y = 0; y < ksp; ++y) M = fmaxf(M, fac[y * 32 + tid]);
-            for (int y = 0; y < ksp; ++y) {
-                const float f = ok ? __builtin_amdgcn_exp2f(fac[y * 32 + tid] - M) : 0.f;
-                fac[y * 32 + tid] = f;
-                zt = fmaf(zp[y * 32 + tid], f, zt);
-            }
-            if (ok) Zs[tid] = 1.f / zt;
-        }
-        __syncthreads();
-        // four entries of one matrix row per thread: entry 4*tid + k is (layer i, layer j0 + k)
-        if (tid < kDirectGram / 4) {
-        const int a = tid >> 6, i = (a ? 16 : 0) + 4 * ((tid >> 2) & 3) + ((tid >> 4) & 3), j0 = (a == 2 ? 16 : 0) + (tid & 3) * 4;
-        float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int y = 0; y < ksp; y += 4) {   // four loads in flight, added in order
-            if (y) {
+            for (int k2 = 0; k2 < 8; ++k2) t[k2] = gp[(size_t)(y + k2) * (NACC * 1024) + i];
 #pragma unroll
-                for (int k2 = 0; k2 < 4; ++k2) t[k2] = g4[(size_t)min(y + k2, ksp - 1) * (kDirectGram / 4)];
-            }
-#pragma unroll
-            for (int k2 = 0; k2 < 4; ++k2) {
-                if (y + k2 >= ksp) break;
-                const float fi = fac[(y + k2) * 32 + i], *fj = fac + (y + k2) * 32 + j0;
-                g.x = fmaf(t[k2].x, fi * fj[0], g.x);
-                g.y = fmaf(t[k2].y, fi * fj[1], g.y);
-                g.z = fmaf(t[k2].z, fi * fj[2], g.z);
-                g.w = fmaf(t[k2].w, fi * fj[3], g.w);
-            }
+            for (int k2 = 0; k2 < 8; ++k2) g += t[k2];
         }
-        reinterpret_cast<float4 *>(Gs)[tid] = g;
-        }
-    } else {
-        for (int i = tid; i < NACC * 1024; i += kThreads) {
-            float g = 0.f;
-            int y = 0;
-            for (; y + 8 <= ksp; y += 8) {   // eight loads in flight, added in order
-                float t[8];
-#pragma unroll
-                for (int k2 = 0; k2 < 8; ++k2) t[k2] = gp[(size_t)(y + k2) * (NACC * 1024) + i];
-#pragma unroll
-                for (int k2 = 0; k2 < 8; ++k2) g += t[k2];
-            }
-            for (; y < ksp; ++y) g += gp[(size_t)y * (NACC * 1024) + i];
-            Gs[i] = g;
-        }
-        for (int l = tid; l < L; l += kThreads) Zs[l] = p.rowZt[(size_t)rowl * L + l];
+        for (; y < ksp; ++y) g += gp[(size_t)y * (NACC * 1024) + i];
+        Gs[i] = g;
     }
+    for (int l = tid; l < L; l += kThreads) Zs[l] = p.rowZt[(size_t)rowl * L + l];
     __syncthreads();
     auto G = [&](int i, int j) -> float {   // i >= j
-        if constexpr (DIRECT) return Gs[((i >> 4) + (j >> 4)) * 256 + (i & 3) * 64 + ((i >> 2) & 3) * 16 + (j & 15)];
         const int bi = i >> 5, bj = j >> 5, ii = i & 31;
         const int a = bi * (bi + 1) / 2 + bj;
         const int v = ((ii >> 3) << 2) | (ii & 3), kg = (ii >> 2) & 1;
@@ -971,11 +919,14 @@ __global__ __launch_bounds__(kThreads) void ap_row_final_kernel(APParams p, int 
 }
 
 // ------------------------------------------------------------------------------------------------
-// 5. rows -> head sums.  The rows of a head fall into kClasses classes by token index (t % kClasses);
+// 5. rows -> head sums.  The rows of a head fall into p.classes classes by token index (t % p.classes);
 // a thread owns one matrix entry of one class of one head and adds that class's rows of the batch,
 // one by one in order, to the class's running sum: each sum sees its rows in the same order
 // wherever the batches are cut, so the result does not depend on the batch size.
 constexpr int kClasses = 8;
+// A class of a head is a workgroup of ap_rows_kernel, and ap_final_kernel reads the classes' sums: 16 for up to 16 heads (256 tokens
+// of 16 heads: the call 159 -> 153 us), 8 for more (64 of 32 heads with 16: ap_final_kernel 6.5 -> 11.7 us).
+constexpr int class_count(long long heads) { return heads <= 16 ? 2 * kClasses : kClasses; }
 
 __global__ __launch_bounds__(kThreads) void ap_reduce_kernel(APParams p, int u0)
 {
@@ -993,18 +944,18 @@ __global__ __launch_bounds__(kThreads) void ap_reduce_kernel(APParams p, int u0)
     const int i = e / p.L, j = e % p.L;
     if (i <= j) return;
     const int b = u / p.Hkv, hq = (u % p.Hkv) * p.g + hg;
-    const size_t o = (((size_t)b * p.Hq + hq) * kClasses + cls) * LL + e;
+    const size_t o = (((size_t)b * p.Hq + hq) * p.classes + cls) * LL + e;
     // (the batch with the head's first row starts the sums, also those of classes without rows)
     const bool starts = r_lo == hg * p.Tq;
     float cs = starts ? 0.f : p.head_cos[o], ds = p.want_dist && !starts ? p.head_dist[o] : 0.f;
     auto rowl_of = [&](int r) -> size_t { return (size_t)(u * p.NRG + r / rpg - p.grg0) * rpg + r % rpg; };
     // first row of the range whose token index t = r - hg*Tq is in this class
-    int r = r_lo + ((cls - (r_lo - hg * p.Tq)) % kClasses + kClasses) % kClasses;
-    for (; r + 3 * kClasses < r_hi; r += 4 * kClasses) {   // four rows in flight, added in order
+    int r = r_lo + ((cls - (r_lo - hg * p.Tq)) & (p.classes - 1));
+    for (; r + 3 * p.classes < r_hi; r += 4 * p.classes) {   // four rows in flight, added in order
         float tc[4], td[4];
 #pragma unroll
         for (int k2 = 0; k2 < 4; ++k2) {
-            const size_t rowl = rowl_of(r + k2 * kClasses);
+            const size_t rowl = rowl_of(r + k2 * p.classes);
             tc[k2] = p.row_cos[rowl * LL + e];
             td[k2] = p.want_dist ? p.row_dist[rowl * LL + e] : 0.f;
         }
@@ -1014,7 +965,7 @@ __global__ __launch_bounds__(kThreads) void ap_reduce_kernel(APParams p, int u0)
             ds += td[k2];
         }
     }
-    for (; r < r_hi; r += kClasses) {
+    for (; r < r_hi; r += p.classes) {
         const size_t rowl = rowl_of(r);
         cs += p.row_cos[rowl * LL + e];
         if (p.want_dist) ds += p.row_dist[rowl * LL + e];
@@ -1023,9 +974,170 @@ __global__ __launch_bounds__(kThreads) void ap_reduce_kernel(APParams p, int u0)
     if (p.want_dist) p.head_dist[o] = ds;
 }
 
+// 4 and 5 in one for ap_direct_kernel's partials (up to 32 layers): a workgroup takes the rows of one class of one head, R at
+// a time, 256 threads to a row.  A row's partials are at exponents of their own (rowM, rowZ [row][ksp][L]) and are brought to the
+// row's largest first; its threads then form the entries of its matrices in LDS, and the R rows' are added to the class's sums in
+// order, so the sums do not depend on R, and the rows' matrices never cross memory.  Bound by the latency of a row's few
+// steps (2.2 us), hence the rows side by side, and the next rows' first partials and exponents asked for ahead.  (A workgroup
+// per row and a kernel for the sums, 64 tokens of 32 heads: 13.4 + 5.9 us; R = 1 18.9, R = 4 12.0.)
+__host__ __device__ constexpr int ap_rows_floats(int ksp) { return kDirectGram + 32 + ksp * 64 + 2 * 512; }   // of LDS for a row
+constexpr int kRowsLds = 64 << 10;   // a launch's without asking for more
+
+template <int R>
+__global__ __launch_bounds__(R * kThreads) void ap_rows_kernel(APParams p, int ksp, int u0)
+{
+    extern __shared__ float sm_rows[];
+    const int L = p.L, LL = L * L, tid = threadIdx.x % kThreads, g = threadIdx.x / kThreads;   // g: which of the R rows
+    const int hg = blockIdx.x % p.g, u = u0 + blockIdx.x / p.g, cls = blockIdx.y;
+    // rows of unit u that this batch holds, and those of them that belong to head hg (see ap_reduce_kernel)
+    const int rg_lo = max(p.grg0, u * p.NRG) - u * p.NRG, rg_hi = min(p.grg0 + p.nrg, (u + 1) * p.NRG) - u * p.NRG;
+    const int rpg = p.NW * 32;
+    const int r_lo = max(rg_lo * rpg, hg * p.Tq), r_hi = min(min(rg_hi * rpg, p.Rk), (hg + 1) * p.Tq);
+    if (r_lo >= r_hi) return;
+    float *const Gs = sm_rows + g * ap_rows_floats(ksp);      // [kDirectGram] the row's Gram matrix
+    float *const Zs = Gs + kDirectGram;                       // [32] 1 / Z of the layer
+    float *const fac = Zs + 32, *const zp = fac + ksp * 32;   // [ksp][32] exponent, then factor, of (partial, layer); Z
+    float *const rc = zp + ksp * 32, *const rd = rc + 512;    // the row's cosines and distances, by pair
+    // pair number t: (i, j) with t = i(i-1)/2 + j
+    auto pair_of = [](int t, int &i, int &j) {
+        i = (int)((1.f + sqrtf(1.f + 8.f * (float)t)) * 0.5f);
+        i += (i + 1) * i / 2 <= t ? 1 : 0;     // (the root may be off by one)
+        i -= i * (i - 1) / 2 > t ? 1 : 0;
+        j = t - i * (i - 1) / 2;
+    };
+    // the row's entries that this thread forms, and those of the class that it adds up
+    constexpr int E = 512 / kThreads, A = R == 1 ? 2 : 1;
+    int ei[E], ej[E], at[A];
+    float cs[A], ds[A];
+    const int b = u / p.Hkv, hq = (u % p.Hkv) * p.g + hg;
+    const size_t o = (((size_t)b * p.Hq + hq) * p.classes + cls) * LL;
+    const bool starts = r_lo == hg * p.Tq;   // (the batch with the head's first row starts the sums, also those of classes without rows)
+#pragma unroll
+    for (int k = 0; k < E; ++k) pair_of(k * kThreads + tid, ei[k], ej[k]);
+#pragma unroll
+    for (int k = 0; k < A; ++k) {
+        int i, j;
+        pair_of(k * kThreads + (int)threadIdx.x, i, j);
+        at[k] = i < L ? i * L + j : -1;
+        cs[k] = at[k] >= 0 && !starts ? p.head_cos[o + at[k]] : 0.f;
+        ds[k] = at[k] >= 0 && !starts && p.want_dist ? p.head_dist[o + at[k]] : 0.f;
+    }
+    auto rowl_of = [&](int r) -> size_t { return (size_t)(u * p.NRG + r / rpg - p.grg0) * rpg + r % rpg; };
+    // four entries of one matrix row per thread: entry 4*tid + k is (layer gi, layer gj + k)
+    const int gt = min(tid, kDirectGram / 4 - 1), ga = gt >> 6;
+    const int gi = (ga ? 16 : 0) + 4 * ((gt >> 2) & 3) + ((gt >> 4) & 3), gj = (ga == 2 ? 16 : 0) + (gt & 3) * 4;
+    const int l = tid & 31, y0 = tid >> 5;        // exponents: layer l of partials y0, y0 + 8, ...
+    const int lc = min(l, L - 1);
+    float4 t[4];
+    float m0 = 0.f, z0 = 0.f;
+    auto ask = [&](size_t rowl) __attribute__((always_inline)) {
+        const float4 *g4 = reinterpret_cast<const float4 *>(p.Gpart + rowl * ksp * kDirectGram) + gt;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t[k] = g4[(size_t)min(k, ksp - 1) * (kDirectGram / 4)];
+        const size_t first = (rowl * ksp + min(y0, ksp - 1)) * L + lc;
+        m0 = p.rowM[first];
+        z0 = p.rowZ[first];
+    };
+    // first row of the range whose token index t = r - hg*Tq is in this class; this group's is g rows of the class further on
+    // (past the last: the last once more, and it is not added)
+    const int r_first = r_lo + ((cls - (r_lo - hg * p.Tq)) & (p.classes - 1));
+    const int n_rows = r_first < r_hi ? (r_hi - r_first + p.classes - 1) / p.classes : 0;
+    auto row_at = [&](int n) -> size_t { return rowl_of(r_first + min(n, n_rows - 1) * p.classes); };
+    if (n_rows) ask(row_at(g));
+    for (int n = 0; n < n_rows; n += R) {
+        const size_t rowl = row_at(n + g);
+        for (int y = y0; y < ksp; y += kThreads / 32) {
+            const size_t e = (rowl * ksp + y) * L + lc;
+            fac[y * 32 + l] = y == y0 ? m0 : p.rowM[e];
+            zp[y * 32 + l] = y == y0 ? z0 : p.rowZ[e];
+        }
+        __syncthreads();
+        if (tid < 32) {   // (columns of layers that do not exist: 0)
+            const bool ok = tid < L;
+            float M = kMInit, zt = 0.f;
+            float m[4], z[4];   // (four reads in flight)
+            for (int y = 0; y < ksp; y += 4) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) m[k] = fac[min(y + k, ksp - 1) * 32 + tid];
+                M = fmaxf(fmaxf(M, fmaxf(m[0], m[1])), fmaxf(m[2], m[3]));
+            }
+            for (int y = 0; y < ksp; y += 4) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    m[k] = fac[min(y + k, ksp - 1) * 32 + tid];
+                    z[k] = zp[min(y + k, ksp - 1) * 32 + tid];
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (y + k >= ksp) break;
+                    const float f = ok ? __builtin_amdgcn_exp2f(m[k] - M) : 0.f;
+                    fac[(y + k) * 32 + tid] = f;
+                    zt = fmaf(z[k], f, zt);
+                }
+            }
+            if (ok) Zs[tid] = 1.f / zt;
+        }
+        __syncthreads();
+        const float4 *g4 = reinterpret_cast<const float4 *>(p.Gpart + rowl * ksp * kDirectGram) + gt;
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int y = 0; y < ksp; y += 4) {   // four partials at a time, the next four in flight, added in order
+            float4 c[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) c[k] = t[k];
+            if (y + 4 < ksp) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) t[k] = g4[(size_t)min(y + 4 + k, ksp - 1) * (kDirectGram / 4)];
+            } else if (n + R < n_rows) {
+                ask(row_at(n + R + g));
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (y + k >= ksp) break;
+                const float fi = fac[(y + k) * 32 + gi], *fj = fac + (y + k) * 32 + gj;
+                s.x = fmaf(c[k].x, fi * fj[0], s.x);
+                s.y = fmaf(c[k].y, fi * fj[1], s.y);
+                s.z = fmaf(c[k].z, fi * fj[2], s.z);
+                s.w = fmaf(c[k].w, fi * fj[3], s.w);
+            }
+        }
+        if (tid < kDirectGram / 4) reinterpret_cast<float4 *>(Gs)[tid] = s;
+        __syncthreads();
+        auto G = [&](int i, int j) -> float { return Gs[((i >> 4) + (j >> 4)) * 256 + (i & 3) * 64 + ((i >> 2) & 3) * 16 + (j & 15)]; };   // i >= j
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            if (ei[k] >= L) continue;
+            const float gij = G(ei[k], ej[k]), gii = G(ei[k], ei[k]), gjj = G(ej[k], ej[k]);
+            rc[k * kThreads + tid] = gij * rsqrtf(gii * gjj);
+            if (p.want_dist) {
+                const float zi = Zs[ei[k]], zj = Zs[ej[k]];
+                rd[k * kThreads + tid] = sqrtf(fmaxf(gii * zi * zi + gjj * zj * zj - 2.f * gij * zi * zj, 0.f));
+            }
+        }
+        __syncthreads();   // (the next rows' are written three barriers on)
+#pragma unroll
+        for (int k = 0; k < A; ++k) {
+            if (at[k] < 0) continue;
+#pragma unroll
+            for (int w = 0; w < R; ++w) {
+                if (n + w >= n_rows) break;
+                const float *const row = sm_rows + w * ap_rows_floats(ksp) + kDirectGram + 32 + ksp * 64 + k * kThreads + threadIdx.x;
+                cs[k] += row[0];
+                if (p.want_dist) ds[k] += row[512];
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < A; ++k) {
+        if (at[k] < 0) continue;
+        p.head_cos[o + at[k]] = cs[k];
+        if (p.want_dist) p.head_dist[o + at[k]] = ds[k];
+    }
+}
+
 // head sums -> means over tokens, average over heads, mirrored matrices with cos 1 / distance 0 on
 // the diagonal.  A workgroup takes 8 entries (conversation, i, j); 32 threads share an entry's heads
 // (h = lane, lane + 32, ...) and their sums are added in lane order.
+template <int CLASSES>
 __global__ __launch_bounds__(kThreads) void ap_final_kernel(int B, int L, int Hq, float inv_tokens,
                                                             const float *__restrict__ head_cos,
                                                             const float *__restrict__ head_dist,
@@ -1042,11 +1154,11 @@ __global__ __launch_bounds__(kThreads) void ap_final_kernel(int B, int L, int Hq
         const int b = (int)(idx / LL), e = (int)(idx % LL), i = e / L, j = e % L;
         const int lo = i > j ? e : j * L + i;   // the entry below the diagonal holds the sums
         for (int h = hl; h < Hq; h += 32) {
-            const size_t o = ((size_t)b * Hq + h) * LL, oc = o * kClasses + lo;
+            const size_t o = ((size_t)b * Hq + h) * LL, oc = o * CLASSES + lo;
             float hc = 0.f, hd = 0.f;   // the classes' sums, in order
             if (i != j) {
 #pragma unroll
-                for (int cl = 0; cl < kClasses; ++cl) {
+                for (int cl = 0; cl < CLASSES; ++cl) {
                     hc += head_cos[oc + (size_t)cl * LL];
                     if (pair_dist) hd += head_dist[oc + (size_t)cl * LL];
                 }
@@ -1254,7 +1366,7 @@ constexpr int kGramTargetWorkgroups = 512;
 void ap_layout(const krul_shape_t *s, int nrg, APPlan *pl)
 {
     const size_t L = s->n_layers, LL = L * L, NB = (L + 31) / 32, NACC = NB * (NB + 1) / 2;
-    const size_t heads = (size_t)s->batch * s->n_q_heads * kClasses * LL * sizeof(float);
+    const size_t heads = (size_t)s->batch * s->n_q_heads * class_count((long long)s->batch * s->n_q_heads) * LL * sizeof(float);
     const size_t rows = (size_t)nrg * pl->NW * 32;
     // the Gram kernel splits the keys until it has enough workgroups, but keeps at least 16 key blocks
     // per workgroup so that the partial matrices stay small beside the weights
@@ -1292,8 +1404,8 @@ void ap_layout(const krul_shape_t *s, int nrg, APPlan *pl)
     pl->rowz_off = off; off += align_up(rows * L * pl->nsplit * sizeof(float));
     pl->rowzt_off = off; off += align_up(rows * L * sizeof(float));
     pl->gpart_off = off; off += align_up(rows * pl->ksp * (pl->direct ? kDirectGram : NACC * 1024) * sizeof(float));
-    pl->row_cos_off = off; off += align_up(rows * LL * sizeof(float));
-    pl->row_dist_off = off; off += align_up(rows * LL * sizeof(float));
+    pl->row_cos_off = off; off += pl->direct ? 0 : align_up(rows * LL * sizeof(float));
+    pl->row_dist_off = off; off += pl->direct ? 0 : align_up(rows * LL * sizeof(float));
     pl->e_off = off; off += pl->direct ? 0 : align_up((size_t)nrg * pl->NW * L * pl->NKB * 2048);
     pl->total_bytes = off;
     pl->nrg_batch = nrg;
@@ -1437,6 +1549,7 @@ int run_all_pairs(const krul_shape_t *s, const void *q, const void *k, const kru
     p.kps = pl.kps;
     p.tpw = pl.tpw;
     p.want_dist = pair_dist != nullptr;
+    p.classes = class_count((long long)s->batch * s->n_q_heads);
     p.E = ws + pl.e_off;
     p.dump = ws + pl.dump_off;
     p.rowM = reinterpret_cast<float *>(ws + pl.rowm_off);
@@ -1473,25 +1586,31 @@ int run_all_pairs(const krul_shape_t *s, const void *q, const void *k, const kru
         } else {
             hipLaunchKernelGGL(ap_weights_generic_kernel<uint16_t>, dim3(rows * L), dim3(64), p.d * sizeof(float), st, p);
         }
+        const int u0 = g0 / p.NRG, u1 = (g0 + p.nrg - 1) / p.NRG, heads = (u1 - u0 + 1) * p.g;
         if (pl.direct) {
-            hipLaunchKernelGGL(ap_row_final_kernel<true>, dim3(rows), dim3(kThreads), (kDirectGram + 32 + pl.ksp * 64) * sizeof(float), st, p, pl.ksp);
+            // four rows of a class at a time where it has them and the classes leave CUs idle (and there is LDS for their exponents):
+            // with more workgroups than CUs one at a time is as fast or faster (3 x 90 tokens: 312 us against 319)
+            const size_t lds = ap_rows_floats(pl.ksp) * sizeof(float);
+            if (p.Tq > p.classes && heads * p.classes <= 256 && 4 * lds <= kRowsLds)
+                hipLaunchKernelGGL(ap_rows_kernel<4>, dim3(heads, p.classes), dim3(4 * kThreads), 4 * lds, st, p, pl.ksp, u0);
+            else
+                hipLaunchKernelGGL(ap_rows_kernel<1>, dim3(heads, p.classes), dim3(kThreads), lds, st, p, pl.ksp, u0);
         } else {
-        hipLaunchKernelGGL(ap_scale_kernel, dim3(rows), dim3(kThreads), 0, st, p);
-        switch (NB) {
-        case 1: hipLaunchKernelGGL((ap_gram_kernel<1, 4, 8>), dim3(rblocks, pl.ksp), dim3(512), 0, st, p, pl.ksp, pl.kb_per); break;
-        case 2: hipLaunchKernelGGL((ap_gram_kernel<2, 2, 8>), dim3(rblocks * 2, pl.ksp), dim3(512), 0, st, p, pl.ksp, pl.kb_per); break;
-        case 3: hipLaunchKernelGGL((ap_gram_kernel<3, 1, 8>), dim3(rblocks * 4, pl.ksp), dim3(512), 0, st, p, pl.ksp, pl.kb_per); break;
-        default: hipLaunchKernelGGL((ap_gram_kernel<4, 1, 4>), dim3(rblocks * 8, pl.ksp), dim3(256), 0, st, p, pl.ksp, pl.kb_per); break;
+            hipLaunchKernelGGL(ap_scale_kernel, dim3(rows), dim3(kThreads), 0, st, p);
+            switch (NB) {
+            case 1: hipLaunchKernelGGL((ap_gram_kernel<1, 4, 8>), dim3(rblocks, pl.ksp), dim3(512), 0, st, p, pl.ksp, pl.kb_per); break;
+            case 2: hipLaunchKernelGGL((ap_gram_kernel<2, 2, 8>), dim3(rblocks * 2, pl.ksp), dim3(512), 0, st, p, pl.ksp, pl.kb_per); break;
+            case 3: hipLaunchKernelGGL((ap_gram_kernel<3, 1, 8>), dim3(rblocks * 4, pl.ksp), dim3(512), 0, st, p, pl.ksp, pl.kb_per); break;
+            default: hipLaunchKernelGGL((ap_gram_kernel<4, 1, 4>), dim3(rblocks * 8, pl.ksp), dim3(256), 0, st, p, pl.ksp, pl.kb_per); break;
+            }
+            hipLaunchKernelGGL(ap_row_final_kernel, dim3(rows), dim3(kThreads), rf_smem, st, p, pl.ksp);
+            hipLaunchKernelGGL(ap_reduce_kernel, dim3(heads, (LL + kThreads - 1) / kThreads, p.classes), dim3(kThreads), 0, st, p, u0);
         }
-        hipLaunchKernelGGL(ap_row_final_kernel<false>, dim3(rows), dim3(kThreads), rf_smem, st, p, pl.ksp);
-        }
-        const int u0 = g0 / p.NRG, u1 = (g0 + p.nrg - 1) / p.NRG;
-        hipLaunchKernelGGL(ap_reduce_kernel, dim3((u1 - u0 + 1) * p.g, (LL + kThreads - 1) / kThreads, kClasses), dim3(kThreads),
-                           0, st, p, u0);
         if (hipGetLastError() != hipSuccess) return KRUL_ELAUNCH;
     }
     const size_t n_out = (size_t)p.B * LL;
-    hipLaunchKernelGGL(ap_final_kernel, dim3((unsigned)((n_out + 7) / 8)), dim3(kThreads), 0, st, p.B, L, p.Hq,
+    const auto final_kernel = p.classes == kClasses ? ap_final_kernel<kClasses> : ap_final_kernel<2 * kClasses>;
+    hipLaunchKernelGGL(final_kernel, dim3((unsigned)((n_out + 7) / 8)), dim3(kThreads), 0, st, p.B, L, p.Hq,
                        1.0f / (float)p.Tq, p.head_cos, p.head_dist, pair_score, pair_dist, head_score);
     return hipGetLastError() == hipSuccess ? KRUL_OK : KRUL_ELAUNCH;
 }
