@@ -103,6 +103,22 @@ __device__ inline void lds_barrier()
     asm volatile("" ::: "memory");
 }
 
+// Over the eight lanes that share lane % 8, by vector instructions (shuffles go through LDS and take ten times as long):
+// op applied as a butterfly over 8, 16 and 32, the same in each of them.
+template <class Op>
+__device__ inline float over_eighths(float v, Op op)
+{
+    v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x128, 0xF, 0xF, true)));   // row_ror 8
+    const unsigned u = __float_as_uint(v);
+    const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    v = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const unsigned w = __float_as_uint(v);
+    const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ inline float eighths_max(float v) { return over_eighths(v, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ inline float eighths_sum(float v) { return over_eighths(v, [](float a, float b) { return a + b; }); }
+
 constexpr int q_pitch(int ks) { return ks * 32 + 16; }   // bytes of a query row's plane in LDS: 16 rows' 16-byte reads fall into different banks
 
 // KS: MFMA steps of 16 elements that cover the head (head_dim up to 16 * KS; what is past it counts as zero); RB: 32-row blocks per wave; IR: the
@@ -240,9 +256,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
         for (int rb = 0; rb < RB; ++rb) {
             const int mrow = wave * 8 + (lane & 7), pw = lane >> 4, pl = ((lane >> 3) & 1) * 32 + mrow;
             const f32x4 v = part[rb][pw][pl];
-            float M = v.x;
-#pragma unroll
-            for (int o = 8; o < 64; o <<= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
+            float M = eighths_max(v.x);
             const int rrow = rb * 32 + mrow;
             const size_t rec = rec0 + (size_t)l * R_WG + rrow;
             // (pointers that say which memory they lead to: chosen between at run time they would be generic, and a
@@ -260,14 +274,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
                 M = fmaxf(M, rr.x);
             }
             const float f = __builtin_amdgcn_exp2f(v.x - M), fr = __builtin_amdgcn_exp2f(rr.x - M);
-            float zs = v.y * f, ns = v.z * (f * f), cc = v.w * (f * f_prev[rb]), zi = IR ? part_ir[rb][pw][pl] * f : 0.f;
-#pragma unroll
-            for (int o = 8; o < 64; o <<= 1) {
-                zs += __shfl_xor(zs, o, 64);
-                ns += __shfl_xor(ns, o, 64);
-                cc += __shfl_xor(cc, o, 64);
-                if (IR) zi += __shfl_xor(zi, o, 64);
-            }
+            const float zs = eighths_sum(v.y * f), ns = eighths_sum(v.z * (f * f)), cc = eighths_sum(v.w * (f * f_prev[rb]));
+            float zi = IR ? eighths_sum(part_ir[rb][pw][pl] * f) : 0.f;
             const f32x4 out = {M, fmaf(rr.y, fr, zs), fmaf(rr.z, fr * fr, ns), fmaf(rr.w, fr * f_run[rb], cc)};
             if (IR) zi = fmaf(ri, fr, zi);
             f_prev[rb] = f;
