@@ -41,20 +41,28 @@ struct MfmaForm {
     int variant, wr, wk, rb;
     int kt;               // keys per tile
     int resident;         // workgroups that share a CU
-    float step[2];        // us per layer step (one key tile, one layer) at head_dim 64, 128
-    float stream[2];      // TB/s it draws from memory when the whole chip streams keys, at head_dim 64, 128
+    // for calls of more than kShortCall us, see choose_long
+    float step[3];        // us per layer step (one key tile, one layer) with every place taken, heads up to 64, 96, 128
+    float stream[3];      // TB/s it draws from memory when the whole chip streams keys
+    float in_phase;       // steps of two workgroups on a CU that started together take longer: they want the same units at once
+    float start[3];       // us before a workgroup's first step and after its last
+    // for shorter ones, see choose_short
+    float short_step[2], short_stream[2];   // the same at head_dim 64, 128
     constexpr int rows() const { return wr * rb * 32; }
 };
-// Measured (one MI355X; steps: few workgroups, keys in the last-level cache, and full rounds where they are slower;
-// streams: one to eight query tokens over 4096 to 131072 keys, 16 tokens over 32768).
-constexpr MfmaForm kWideForm = {kMfmaWide, 4, 2, 1, 256, 1, {3.1f, 3.4f}, {4.6f, 5.6f}};
-constexpr MfmaForm kWideShortForm = {kMfmaWideShort, 4, 2, 1, 128, 1, {1.85f, 2.2f}, {4.6f, 5.6f}};
-constexpr MfmaForm kMidForm = {kMfmaMid, 2, 4, 1, 512, 1, {3.2f, 3.7f}, {4.6f, 5.6f}};
-constexpr MfmaForm kMidShortForm = {kMfmaMidShort, 2, 2, 1, 128, 2, {1.55f, 2.2f}, {4.1f, 4.9f}};
-constexpr MfmaForm kSlimDeepForm = {kMfmaSlimDeep, 1, 4, 1, 512, 1, {3.0f, 5.87f}, {5.6f, 5.75f}};
-constexpr MfmaForm kSlimShortForm = {kMfmaSlimShort, 1, 4, 1, 256, 2, {1.9f, 2.6f}, {5.05f, 5.25f}};
-constexpr MfmaForm kBigForm = {kMfmaBig, 4, 2, 2, 256, 1, {}, {}};   // (taken by rule, see choose_mfma)
-constexpr float kWorkgroupStart = 5.0f;   // us before a workgroup's first step and after its last
+// Long calls: fitted (one MI355X) to 3870 times of 190 calls of one to 2048 tokens over 72 to 32254 keys, each under up to 40 plans, dense
+// and with strides; the streams of the one-token shapes to calls over 4096 to 131072 keys, beyond the last-level cache.  Short calls: steps of
+// few workgroups, keys in the last-level cache, and full rounds where they are slower; streams of one to eight query tokens over 4096 to
+// 131072 keys, 16 tokens over 32768.
+constexpr MfmaForm kWideForm = {kMfmaWide, 4, 2, 1, 256, 1, {2.55f, 2.75f, 3.2f}, {3.8f, 4.4f, 4.8f}, 1.f, {6.f, 4.f, 2.3f}, {3.1f, 3.4f}, {4.6f, 5.6f}};
+constexpr MfmaForm kWideShortForm = {kMfmaWideShort, 4, 2, 1, 128, 1, {1.65f, 1.9f, 2.05f}, {3.5f, 3.8f, 4.4f}, 1.f, {2.3f, 2.3f, 2.3f}, {1.85f, 2.2f}, {4.6f, 5.6f}};
+constexpr MfmaForm kMidForm = {kMfmaMid, 2, 4, 1, 512, 1, {2.55f, 3.f, 3.4f}, {5.4f, 5.5f, 5.8f}, 1.f, {6.f, 4.f, 2.3f}, {3.2f, 3.7f}, {4.6f, 5.6f}};
+constexpr MfmaForm kMidShortForm = {kMfmaMidShort, 2, 2, 1, 128, 2, {1.22f, 1.5f, 1.93f}, {4.5f, 4.6f, 4.9f}, 1.15f, {2.3f, 2.3f, 2.3f}, {1.55f, 2.2f}, {4.1f, 4.9f}};
+constexpr MfmaForm kSlimDeepForm = {kMfmaSlimDeep, 1, 4, 1, 512, 1, {2.f, 3.6f, 4.f}, {5.7f, 5.9f, 6.1f}, 1.f, {6.f, 6.f, 6.f}, {3.0f, 5.87f}, {5.6f, 5.75f}};
+constexpr MfmaForm kSlimShortForm = {kMfmaSlimShort, 1, 4, 1, 256, 2, {1.4f, 1.8f, 1.8f}, {5.3f, 5.45f, 5.65f}, 1.1f, {2.3f, 2.3f, 2.3f}, {1.9f, 2.6f}, {5.05f, 5.25f}};
+constexpr MfmaForm kBigForm = {kMfmaBig, 4, 2, 2, 256, 1, {6.f, 6.f, 6.f}, {4.3f, 4.3f, 4.3f}, 1.f, {2.3f, 2.3f, 2.3f}, {}, {}};
+constexpr float kShortCall = 82.0f;       // us of the estimate of choose_long (some 8 less than the call takes)
+constexpr float kWorkgroupStart = 5.0f;   // short calls: us before a workgroup's first step and after its last
 constexpr int kCUs = 256;
 
 // What a plan's records may take: 512 MB, or what one round of 128-row workgroups, or `rows` query rows with a single key
@@ -65,7 +73,7 @@ long long record_limit(const krul_shape_t *s, long long rows)
     const long long most = rows > 128ll * kCUs ? rows : 128ll * kCUs, floor = 512ll << 20;
     return most * s->n_layers * 16 > floor ? most * s->n_layers * 16 : floor;
 }
-// us that records take to be written and read back.  A few of them are still in the caches when they are read and cost
+// us that records take to be written and read back (long calls have a fit of their own).  A few of them are still in the caches when they are read and cost
 // next to nothing (117 tokens over 566 keys of 32 heads: 57 us with 10 MB, 66 with the plan that leaves 6), except beside a
 // prefill chunk's uneven splits.
 double record_time(long long bytes, bool chunk)
@@ -87,23 +95,32 @@ struct MfmaChoice {
     long long n_split, tiles_per_split, n_chunks;
 };
 
+long long record_bytes(const krul_shape_t *s, const MfmaForm &f, long long n_split)
+{
+    const long long rows = (long long)s->n_q_heads / s->n_kv_heads * s->n_query;
+    return (long long)s->batch * s->n_kv_heads * ceil_div(rows, f.rows()) * f.rows() * n_split * s->n_layers * 16;
+}
+
 // Which tile shape, how many key splits and how many layer chunks.
 //
-// A workgroup walks (tiles of its key split) x (layers of its chunk) steps one after the other, so a problem takes
-// about  rounds * (steps * step time + start), rounds = workgroups / (CUs * resident) rounded up, and no less than
-// its keys take from memory.  Three things shorten it, and the candidates below are compared by that estimate:
-//   - more key splits, down to one key tile each;
+// A workgroup walks (tiles of its key split) x (layers of its chunk) steps one after the other, and workgroups run in
+// rounds of CUs * resident.  Candidates are compared by an estimate of their time: rounds of steps, or what the keys take from
+// memory, whichever is more.
+//   - key splits: for a number of rounds, or one tile each;
 //   - layer chunks (only where every key split is one tile): the chain of layers is cut into pieces that run side
 //     by side, each reading its first layer a second time.  What a problem too small to fill the chip needs (one
-//     token over 4096 keys 104 -> 63 us, 20 over 300 80 -> 30 us), and what fills a last round that would be nearly
-//     empty (3 x 40 tokens over 3000 keys 404 -> 297 us);
-//   - for more than 64 rows the 64-row shape where 128-row tiles would leave much of the last one empty (the same
-//     example in 64-row tiles: 253 us).
+//     token over 4096 keys 104 -> 60 us, 20 over 300 80 -> 30 us), and what fills a last round that would be nearly
+//     empty;
+//   - tile shapes: for more than 64 rows the 64-row shapes where 128-row tiles would leave much of the last one empty, for
+//     many query rows on dense keys 256 x 256 tiles (two 32-row blocks per wave, the previous layer's exponentials kept
+//     as binary16 pairs: a third fewer bytes per logit and half the operands, but longer workgroups).
 //
-// in_static: for krul_pair_similarity_static.  Its limit on records is the library's own area, so it takes the plan of the
-// call with a workspace where that fits, and the fastest that fits where it does not.  (Preferred in every call, such
-// plans cost 2 x 129 tokens over 7967 keys of an 80-layer model a third of its speed: 144 workgroups on 256 CUs.)
-MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static)
+// There are two estimates.  choose_short's is simple -- rounds, always whole, of steps and a start -- and takes the number of splits for many
+// query rows by rule; its plans of calls of up to 90 us are within 1 % (prefill chunks 12 %) of the best of up to 40.  Longer calls
+// lose by it (10 % on average, up to 1.8 times the time: 1042 tokens over 19743 keys of 32/8 heads 14.9 ms in 272
+// workgroups, one round and a sixteenth, 9.4 in 1768), and choose_long has the last word where its own choice is 7 % faster by
+// its estimate.
+MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static)
 {
     const long long B = s->batch, L = s->n_layers, Hkv = s->n_kv_heads, S = s->n_hist, Tq = s->n_query;
     const long long Rk = s->n_q_heads / Hkv * Tq, d = s->head_dim;
@@ -144,7 +161,7 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, boo
         const double steps = (double)(c.tiles_per_split * (ceil_div(L - 1, chunks) + 1));
         const double layers_read = (double)(L - 1 + chunks);
         const long long record_bytes = n_splits_all * L * f.rows() * 16;
-        double t_steps = ceil(n_wg / slots) * (steps * f.step[d > 64] + kWorkgroupStart);
+        double t_steps = ceil(n_wg / slots) * (steps * f.short_step[d > 64] + kWorkgroupStart);
         const bool chunk = causal && Tq > f.rows();
         if (chunk) {
             // The tiles right of a row tile's diagonal are not walked and splits without a tile left stop at once.  Row
@@ -155,7 +172,7 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, boo
             // one even round, 777 against 799).
             const double tiles_seen = fmin((double)ceil_div(S, f.kt), ((double)S - 0.5 * (double)(Tq - f.rows())) / f.kt + 0.5);
             const double live = (double)(B * Hkv * nrt * chunks) * (c.n_split > 1 ? fmin((double)c.n_split, tiles_seen / (double)c.tiles_per_split + (c.tiles_per_split > 1 ? 0.5 : 0.0)) : 1.0);
-            const double tile_steps = (double)(ceil_div(L - 1, chunks) + 1) * f.step[d > 64];
+            const double tile_steps = (double)(ceil_div(L - 1, chunks) + 1) * f.short_step[d > 64];
             if (live > slots && c.tiles_per_split > 1)
                 t_steps = (double)(B * Hkv * nrt) * tiles_seen * tile_steps / slots + 0.5 * (double)c.tiles_per_split * tile_steps + kWorkgroupStart;
             else
@@ -166,7 +183,7 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, boo
         }
         // (idle places draw no keys: the stream is up to 15 % slower)
         const double bytes = (double)(B * d * 2) * (double)(Hkv * S + s->n_q_heads * Tq) * layers_read;
-        const double t_stream = bytes / (f.stream[d > 64] * 1e6 * fmin(1.0, 0.85 + 0.15 * n_wg / slots)) + kWorkgroupStart;
+        const double t_stream = bytes / (f.short_stream[d > 64] * 1e6 * fmin(1.0, 0.85 + 0.15 * n_wg / slots)) + kWorkgroupStart;
         // (slim tiles have next to nothing to do but wait for keys; the others' steps hide most of the stream)
         const double t = fmax(t_steps, t_stream) + record_time(record_bytes, chunk) + (Rk > 32 ? 0.1 * fmin(t_steps, t_stream) : 0.0);
         // The fastest within the limit on records; where none is, the one with the fewest.
@@ -210,6 +227,122 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, boo
         consider_form(kMidShortForm);
     }
     return best;
+}
+
+// o: the plan of choose_short, which stays unless there is one that takes 7 % less.
+MfmaChoice choose_long(const krul_shape_t *s, bool want_ir, bool plain_keys, const MfmaChoice &o)
+{
+    const long long B = s->batch, L = s->n_layers, Hkv = s->n_kv_heads, S = s->n_hist, Tq = s->n_query;
+    const long long Rk = s->n_q_heads / Hkv * Tq, d = s->head_dim;
+    const long long limit = record_limit(s, B * Hkv * ceil_div(Rk, 128) * 128);
+    const bool single = (s->flags & KRUL_FLAG_SINGLE_SPLIT) != 0, causal = (s->flags & KRUL_FLAG_CAUSAL) != 0;
+    const auto splits = [&](const MfmaForm &f, long long want, long long chunks) {
+        const long long tiles = ceil_div(S, f.kt), n = want < 1 || single ? 1 : (want < tiles ? want : tiles);
+        const long long tps = ceil_div(tiles, n);
+        return MfmaChoice{&f, ceil_div(tiles, tps), tps, chunks};
+    };
+
+    MfmaChoice best = {nullptr, 0, 0, 0};
+    double best_t = 0.0;
+    long long best_bytes = 0;
+    const int dc = d <= 64 ? 0 : d <= 96 ? 1 : 2;
+    // us of a plan but for what they all have in common
+    const auto time_of = [&](const MfmaForm &f, const MfmaChoice &c, long long records) {
+        const long long nrt = ceil_div(Rk, f.rows());
+        const double slots = (double)kCUs * f.resident, n = (double)(B * Hkv * nrt * c.n_split * c.n_chunks), rounds = ceil(n / slots);
+        // (workgroups in patches share keys and query rows through the L2: four splits of eight row tiles 61.4 ms, one 68.4)
+        const int patch = patch_rows((int)nrt, (int)c.n_split);
+        const double shared = f.variant == kMfmaBig && patch == 8 ? 0.96 : f.variant == kMfmaWide && patch ? 0.98 : 1.0;
+        const double walk = (double)(c.tiles_per_split * (ceil_div(L - 1, c.n_chunks) + 1)) * f.step[dc] * shared;   // one workgroup's
+        const auto part = [](double taken) { return 0.8 + 0.2 * taken; };   // of a step's time with that share of the places taken
+        double t;
+        if (causal && Tq > f.rows()) {
+            // A prefill chunk: the tiles right of a row tile's diagonal are not walked and splits without a tile left stop at
+            // once.  Row tiles see S - Tq/2 + rows/2 keys on average.  Splits of one tile are alike; longer ones differ, and the last of
+            // them run beside idle CUs for about half a split.  Workgroups that stop at once upset the hand-out of the
+            // others: more than a round with them is hardly better than two rounds.
+            const double seen = fmin((double)ceil_div(S, f.kt), ((double)S - 0.5 * (double)(Tq - f.rows())) / f.kt + 0.5);
+            const double of_splits = fmin((double)c.n_split, seen / (double)c.tiles_per_split + (c.tiles_per_split > 1 ? 0.5 : 0.0));
+            const double live = (double)(B * Hkv * nrt * c.n_chunks) * of_splits;
+            const double full = c.tiles_per_split > 1 ? fmin(1.0, seen / ((double)c.tiles_per_split * of_splits)) : 1.0;   // of a live split's tiles
+            if (live > slots) t = (1.05 * full * live / slots + 0.5) * walk;
+            else if (n > slots && live > 0.5 * slots) t = 1.7 * walk;
+            else t = walk * (live > kCUs ? f.in_phase : 1.0) * part(live / slots);
+            t += f.start[dc];
+        } else {
+            const double full = floor(n / slots), last = n / slots - full;
+            t = (full + (last > 0.0 ? part(last) : 0.0)) * walk * (n > kCUs ? 1.0 + (f.in_phase - 1.0) / rounds : 1.0) + rounds * f.start[dc];
+        }
+        // (keys that several row tiles read are not always found in the L2; idle places draw none)
+        const double bytes = (double)(B * d * 2) * ((double)(Hkv * S) * (nrt > 1 ? 1.28 : 1.0) + (double)(s->n_q_heads * Tq)) * (double)(L - 1 + c.n_chunks);
+        const double stream = bytes / (f.stream[dc] * 1e6 * (0.77 + 0.23 * n / slots / rounds)) + f.start[dc];
+        return sqrt(sqrt(t * t * t * t + stream * stream * stream * stream)) + 0.34 * fmax(0.0, (double)records / 1e6 - 10.0);
+    };
+    const double to_beat = 0.93 * time_of(*o.form, o, record_bytes(s, *o.form, o.n_split));
+    if (to_beat <= kShortCall) return o;   // (the candidates take the host 1 to 5 us)
+    const auto consider = [&](const MfmaForm &f, long long want, long long chunks, bool over_limit = false) {
+        const MfmaChoice c = splits(f, want, chunks);
+        if (chunks > 1 && c.tiles_per_split > 1) return;
+        const long long bytes = record_bytes(s, f, c.n_split);
+        const double t = time_of(f, c, bytes);
+        // The fastest within the limit on records; where none is, the one with the fewest.
+        const long long over = over_limit ? 0 : bytes;
+        if (!best.form || (over <= limit ? best_bytes > limit || t < best_t : best_bytes > limit && over < best_bytes)) {
+            best = c;
+            best_t = t;
+            best_bytes = over;
+        }
+    };
+    const auto consider_form = [&](const MfmaForm &f) {
+        const long long tiles = ceil_div(S, f.kt), nrt = ceil_div(Rk, f.rows()), units = B * Hkv * nrt;
+        const long long slots = (long long)kCUs * f.resident;
+        // Splits of several tiles for one to eight rounds, or all of the keys -- not for up to 64 rows, where the stream of keys is
+        // the bound: a split of several tiles parks its running records in memory between tiles, and that cost a quarter of
+        // the bandwidth (a decode step over 131072 tokens: 57 % of 8 TB/s against 74 % with one tile per split) -- then one
+        // tile per split and the layers in chunks.
+        if (Rk > 64) {
+            for (int r = 1; r <= 8 && slots * r / units < tiles; ++r) consider(f, slots * r / units, 1);
+            // row tiles in patches of eight by four splits (their records are allowed beyond the limit, up to four times
+            // the least)
+            if (nrt % 8 == 0 && tiles >= 16) consider(f, 4, 1, &f == &kBigForm);
+        }
+        const long long most = tiles < 1024 ? tiles : 1024;
+        consider(f, most, 1);
+        // (the deep ring takes too long to fill for a piece of the chain; the many-query kernel takes the whole of it)
+        if (most < tiles || single || &f == &kSlimDeepForm || &f == &kBigForm) return;
+        // (Few cuts, spread over their logarithm; those of 31 pairs that shorten the longest chunk.  A model's own -- ceil(pairs / k) for k = 1,
+        // 2, ... -- were tried in their place: 0.91 to 1.17 times the speed over 30 calls of 24 to 80 layers, 0.99 on average.)
+        static const int kChunks[] = {2, 3, 4, 5, 6, 8, 11, 16, 31};
+        for (const int c : kChunks) {
+            if (c > L - 1 || units * tiles * c > 8 * slots) break;
+            consider(f, tiles, c);
+        }
+    };
+    if (Rk <= 32) {
+        consider_form(kSlimDeepForm);
+        consider_form(kSlimShortForm);
+    } else {
+        if (Rk > 64) {
+            consider_form(kWideForm);
+            consider_form(kWideShortForm);
+            if (plain_keys && !want_ir && !causal && d == 128 && Rk > 128) consider_form(kBigForm);
+        }
+        consider_form(kMidForm);
+        consider_form(kMidShortForm);
+    }
+    return best_t > kShortCall && best_t < to_beat ? best : o;
+}
+
+// in_static: for krul_pair_similarity_static.  Its limit on records is the library's own area: the plan of the call with a
+// workspace where that fits, and otherwise choose_short's within the limit.  (What that does not fit is refused: large calls
+// with many query rows, which should bring a workspace.)
+MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static)
+{
+    const MfmaChoice c = choose_long(s, want_ir, plain_keys, choose_short(s, want_ir, plain_keys, false));
+    if (!in_static) return c;
+    const auto fits = [&](const MfmaChoice &m) { return record_bytes(s, *m.form, m.n_split) <= static_limit(s); };
+    const MfmaChoice o = choose_short(s, want_ir, plain_keys, true);
+    return fits(o) && fits(c) ? c : o;
 }
 
 }  // namespace

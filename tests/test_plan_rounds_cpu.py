@@ -1,0 +1,22 @@
+"""Plans of long calls: the workgroups fill the rounds they run in, within the limit on records, whatever the number of row tiles."""
+import math
+
+import pytest
+
+import paper_2507_08045_amd as kr
+
+# (B, L, Hq, Hkv, d, S, Tq): numbers of units and row tiles for which ceil(256 / tiles) splits are just over one round
+SHAPES = [(1, 32, 32, 8, 128, 19743, 1042), (3, 32, 32, 8, 128, 12162, 128), (1, 32, 32, 8, 128, 27723, 299), (2, 32, 32, 8, 128, 15337, 175),
+          (6, 32, 32, 8, 128, 2702, 700), (1, 32, 32, 8, 128, 2573, 806), (5, 32, 32, 8, 128, 971, 417), (2, 24, 16, 4, 64, 18625, 120)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"{s[0]}x{s[6]}-over-{s[5]}")
+def test_rounds_are_full(shape):
+    B, L, Hq, Hkv, d, S, Tq = shape
+    sh = kr.KrulShape(*shape, kr.KRUL_BF16, 0.0, 0)
+    p = kr.plan(sh)
+    places = 512 if p["form"] in (5, 6) else 256   # workgroups that run side by side
+    rounds = p["n_workgroups"] / places
+    assert rounds / math.ceil(rounds) >= 0.85, p
+    assert kr.workspace_bytes(sh) <= (520 << 20)
+
