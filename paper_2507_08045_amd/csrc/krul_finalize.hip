@@ -1,16 +1,18 @@
 // Row similarity and token-wise aggregation (Sec. 5 / Sec. 7: per-token similarities
 // are added up; Sec. 4.2: the average over heads).
 //
-// finalize_heads: one workgroup per (conversation, pair, query head).  A few lanes
-// share each query row: they merge the row's partial records of the two layers
+// finalize_heads: a workgroup per (conversation, pair, query head), or a wave per few heads of a kv head.  A few
+// lanes share each query row: they merge the row's partial records of the two layers
 // onto a common reference exponent (fixed butterfly order), form the cosine and
 // (from the a^2 + b^2 - 2ab expansion of Sec. 7) the Euclidean distance of the two
-// attention rows, and the workgroup sums over rows in a fixed tree order.
+// attention rows, and the sum over rows is taken in a fixed tree order.
 // finalize_pairs: 32 lanes per (conversation, pair) average the heads (pair_average).
 //
-// These kernels are bound by the latency of their few loads, unless there are thousands of rows: record addresses are
-// one multiplication apart, and a lane asks for the records of four partials at once.  (One merge after the other,
-// each load waited for: 7.9 us for 64 rows of 992 heads with 16 partials, 6.9 us now; 36 -> 29 us for 2048 rows.)
+// These kernels are bound by the latency of one chain of steps, unless there are thousands of rows: which rows, their
+// records, the merges, the sums.  So the rows are found without a division, a lane asks for the records of four partials at once (one
+// merge after the other, each load waited for: 7.9 us for 64 rows of 992 heads with 16 partials, 6.9 so) and
+// everything between lanes goes by vector instructions (with
+// divisions and shuffles: 4.0 us for 6 heads of 16 rows, 3.7 so; an empty kernel takes 2.5).
 #include "krul_common.h"
 #include "krul_select_core.h"
 
@@ -53,23 +55,45 @@ __device__ inline void merge_into(RowAcc &r, float ma, float za, float na, float
     r.Mb = Mb;
 }
 
+template <int OFF>
+__device__ inline void join(RowAcc &r)
+{
+    const float ma = across<OFF>(r.Ma), za = across<OFF>(r.Za), na = across<OFF>(r.Na), mb = across<OFF>(r.Mb);
+    const float zb = across<OFF>(r.Zb), nb = across<OFF>(r.Nb), c = across<OFF>(r.C);
+    merge_into(r, ma, za, na, mb, zb, nb, c);
+}
+
+// n / d for n < 2^31 by a multiplication: m = floor(2^32 (2^s - d) / d) + 1 with s = ceil(log2 d) (Granlund and Montgomery, "Division by
+// invariant integers using multiplication").
+struct Div {
+    unsigned d, m, s;
+    static Div by(unsigned d)
+    {
+        unsigned s = 0;
+        while ((1ull << s) < d) ++s;
+        return {d, (unsigned)((((1ull << s) - d) << 32) / d) + 1u, s};
+    }
+    __device__ unsigned operator()(unsigned n) const { return (__umulhi(n, m) + n) >> s; }
+};
+
 // Where a row's records of layer l are: partial p at at + p * step (see state_index).
 struct RowRecords {
     size_t at, step;
     int next_layer;   // from a layer's record to the next layer's
 };
-__device__ inline RowRecords row_records(const StateLayout &y, int u, int r, int l)
+__device__ inline RowRecords row_records(const StateLayout &y, const Div &by_tile, int u, int r, int l)
 {
     RowRecords q;
     if (y.variant == kGeneric) {
         q.step = (size_t)y.n_layers;
         q.next_layer = 1;
+        q.at = ((size_t)u * y.rows_per_unit + r) * y.n_split * y.n_layers + l;
     } else {
-        const int r_wg = y.wr * y.rb * 32;
+        const unsigned r_wg = by_tile.d, rt = by_tile((unsigned)r);
         q.step = (size_t)y.n_row_tiles * y.n_layers * r_wg;
-        q.next_layer = r_wg;
+        q.next_layer = (int)r_wg;
+        q.at = (((size_t)u * y.n_split * y.n_row_tiles + rt) * y.n_layers + l) * r_wg + ((unsigned)r - rt * r_wg);
     }
-    q.at = state_index(y, u, r, 0, l);
     return q;
 }
 
@@ -79,9 +103,13 @@ struct HeadsArgs {
     StateLayout lay;
     const float4 *state;
     const float *state_ir;
-    int L, Hq, Hkv, Tq, G;
+    int L, Hq, Hkv, Tq;
+    int G;               // lanes that share a row; a wave takes 64 / G rows
+    int TP, H;           // PER_WAVE: rows of a head (Tq, to a power of two), heads of a wave
+    int groups;          // ceil(heads per kv head / H)
+    Div by_groups, by_hkv, by_pairs, by_tile;   // divisions by groups, Hkv, L - 1, the rows of a row tile
     int want_dist, accumulate;
-    int n_items;   // (conversation, pair, head) triples; the (conversation, layer, head) triples of the layer test follow
+    int n_items;   // (conversation, pair, kv head, group of heads); the (conversation, layer, head) triples of the layer test follow
     int n_all;
     int first;     // of this launch
     float *head_cos, *head_dist, *head_ir;
@@ -91,11 +119,11 @@ struct HeadsArgs {
 // each merges the partials p = g, g+G, ... and a butterfly over g joins them.  Lanes with
 // the same g read consecutive rows, i.e. consecutive records.
 //
-// PER_WAVE (few rows: all of a head's rows fit the lanes of one wave, G * Tq <= 64): every wave takes a
-// (conversation, pair, query head) of its own and sums the rows by shuffles -- a decode step has one row
-// per head, and a workgroup per head would be 252 idle threads and four times the workgroups.
-//
-// Calls f(t, row, g, RW) for the lanes' rows; RW rows share a wave's 64 lanes.
+// PER_WAVE (few rows): a wave takes H heads of a kv head by itself -- their rows lie one after the other --, lanes
+// g*(64/G) + h*TP + t.  A decode step has one row per head: a wave per head would read 64 bytes for 16 and leave three lanes in
+// four idle (8 x 992 heads of 8 partials: 10.0 us, 5.2 so).
+
+// The layer test's rows of head h: calls f(t, row, g, RW) for the lanes' rows; RW rows share a wave's 64 lanes.
 template <bool PER_WAVE, class F>
 __device__ inline void for_rows(const HeadsArgs &p, int h, F f)
 {
@@ -115,16 +143,29 @@ __device__ inline float sum_rows(float v, float *red)
     return v;
 }
 
+// Sum over n lanes (a power of two), the same in each of them.
+__device__ inline float sum_over(float v, int n)
+{
+    if (n > 32) v += across<32>(v);
+    if (n > 16) v += across<16>(v);
+    if (n > 8) v += across<8>(v);
+    if (n > 4) v += across<4>(v);
+    if (n > 2) v += across<2>(v);
+    if (n > 1) v += across<1>(v);
+    return v;
+}
+
 // IR: also the Initial-Recent layer test (Sec. 4.2; Alg. 1 first loop): per (conversation, layer, head) the
 // mean over query rows of Zir / Z -- the attention mass on T_initial and T_recent -- from the
 // partial records of each row, merged onto a common exponent like the similarity sums.
 template <bool PER_WAVE, bool IR>
 __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
 {
-    __shared__ float red[kThreads / 64];
-    int item = p.first + (PER_WAVE ? blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6) : blockIdx.x);
+    __shared__ float red[IR && !PER_WAVE ? kThreads / 64 : 1];
+    __shared__ float2 red2[PER_WAVE ? 1 : kThreads / 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int item = p.first + (PER_WAVE ? blockIdx.x * (kThreads / 64) + wave : blockIdx.x);
     if (PER_WAVE && item >= p.n_all) return;   // (a whole wave: no barrier follows in this form)
-    const bool first = (PER_WAVE ? threadIdx.x & 63 : threadIdx.x) == 0;
     const int P = p.lay.partials;
 
     if (IR && item >= p.n_items) {
@@ -134,7 +175,7 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
         for_rows<PER_WAVE>(p, h, [&](int t, int r, int g, int RW) {
             float M = kMInit, Z = 0.f, I = 0.f;
             if (t < p.Tq) {
-                const RowRecords q = row_records(p.lay, u, r, l);
+                const RowRecords q = row_records(p.lay, p.by_tile, u, r, l);
                 for (int p0 = g; p0 < P; p0 += kBatch * p.G) {
                     float am[kBatch], az[kBatch], ai[kBatch];
 #pragma unroll
@@ -166,16 +207,30 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
             if (t < p.Tq && g == 0) mass += I / Z;
         });
         mass = sum_rows<PER_WAVE>(mass, red);
-        if (first) p.head_ir[item] = mass / (float)p.Tq;
+        if ((PER_WAVE ? lane : threadIdx.x) == 0) p.head_ir[item] = mass / (float)p.Tq;
         return;
     }
 
-    const int NP = p.L - 1, h = item % p.Hq, l = item / p.Hq % NP, u = item / (p.Hq * NP) * p.Hkv + h / (p.Hq / p.Hkv);
+    // (conversation b, pair l, kv head, group of heads): each is the remainder of a division
+    const int t1 = p.groups > 1 ? (int)p.by_groups(item) : item, group = item - t1 * p.groups;
+    const int bl = (int)p.by_hkv(t1), kvh = t1 - bl * p.Hkv;
+    const int b = (int)p.by_pairs(bl), l = bl - b * (p.L - 1), u = b * p.Hkv + kvh;
+    const int RW = 64 / p.G, g = lane / RW, in_wave = lane % RW;   // (powers of two)
+    const int heads = p.lay.rows_per_unit / p.Tq;   // of the kv head
+    const int head = group * p.H + (PER_WAVE ? in_wave / p.TP : 0), t_first = PER_WAVE ? in_wave % p.TP : wave * RW + in_wave;
+    const int out = bl * p.Hq + kvh * heads + head;
+    const bool writes = head < heads && (PER_WAVE ? g == 0 && t_first == 0 : threadIdx.x == 0);
+    float old_cos = 0.f, old_dist = 0.f;   // token-wise running sums over several calls (Sec. 5, Sec. 7 "adds up")
+    if (p.accumulate && writes) {
+        old_cos = p.head_cos[out];
+        if (p.want_dist) old_dist = p.head_dist[out];
+    }
     float cs = 0.f, ds = 0.f;
-    for_rows<PER_WAVE>(p, h, [&](int t, int r, int g, int RW) {
+    for (int t = t_first; t - t_first < p.Tq; t += PER_WAVE ? 64 : kThreads / 64 * RW) {   // (PER_WAVE: once)
         RowAcc acc = {kMInit, 0.f, 0.f, kMInit, 0.f, 0.f, 0.f};
-        if (t < p.Tq) {
-            const RowRecords q = row_records(p.lay, u, r, l);
+        const bool row = t < p.Tq && head < heads;
+        if (row) {
+            const RowRecords q = row_records(p.lay, p.by_tile, u, head * p.Tq + t, l);
             for (int p0 = g; p0 < P; p0 += kBatch * p.G) {
                 float4 a[kBatch], c[kBatch];
 #pragma unroll
@@ -189,14 +244,13 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
                     if (p0 + i * p.G < P) merge_into(acc, a[i].x, a[i].y, a[i].z, c[i].x, c[i].y, c[i].z, c[i].w);
             }
         }
-        for (int off = 32; off >= RW; off >>= 1) {
-            const float ma = __shfl_xor(acc.Ma, off, 64), za = __shfl_xor(acc.Za, off, 64);
-            const float na = __shfl_xor(acc.Na, off, 64), mb = __shfl_xor(acc.Mb, off, 64);
-            const float zb = __shfl_xor(acc.Zb, off, 64), nb = __shfl_xor(acc.Nb, off, 64);
-            const float c = __shfl_xor(acc.C, off, 64);
-            merge_into(acc, ma, za, na, mb, zb, nb, c);
-        }
-        if (t < p.Tq && g == 0) {
+        if (RW <= 32) join<32>(acc);
+        if (RW <= 16) join<16>(acc);
+        if (RW <= 8) join<8>(acc);
+        if (RW <= 4) join<4>(acc);
+        if (RW <= 2) join<2>(acc);
+        if (RW <= 1) join<1>(acc);
+        if (row && g == 0) {
             cs += acc.C * rsqrtf(acc.Na * acc.Nb);
             if (p.want_dist) {   // (Z is only accumulated when the distance is asked for)
                 const float ia = 1.f / acc.Za, ib = 1.f / acc.Zb;
@@ -204,16 +258,25 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
                 ds += sqrtf(fmaxf(d2, 0.f));
             }
         }
-    });
-    cs = sum_rows<PER_WAVE>(cs, red);
-    ds = sum_rows<PER_WAVE>(ds, red);
-    if (first) {
-        if (p.accumulate) {   // token-wise running sums over several calls (Sec. 5, Sec. 7 "adds up")
-            p.head_cos[item] += cs;
-            if (p.want_dist) p.head_dist[item] += ds;
+    }
+    cs = sum_over(cs, PER_WAVE ? p.TP : RW);
+    ds = sum_over(ds, PER_WAVE ? p.TP : RW);
+    if constexpr (!PER_WAVE) {
+        if (lane == 0) red2[wave] = make_float2(cs, ds);
+        __syncthreads();
+        cs = ds = 0.f;
+        for (int i = 0; i < kThreads / 64; ++i) {
+            cs += red2[i].x;
+            ds += red2[i].y;
+        }
+    }
+    if (writes) {
+        if (p.accumulate) {
+            p.head_cos[out] = old_cos + cs;
+            if (p.want_dist) p.head_dist[out] = old_dist + ds;
         } else {
-            p.head_cos[item] = cs / (float)p.Tq;
-            p.head_dist[item] = ds / (float)p.Tq;
+            p.head_cos[out] = cs / (float)p.Tq;
+            p.head_dist[out] = ds / (float)p.Tq;
         }
     }
 }
@@ -296,23 +359,32 @@ hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, i
     p.Tq = Tq;
     p.want_dist = pair_dist != nullptr;
     p.accumulate = accumulate ? 1 : 0;
-    p.n_items = B * (L - 1) * Hq;
-    p.n_all = p.n_items + (ir ? B * L * Hq : 0);
     p.head_cos = head_cos;
     p.head_dist = head_dist;
     if (ir) {
         p.state_ir = ir->state_ir;
         p.head_ir = ir->head_ir;
     }
-    p.G = 1;
-    if (Tq <= 8) {   // few rows: a wave per head, G lanes per row with G * Tq <= 64
-        while (p.G * 2 * Tq <= 64 && p.G < lay.partials) p.G <<= 1;
-        launch_heads<true>(p, ir != nullptr, st);
+    const int heads = Hq / Hkv;
+    p.G = p.TP = p.H = 1;
+    const bool per_wave = Tq <= 8;
+    if (per_wave) {   // few rows: heads of a kv head as long as a lane has one batch of partials, lanes left over share rows
+        while (p.TP < Tq) p.TP <<= 1;
+        while (p.H < heads && 2 * p.H * p.TP <= 64 && 64 / (2 * p.H * p.TP) * kBatch >= lay.partials) p.H <<= 1;
+        while (p.G * 2 * p.H * p.TP <= 64 && p.G < lay.partials) p.G <<= 1;
     } else {
         // lanes per row: enough to keep a workgroup's 256 threads busy, at most one per partial
         while (p.G < 64 && p.G * Tq < kThreads && p.G < lay.partials) p.G <<= 1;
-        launch_heads<false>(p, ir != nullptr, st);
     }
+    p.groups = (heads + p.H - 1) / p.H;
+    p.by_groups = Div::by((unsigned)p.groups);
+    p.by_hkv = Div::by((unsigned)Hkv);
+    p.by_pairs = Div::by((unsigned)L - 1);
+    p.by_tile = Div::by(lay.variant == kGeneric ? 1u : (unsigned)(lay.wr * lay.rb * 32));
+    p.n_items = B * (L - 1) * Hkv * p.groups;
+    p.n_all = p.n_items + (ir ? B * L * Hq : 0);
+    if (per_wave) launch_heads<true>(p, ir != nullptr, st);
+    else launch_heads<false>(p, ir != nullptr, st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || accumulate || !pair_cos) return e;   // (no pair scores asked for: the caller forms them)
     PairsArgs a = {};

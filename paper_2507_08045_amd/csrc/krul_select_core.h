@@ -15,6 +15,26 @@
 
 namespace krul {
 
+// The value of the lane OFF places on (lane ^ OFF), by vector instructions: a shuffle goes through LDS and takes ten times
+// as long, and sums of this kind stand one after the other.
+template <int OFF>
+__device__ inline float across(float v)
+{
+    static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8 || OFF == 16 || OFF == 32, "a power of two below 64");
+    const int i = __builtin_bit_cast(int, v);
+    if constexpr (OFF >= 16) {   // (the lower and the upper rows' values, in every lane)
+        const auto r = OFF == 32 ? __builtin_amdgcn_permlane32_swap((unsigned)i, (unsigned)i, false, false)
+                                 : __builtin_amdgcn_permlane16_swap((unsigned)i, (unsigned)i, false, false);
+        return __uint_as_float(__lane_id() & OFF ? r[0] : r[1]);
+    }
+    int o;
+    if constexpr (OFF == 8) o = __builtin_amdgcn_mov_dpp(i, 0x128, 0xF, 0xF, true);        // row_ror 8
+    else if constexpr (OFF == 2) o = __builtin_amdgcn_mov_dpp(i, 0x4E, 0xF, 0xF, true);    // quad_perm 2 3 0 1
+    else if constexpr (OFF == 1) o = __builtin_amdgcn_mov_dpp(i, 0xB1, 0xF, 0xF, true);    // quad_perm 1 0 3 2
+    else o = __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(i, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);   // row_half_mirror (7), quad_perm 3 2 1 0
+    return __builtin_bit_cast(float, o);
+}
+
 // Average of a pair's Hq head values (times scale) by the 32 lanes of a half-wave: lane k takes heads k, k + 32, ... in
 // order, a butterfly adds the lanes' sums.  The one order in which heads are averaged, whichever kernel does it.
 // out: the scaled values go there, if anywhere; it may be head (every value is read once).
@@ -26,8 +46,11 @@ __device__ inline float pair_average(const float *head, int Hq, float scale, int
         if (out) out[h] = v;
         s += v;
     }
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o, 32);
+    s += across<16>(s);
+    s += across<8>(s);
+    s += across<4>(s);
+    s += across<2>(s);
+    s += across<1>(s);
     return s / (float)Hq;
 }
 
