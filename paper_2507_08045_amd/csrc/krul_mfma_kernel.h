@@ -24,7 +24,7 @@
 // per layer step from their LDS staging area).  In the result every lane owns ONE query
 // row (column lane%32) and 16 keys, so all softmax sums are lane-local: no cross-lane
 // traffic in the loop.  Lanes l and l+32 and the WK waves along the keys are independent
-// partials of a row, merged one step late by the first wave of each wave row.
+// partials of a row, merged one step late by one wave of each wave row.
 //
 // Software pipeline.  While a wave takes the exponentials of chunk c's block it issues the
 // MFMA chain that forms chunk c+1's logits (double-buffered accumulators); the order
@@ -376,10 +376,13 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
         return a;
     };
 
+    // The wave along the keys that merges its wave row's partials.  Waves w and w + 4 share a SIMD: eight waves' mergers are
+    // on SIMDs of their own, and each has a neighbour that does not merge (all of wk 0: 1 to 3 % slower, two SIMDs waited for the others).
+    const int merger = C::NW == 8 ? wr * WK / 4 % WK : 0;
     // Splits that span several key tiles: a row's running record (layer l, all keys so far) is the row
     // record the merge below stores after every tile; at the next tile ONE of the row's partials -- the
-    // first half-wave of the first wave along the keys -- takes it up again, the others start empty.
-    const bool carries = wk == 0 && half == 0;
+    // first half-wave of the merging wave -- takes it up again, the others start empty.
+    const bool carries = wk == merger && half == 0;
     const size_t row_rec = rec0 + wr * 32 + l32;   // + l * R_WG: this lane's row, layer l
 
     float e[NBLK][16];
@@ -410,7 +413,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
     int step = 0;   // layer steps done
     // The 2*WK partials of a row (two half-waves, WK waves) are merged one step late, so that
     // the merge costs no barrier of its own: at the end of a step every lane posts its record
-    // in LDS; after the next chunk barrier the first wave of each wave row brings the partials
+    // in LDS; after the next chunk barrier one wave of each wave row brings the partials
     // of its rows onto their common exponent, adds them in a fixed order and stores the row
     // records (after every tile: the stored record is also the running record the next tile starts from).  The cross term of partial p carries the exponents of two layers: gprev[p] is
     // the factor that took p's exponent of the previous layer onto that layer's merged one.
@@ -491,7 +494,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
                     __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0((PF - 1) * NLD));
                 __builtin_amdgcn_s_barrier();
                 if (c == 0 && mg_on) {
-                    if (wk == 0) merge_rows();
+                    if (wk == merger) merge_rows();
                     mg_on = false;
                 }
                 if (c == 0) {
@@ -663,7 +666,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
     if (mg_on) {
         __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
         __builtin_amdgcn_s_barrier();
-        if (wk == 0) merge_rows();
+        if (wk == merger) merge_rows();
     }
 }
 
