@@ -259,27 +259,51 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
     };
     // Paged keys: a copy instruction moves RPI whole keys, which lie in one page (pages hold a power of
     // two >= 8 keys and tiles start on multiples of them); its page comes from the conversation's block
-    // table by a scalar load, and it gets a descriptor of its own, bounded by the keys that exist.
+    // table, and it gets a descriptor of its own, bounded by the keys that exist.
     // (On this chip the scalar offset of a buffer instruction takes part in the range check, like the
     // lane offset: the dense path below relies on that.)
     typedef const __attribute__((address_space(4))) int *const_i32_ptr;
     const const_i32_ptr page_row = KA == 2 ? (const_i32_ptr)(uintptr_t)(p.block_table + (size_t)b * p.max_blocks) : nullptr;
-    // Where each copy instruction of a tile starts, relative to the layer's pool (wave-uniform, in scalar
-    // registers).  Every layer has the same pages, so the table is read once per tile, not once per
-    // layer step: a lookup inside the step would make the wave wait for the scalar load at every chunk.
-    long long page_off[KA == 2 ? NC : 1][KA == 2 ? NLD : 1];   // in elements
+    // Where each copy instruction of a tile starts, relative to the layer's pool, and how many of them, in this order, have
+    // keys to copy.  Every layer has the same pages, so the table is read once per tile, not once per
+    // layer step: a lookup inside the step would make the wave wait for the load at every chunk.  Up to eight offsets are kept in
+    // scalar registers; more (16 or 32 of 64 bits) have no room there beside the rest and a lane each.  (Left to the compiler,
+    // which kept 70 to 190 scalar registers in lanes: one token over 4096 keys 53.5 us, 52.4 so, 8 of them 378 and 370.  Eight
+    // offsets in lanes as well: 512 tokens over 3575 keys 739 us, 724 so.)
+    constexpr bool LANES = KA == 2 && NC * NLD > 8;
+    static_assert(!LANES || NC * NLD <= 64, "a lane per copy instruction");
+    long long page_off[KA == 2 && !LANES ? NC : 1][KA == 2 && !LANES ? NLD : 1];   // in bytes
+    [[maybe_unused]] int off_lo = 0, off_hi = 0;   // LANES: of the lane's instruction
+    [[maybe_unused]] int n_copies = 0;
     auto load_pages = [&](int tile_key0) __attribute__((always_inline)) {
-        if constexpr (KA == 2) {
+        if constexpr (LANES) {
+            const int krow = tile_key0 + lane / NLD * C::CH + (wave * NLD + lane % NLD) * RPI, kcl = min(krow, S - 1);
+            const long long off = ((long long)p.block_table[(size_t)b * p.max_blocks + (kcl >> p.page_shift)] * p.k_stride_page +
+                                   (long long)(kcl & ((1 << p.page_shift) - 1)) * (long long)k_stride_s) * 2;
+            off_lo = (int)off;
+            off_hi = (int)(off >> 32);
+            n_copies = __popcll(__ballot(lane < NC * NLD && krow < S));
+        } else if constexpr (KA == 2) {
             const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+            n_copies = 0;
 #pragma unroll
             for (int c = 0; c < NC; ++c)
 #pragma unroll
                 for (int j = 0; j < NLD; ++j) {
-                    const int kcl = min(tile_key0 + c * C::CH + (wave_u * NLD + j) * RPI, S - 1);   // (stay inside the table row)
-                    page_off[c][j] = (long long)page_row[kcl >> p.page_shift] * p.k_stride_page +
-                                     (long long)(kcl & ((1 << p.page_shift) - 1)) * (long long)k_stride_s;
+                    const int krow = tile_key0 + c * C::CH + (wave_u * NLD + j) * RPI;
+                    const int kcl = min(krow, S - 1);   // (stay inside the table row)
+                    page_off[c][j] = ((long long)page_row[kcl >> p.page_shift] * p.k_stride_page +
+                                      (long long)(kcl & ((1 << p.page_shift) - 1)) * (long long)k_stride_s) * 2;
+                    n_copies += krow < S ? 1 : 0;
                 }
         }
+    };
+    auto copy_off = [&](int c, int j) __attribute__((always_inline)) -> long long {
+        if constexpr (LANES)
+            return (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane(off_hi, c * NLD + j) << 32) |
+                               (unsigned)__builtin_amdgcn_readlane(off_lo, c * NLD + j));
+        else
+            return page_off[c][j];
     };
     load_pages(key_begin);
     const unsigned page_copy_bytes = (unsigned)(RPI - 1) * k_row_bytes + d_bytes;
@@ -287,20 +311,20 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
         unsigned char *dst = slot_ptr(c);
         const int key0 = fetch_key0 + c * C::CH;
         if constexpr (KA == 2) {
-            const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+            int dst0 = __builtin_amdgcn_readfirstlane(wave) * NLD * 1024;
+            asm volatile("" : "+s"(dst0));   // (opaque: every copy's place in LDS would else be kept in a scalar register of its own, and there are not so many)
 #pragma unroll
             for (int j = 0; j < NLD; ++j) {
-                const int krow = key0 + (wave_u * NLD + j) * RPI;        // first key of this instruction
-                const uint16_t *base = fetch_k + page_off[c][j];
+                const uint16_t *base = reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(fetch_k) + copy_off(c, j));
                 // All RPI keys or none: a page has room for all its keys, so the ones past the last key of
                 // the conversation can be read (they are masked like any key a row does not see), and the
                 // range needs no arithmetic.  (A clamp to the keys that exist would also be selected as a
                 // vector instruction, which makes the descriptor a per-lane value issued in a retry loop.)
-                const unsigned bytes = live && krow < S ? page_copy_bytes : 0u;
+                const unsigned bytes = live && c * NLD + j < n_copies ? page_copy_bytes : 0u;
                 const __amdgpu_buffer_rsrc_t rsrc =
                     __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), 0, (int)bytes, 0x00020000);
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rsrc, (__attribute__((address_space(3))) void *)(dst + (wave * NLD + j) * 1024), 16,
+                    rsrc, (__attribute__((address_space(3))) void *)(dst + dst0 + j * 1024), 16,
                     (int)k_lane_off(j, (unsigned)(lane / PPR) * k_row_bytes), 0, 0, 0);
             }
             return;
