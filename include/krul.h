@@ -406,7 +406,7 @@ int krul_calibration_block(int32_t row_blocks, int32_t parts, int32_t iters, flo
 /*
  * Measurement aid, host-only: which kernel form krul_pair_similarity takes for this shape on dense keys: 0 the
  * kernel for float32 inputs and heads above 128 (or, if it is asked for, the portable vector-ALU kernel); 1 to 7 the matrix-core kernel's tile shapes (1 wide 128 rows x 256 keys, 2 mid
- * 64 x 512, 4 slim with a deep ring 32 x 512, 5 / 6 / 7 the short forms of slim / mid / wide); 8 the
+ * 64 x 512, 4 slim with a deep ring 32 x 512, 5 / 6 / 7 the short forms of slim / mid / wide, 10 wide with a deep ring 128 x 512); 8 the
  * many-query kernel (256 x 256).  Negative: a krul_status_t.  n_workgroups, n_key_splits: may be NULL.  (A grid of
  * more workgroups than row tiles x key splits x units cuts the chain of layers into chunks that run side by side.)
  */

@@ -56,6 +56,7 @@ struct MfmaForm {
 // 131072 keys, 16 tokens over 32768.
 constexpr MfmaForm kWideForm = {kMfmaWide, 4, 2, 1, 256, 1, {2.55f, 2.75f, 3.2f}, {3.8f, 4.4f, 4.8f}, 1.f, {6.f, 4.f, 2.3f}, {3.1f, 3.4f}, {4.6f, 5.6f}};
 constexpr MfmaForm kWideShortForm = {kMfmaWideShort, 4, 2, 1, 128, 1, {1.65f, 1.9f, 2.05f}, {3.5f, 3.8f, 4.4f}, 1.f, {2.3f, 2.3f, 2.3f}, {1.85f, 2.2f}, {4.6f, 5.6f}};
+constexpr MfmaForm kWideDeepForm = {kMfmaWideDeep, 4, 2, 1, 512, 1, {}, {}, 1.f, {}, {}, {}};   // (taken by rule, see choose_mfma)
 constexpr MfmaForm kMidForm = {kMfmaMid, 2, 4, 1, 512, 1, {2.55f, 3.f, 3.4f}, {5.4f, 5.5f, 5.8f}, 1.f, {6.f, 4.f, 2.3f}, {3.2f, 3.7f}, {4.6f, 5.6f}};
 constexpr MfmaForm kMidShortForm = {kMfmaMidShort, 2, 2, 1, 128, 2, {1.22f, 1.5f, 1.93f}, {4.5f, 4.6f, 4.9f}, 1.15f, {2.3f, 2.3f, 2.3f}, {1.55f, 2.2f}, {4.1f, 4.9f}};
 constexpr MfmaForm kSlimDeepForm = {kMfmaSlimDeep, 1, 4, 1, 512, 1, {2.f, 3.6f, 4.f}, {5.7f, 5.9f, 6.1f}, 1.f, {6.f, 6.f, 6.f}, {3.0f, 5.87f}, {5.6f, 5.75f}};
@@ -338,7 +339,14 @@ MfmaChoice choose_long(const krul_shape_t *s, bool want_ir, bool plain_keys, con
 // with many query rows, which should bring a workspace.)
 MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static)
 {
-    const MfmaChoice c = choose_long(s, want_ir, plain_keys, choose_short(s, want_ir, plain_keys, false));
+    MfmaChoice c = choose_long(s, want_ir, plain_keys, choose_short(s, want_ir, plain_keys, false));
+    // Heads up to 64, wide tiles, an even number of them in a split: half as many tiles of twice the keys.  What a layer step
+    // costs beside its blocks -- merging, waiting -- is a third of it there (2 x 128 tokens over 16384 keys of 24 layers, 16/4
+    // heads, 467 us in tiles of 256 keys, 426 so; 256 over 16384 with strides 470 and 448).  With two of 256 it depends: 64 over
+    // 16384 124 and 115, but 166 over 4718 with the causal mask 134 and 141, 33 over 2382 of few layers 26 and 27.  The layer
+    // test has no registers for it.
+    if (c.form == &kWideForm && s->head_dim <= 64 && !want_ir && c.tiles_per_split % 2 == 0 && c.tiles_per_split >= 4)
+        c = MfmaChoice{&kWideDeepForm, c.n_split, c.tiles_per_split / 2, 1};
     if (!in_static) return c;
     const auto fits = [&](const MfmaChoice &m) { return record_bytes(s, *m.form, m.n_split) <= static_limit(s); };
     const MfmaChoice o = choose_short(s, want_ir, plain_keys, true);

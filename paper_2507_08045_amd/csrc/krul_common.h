@@ -31,7 +31,6 @@ constexpr float kMInit = -1.0e30f;
 
 enum Variant : int {
     kGeneric = 0,   // portable VALU kernel: one wave per (row, key split)
-    kF32 = 9,       // float32 inputs and heads above 128: 32 or 64 rows x 128 keys per workgroup tile (4 waves): krul_f32.hip
     kMfmaWide = 1,  // bf16 MFMA, 128 rows x 256 keys per workgroup tile (4x2 waves)
     kMfmaMid = 2,   // bf16 MFMA,  64 rows x 512 keys per workgroup tile (2x4 waves)
     kMfmaSlimDeep = 4,   // bf16 MFMA,  32 rows x 512 keys (1x4 waves, three chunks of keys in flight)
@@ -39,6 +38,8 @@ enum Variant : int {
     kMfmaMidShort = 6,   // bf16 MFMA,  64 rows x 128 keys (2x2 waves)
     kMfmaWideShort = 7,  // bf16 MFMA, 128 rows x 128 keys (4x2 waves)
     kMfmaBig = 8,        // bf16 MFMA, 256 rows x 256 keys (4x2 waves, two 32-row blocks per wave): krul_mfma_big.hip
+    kF32 = 9,       // float32 inputs and heads above 128: 32 or 64 rows x 128 keys per workgroup tile (4 waves): krul_f32.hip
+    kMfmaWideDeep = 10,  // bf16 MFMA, 128 rows x 512 keys (4x2 waves), heads up to 64, without the layer test
 };
 
 // How the state records of one launch are laid out; used by the producer kernels

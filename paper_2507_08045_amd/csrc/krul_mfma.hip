@@ -24,6 +24,7 @@ hipError_t launch_sim_mfma(const SimParams &p, int n_workgroups, hipStream_t st)
         return launch_sim_mfma_big(p, n_workgroups, st);
     case kMfmaWide:
     case kMfmaWideShort:
+    case kMfmaWideDeep:
         return p.d > 96 ? launch_sim_mfma_wide128(p, n_workgroups, st) : p.d > 64 ? launch_sim_mfma_wide96(p, n_workgroups, st)
                                                                           : launch_sim_mfma_wide64(p, n_workgroups, st);
     case kMfmaMid:

@@ -75,7 +75,7 @@ struct Cfg {
     static_assert(NW == 4 || NW == 8, "four or eight waves per workgroup");
     static_assert(CH * PPR % THREADS == 0, "chunk must split evenly over threads");
     static_assert(D == 64 || D == 128, "head_dim 64 or 128");
-    static_assert(NC == 2 || NC == 4, "two or four chunks per tile");
+    static_assert(NC == 2 || NC == 4 || NC == 8, "two, four or eight chunks per tile");
     static_assert(NC == 2 || WK * QPW == NQI, "every wave must issue the same number of copies");
 };
 
@@ -135,6 +135,10 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
     __shared__ __attribute__((aligned(C::SLOT_ALIGN))) unsigned char ring1[C::SLOT_BYTES];
     __shared__ __attribute__((aligned(C::SLOT_ALIGN))) unsigned char ring2[NC > 2 ? C::SLOT_BYTES : 16];
     __shared__ __attribute__((aligned(C::SLOT_ALIGN))) unsigned char ring3[NC > 2 ? C::SLOT_BYTES : 16];
+    __shared__ __attribute__((aligned(NC > 4 ? C::SLOT_ALIGN : 16))) unsigned char ring4[NC > 4 ? C::SLOT_BYTES : 16];
+    __shared__ __attribute__((aligned(NC > 4 ? C::SLOT_ALIGN : 16))) unsigned char ring5[NC > 4 ? C::SLOT_BYTES : 16];
+    __shared__ __attribute__((aligned(NC > 4 ? C::SLOT_ALIGN : 16))) unsigned char ring6[NC > 4 ? C::SLOT_BYTES : 16];
+    __shared__ __attribute__((aligned(NC > 4 ? C::SLOT_ALIGN : 16))) unsigned char ring7[NC > 4 ? C::SLOT_BYTES : 16];
     __shared__ __attribute__((aligned(1024))) unsigned char qlds[C::WR * C::QBYTES];
     __shared__ float4 part[C::NW][64];   // every lane's record of the last step (m, Z, N2, C)
     __shared__ float part_ir[IR ? C::NW : 1][64];   // ... and its Zir
@@ -143,7 +147,11 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
         case 0: return ring0;
         case 1: return ring1;
         case 2: return ring2;
-        default: return ring3;
+        case 3: return ring3;
+        case 4: return ring4;
+        case 5: return ring5;
+        case 6: return ring6;
+        default: return ring7;
         }
     };
 
@@ -698,9 +706,10 @@ template <class C, int KA, bool F16>
 hipError_t launch_mode(const SimParams &p, int n_workgroups, hipStream_t st)
 {
     const dim3 grid(n_workgroups), block(C::THREADS);
-    if (p.want_ir)
-        hipLaunchKernelGGL((sim_mfma_kernel<C, 2, KA, F16>), grid, block, 0, st, p);
-    else if (p.want_dist)
+    if (p.want_ir) {
+        if constexpr (C::NBLK > 4) return hipErrorInvalidValue;   // (no registers for it: the plan takes another shape)
+        else hipLaunchKernelGGL((sim_mfma_kernel<C, 2, KA, F16>), grid, block, 0, st, p);
+    } else if (p.want_dist)
         hipLaunchKernelGGL((sim_mfma_kernel<C, 1, KA, F16>), grid, block, 0, st, p);
     else
         hipLaunchKernelGGL((sim_mfma_kernel<C, 0, KA, F16>), grid, block, 0, st, p);

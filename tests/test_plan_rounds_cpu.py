@@ -20,3 +20,9 @@ def test_rounds_are_full(shape):
     assert rounds / math.ceil(rounds) >= 0.85, p
     assert kr.workspace_bytes(sh) <= (520 << 20)
 
+
+def test_forms_are_told_apart():
+    """Every long 16-bit call takes a matrix-core form, whatever its number: 0 is the kernel of float32 inputs and heads above 128."""
+    for d in (8, 40, 64, 72, 96, 128):
+        for S, Tq in ((16384, 64), (4096, 512), (65536, 1), (906, 1179)):
+            assert kr.plan(kr.KrulShape(1, 24, 16, 4, d, S, Tq, kr.KRUL_BF16, 0.0, 0))["form"] != 0, (d, S, Tq)
