@@ -69,9 +69,8 @@ struct Div {
     unsigned d, m, s;
     static Div by(unsigned d)
     {
-        unsigned s = 0;
-        while ((1ull << s) < d) ++s;
-        return {d, (unsigned)((((1ull << s) - d) << 32) / d) + 1u, s};
+        const unsigned s = d > 1 ? 32 - (unsigned)__builtin_clz(d - 1) : 0;
+        return {d, d == 1u << s ? 1u : (unsigned)((((1ull << s) - d) << 32) / d) + 1u, s};
     }
     __device__ unsigned operator()(unsigned n) const { return (__umulhi(n, m) + n) >> s; }
 };
