@@ -21,46 +21,39 @@ namespace {
 
 constexpr int kThreads = 256;
 
-__device__ inline float block_sum(float v, float *red)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    const int w = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[w] = v;
-    __syncthreads();
-    float s = 0.f;
-    for (int i = 0; i < kThreads / 64; ++i) s += red[i];
-    return s;
-}
-
 // Running merge of partial records of one row for a layer pair (a = layer l, b = l+1):
-// exponents Ma, Mb; Z and N2 of both layers and the cross term C, all relative to them.  (exp2f, not the bare instruction: a
+// exponents Ma, Mb; Z and N2 of both layers and the cross term C, all relative to them; with the layer test (IR) also the sums
+// Ia, Ib over the initial and recent keys.  (exp2f, not the bare instruction: a
 // sum all of whose terms lie 2^126 to 2^149 below the row's largest exponential is subnormal, not zero.)
 struct RowAcc {
-    float Ma, Za, Na, Mb, Zb, Nb, C;
+    float Ma, Za, Na, Mb, Zb, Nb, C, Ia, Ib;
 };
 
-__device__ inline void merge_into(RowAcc &r, float ma, float za, float na, float mb, float zb, float nb, float c)
+template <bool IR>
+__device__ inline void merge_into(RowAcc &r, const RowAcc &o)
 {
-    const float Ma = fmaxf(r.Ma, ma), Mb = fmaxf(r.Mb, mb);
-    const float fa0 = exp2f(r.Ma - Ma), fa1 = exp2f(ma - Ma);
-    const float fb0 = exp2f(r.Mb - Mb), fb1 = exp2f(mb - Mb);
-    r.Za = r.Za * fa0 + za * fa1;
-    r.Na = r.Na * (fa0 * fa0) + na * (fa1 * fa1);
-    r.Zb = r.Zb * fb0 + zb * fb1;
-    r.Nb = r.Nb * (fb0 * fb0) + nb * (fb1 * fb1);
-    r.C = r.C * (fa0 * fb0) + c * (fa1 * fb1);
+    const float Ma = fmaxf(r.Ma, o.Ma), Mb = fmaxf(r.Mb, o.Mb);
+    const float fa0 = exp2f(r.Ma - Ma), fa1 = exp2f(o.Ma - Ma);
+    const float fb0 = exp2f(r.Mb - Mb), fb1 = exp2f(o.Mb - Mb);
+    r.Za = r.Za * fa0 + o.Za * fa1;
+    r.Na = r.Na * (fa0 * fa0) + o.Na * (fa1 * fa1);
+    r.Zb = r.Zb * fb0 + o.Zb * fb1;
+    r.Nb = r.Nb * (fb0 * fb0) + o.Nb * (fb1 * fb1);
+    r.C = r.C * (fa0 * fb0) + o.C * (fa1 * fb1);
+    if (IR) {
+        r.Ia = r.Ia * fa0 + o.Ia * fa1;
+        r.Ib = r.Ib * fb0 + o.Ib * fb1;
+    }
     r.Ma = Ma;
     r.Mb = Mb;
 }
 
-template <int OFF>
+template <int OFF, bool IR>
 __device__ inline void join(RowAcc &r)
 {
-    const float ma = across<OFF>(r.Ma), za = across<OFF>(r.Za), na = across<OFF>(r.Na), mb = across<OFF>(r.Mb);
-    const float zb = across<OFF>(r.Zb), nb = across<OFF>(r.Nb), c = across<OFF>(r.C);
-    merge_into(r, ma, za, na, mb, zb, nb, c);
+    const RowAcc o = {across<OFF>(r.Ma), across<OFF>(r.Za), across<OFF>(r.Na), across<OFF>(r.Mb), across<OFF>(r.Zb), across<OFF>(r.Nb),
+                      across<OFF>(r.C), IR ? across<OFF>(r.Ia) : 0.f, IR ? across<OFF>(r.Ib) : 0.f};
+    merge_into<IR>(r, o);
 }
 
 // n / d for n < 2^31 by a multiplication: m = floor(2^32 (2^s - d) / d) + 1 with s = ceil(log2 d) (Granlund and Montgomery, "Division by
@@ -108,8 +101,7 @@ struct HeadsArgs {
     int groups;          // ceil(heads per kv head / H)
     Div by_groups, by_hkv, by_pairs, by_tile;   // divisions by groups, Hkv, L - 1, the rows of a row tile
     int want_dist, accumulate;
-    int n_items;   // (conversation, pair, kv head, group of heads); the (conversation, layer, head) triples of the layer test follow
-    int n_all;
+    int n_items;   // (conversation, pair, kv head, group of heads)
     int first;     // of this launch
     float *head_cos, *head_dist, *head_ir;
 };
@@ -121,26 +113,6 @@ struct HeadsArgs {
 // PER_WAVE (few rows): a wave takes H heads of a kv head by itself -- their rows lie one after the other --, lanes
 // g*(64/G) + h*TP + t.  A decode step has one row per head: a wave per head would read 64 bytes for 16 and leave three lanes in
 // four idle (8 x 992 heads of 8 partials: 10.0 us, 5.2 so).
-
-// The layer test's rows of head h: calls f(t, row, g, RW) for the lanes' rows; RW rows share a wave's 64 lanes.
-template <bool PER_WAVE, class F>
-__device__ inline void for_rows(const HeadsArgs &p, int h, F f)
-{
-    const int lane = threadIdx.x & 63, wave = PER_WAVE ? 0 : threadIdx.x >> 6;
-    const int RW = 64 / p.G;   // rows per wave
-    for (int t0 = 0; t0 < p.Tq; t0 += (PER_WAVE ? 1 : kThreads / 64) * RW) {
-        const int t = t0 + wave * RW + lane % RW;
-        f(t, (h % (p.Hq / p.Hkv)) * p.Tq + t, lane / RW, RW);
-    }
-}
-template <bool PER_WAVE>
-__device__ inline float sum_rows(float v, float *red)
-{
-    if constexpr (!PER_WAVE) return block_sum(v, red);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // Sum over n lanes (a power of two), the same in each of them.
 __device__ inline float sum_over(float v, int n)
@@ -155,60 +127,17 @@ __device__ inline float sum_over(float v, int n)
 }
 
 // IR: also the Initial-Recent layer test (Sec. 4.2; Alg. 1 first loop): per (conversation, layer, head) the
-// mean over query rows of Zir / Z -- the attention mass on T_initial and T_recent -- from the
-// partial records of each row, merged onto a common exponent like the similarity sums.
+// mean over query rows of Zir / Z -- the attention mass on T_initial and T_recent -- from the same records: a pair's first
+// layer's, the last pair's second layer's too.  (As items of their own, which read every record once more: 17.9 us for 2 x
+// 32 layers of 32 heads of 77 rows with the pairs' scores, 15.4 so.)
 template <bool PER_WAVE, bool IR>
 __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
 {
-    __shared__ float red[IR && !PER_WAVE ? kThreads / 64 : 1];
-    __shared__ float2 red2[PER_WAVE ? 1 : kThreads / 64];
+    __shared__ float4 red[PER_WAVE ? 1 : kThreads / 64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int item = p.first + (PER_WAVE ? blockIdx.x * (kThreads / 64) + wave : blockIdx.x);
-    if (PER_WAVE && item >= p.n_all) return;   // (a whole wave: no barrier follows in this form)
+    const int item = p.first + (PER_WAVE ? blockIdx.x * (kThreads / 64) + wave : blockIdx.x);
+    if (PER_WAVE && item >= p.n_items) return;   // (a whole wave: no barrier follows in this form)
     const int P = p.lay.partials;
-
-    if (IR && item >= p.n_items) {
-        item -= p.n_items;
-        const int h = item % p.Hq, l = item / p.Hq % p.L, u = item / (p.Hq * p.L) * p.Hkv + h / (p.Hq / p.Hkv);
-        float mass = 0.f;
-        for_rows<PER_WAVE>(p, h, [&](int t, int r, int g, int RW) {
-            float M = kMInit, Z = 0.f, I = 0.f;
-            if (t < p.Tq) {
-                const RowRecords q = row_records(p.lay, p.by_tile, u, r, l);
-                for (int p0 = g; p0 < P; p0 += kBatch * p.G) {
-                    float am[kBatch], az[kBatch], ai[kBatch];
-#pragma unroll
-                    for (int i = 0; i < kBatch; ++i) {
-                        const size_t idx = q.at + (size_t)min(p0 + i * p.G, P - 1) * q.step;
-                        am[i] = p.state[idx].x;
-                        az[i] = p.state[idx].y;
-                        ai[i] = p.state_ir[idx];
-                    }
-#pragma unroll
-                    for (int i = 0; i < kBatch; ++i) {
-                        if (p0 + i * p.G >= P) continue;
-                        const float Mn = fmaxf(M, am[i]);
-                        const float f0 = exp2f(M - Mn), f1 = exp2f(am[i] - Mn);
-                        Z = Z * f0 + az[i] * f1;
-                        I = I * f0 + ai[i] * f1;
-                        M = Mn;
-                    }
-                }
-            }
-            for (int off = 32; off >= RW; off >>= 1) {
-                const float m2 = __shfl_xor(M, off, 64), z2 = __shfl_xor(Z, off, 64), i2 = __shfl_xor(I, off, 64);
-                const float Mn = fmaxf(M, m2);
-                const float f0 = exp2f(M - Mn), f1 = exp2f(m2 - Mn);
-                Z = Z * f0 + z2 * f1;
-                I = I * f0 + i2 * f1;
-                M = Mn;
-            }
-            if (t < p.Tq && g == 0) mass += I / Z;
-        });
-        mass = sum_rows<PER_WAVE>(mass, red);
-        if ((PER_WAVE ? lane : threadIdx.x) == 0) p.head_ir[item] = mass / (float)p.Tq;
-        return;
-    }
 
     // (conversation b, pair l, kv head, group of heads): each is the remainder of a division
     const int t1 = p.groups > 1 ? (int)p.by_groups(item) : item, group = item - t1 * p.groups;
@@ -224,31 +153,36 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
         old_cos = p.head_cos[out];
         if (p.want_dist) old_dist = p.head_dist[out];
     }
-    float cs = 0.f, ds = 0.f;
+    const bool last = IR && l == p.L - 2;
+    float cs = 0.f, ds = 0.f, mass_a = 0.f, mass_b = 0.f;
     for (int t = t_first; t - t_first < p.Tq; t += PER_WAVE ? 64 : kThreads / 64 * RW) {   // (PER_WAVE: once)
-        RowAcc acc = {kMInit, 0.f, 0.f, kMInit, 0.f, 0.f, 0.f};
+        RowAcc acc = {kMInit, 0.f, 0.f, kMInit, 0.f, 0.f, 0.f, 0.f, 0.f};
         const bool row = t < p.Tq && head < heads;
         if (row) {
             const RowRecords q = row_records(p.lay, p.by_tile, u, head * p.Tq + t, l);
             for (int p0 = g; p0 < P; p0 += kBatch * p.G) {
                 float4 a[kBatch], c[kBatch];
+                float ia[kBatch], ib[kBatch];
 #pragma unroll
                 for (int i = 0; i < kBatch; ++i) {
-                    const float4 *rec = p.state + q.at + (size_t)min(p0 + i * p.G, P - 1) * q.step;
-                    a[i] = rec[0];
-                    c[i] = rec[q.next_layer];
+                    const size_t at = q.at + (size_t)min(p0 + i * p.G, P - 1) * q.step;
+                    a[i] = p.state[at];
+                    c[i] = p.state[at + q.next_layer];
+                    ia[i] = IR ? p.state_ir[at] : 0.f;
+                    ib[i] = last ? p.state_ir[at + q.next_layer] : 0.f;
                 }
 #pragma unroll
                 for (int i = 0; i < kBatch; ++i)
-                    if (p0 + i * p.G < P) merge_into(acc, a[i].x, a[i].y, a[i].z, c[i].x, c[i].y, c[i].z, c[i].w);
+                    if (p0 + i * p.G < P)
+                        merge_into<IR>(acc, RowAcc{a[i].x, a[i].y, a[i].z, c[i].x, c[i].y, c[i].z, c[i].w, ia[i], ib[i]});
             }
         }
-        if (RW <= 32) join<32>(acc);
-        if (RW <= 16) join<16>(acc);
-        if (RW <= 8) join<8>(acc);
-        if (RW <= 4) join<4>(acc);
-        if (RW <= 2) join<2>(acc);
-        if (RW <= 1) join<1>(acc);
+        if (RW <= 32) join<32, IR>(acc);
+        if (RW <= 16) join<16, IR>(acc);
+        if (RW <= 8) join<8, IR>(acc);
+        if (RW <= 4) join<4, IR>(acc);
+        if (RW <= 2) join<2, IR>(acc);
+        if (RW <= 1) join<1, IR>(acc);
         if (row && g == 0) {
             cs += acc.C * rsqrtf(acc.Na * acc.Nb);
             if (p.want_dist) {   // (Z is only accumulated when the distance is asked for)
@@ -256,17 +190,26 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
                 const float d2 = acc.Na * ia * ia + acc.Nb * ib * ib - 2.f * acc.C * ia * ib;
                 ds += sqrtf(fmaxf(d2, 0.f));
             }
+            if (IR) mass_a += acc.Ia / acc.Za;
+            if (last) mass_b += acc.Ib / acc.Zb;
         }
     }
     cs = sum_over(cs, PER_WAVE ? p.TP : RW);
     ds = sum_over(ds, PER_WAVE ? p.TP : RW);
+    if (IR) {
+        mass_a = sum_over(mass_a, PER_WAVE ? p.TP : RW);
+        mass_b = sum_over(mass_b, PER_WAVE ? p.TP : RW);
+    }
     if constexpr (!PER_WAVE) {
-        if (lane == 0) red2[wave] = make_float2(cs, ds);
+        if (lane == 0) red[wave] = make_float4(cs, ds, mass_a, mass_b);
         __syncthreads();
-        cs = ds = 0.f;
+        cs = ds = mass_a = mass_b = 0.f;
         for (int i = 0; i < kThreads / 64; ++i) {
-            cs += red2[i].x;
-            ds += red2[i].y;
+            const float4 v = red[i];
+            cs += v.x;
+            ds += v.y;
+            if (IR) mass_a += v.z;
+            if (IR) mass_b += v.w;
         }
     }
     if (writes) {
@@ -276,6 +219,11 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
         } else {
             p.head_cos[out] = cs / (float)p.Tq;
             p.head_dist[out] = ds / (float)p.Tq;
+        }
+        if (IR) {   // [B][L][Hq]: pair (b, l) is layer (b, l) after b layers more
+            float *mass = p.head_ir + out + (size_t)b * p.Hq;
+            mass[0] = mass_a / (float)p.Tq;
+            if (last) mass[p.Hq] = mass_b / (float)p.Tq;
         }
     }
 }
@@ -334,9 +282,9 @@ template <bool PER_WAVE>
 void launch_heads(HeadsArgs p, bool ir, hipStream_t st)
 {
     constexpr int per_block = PER_WAVE ? kThreads / 64 : 1, step = kMostBlocks * per_block;
-    for (long long first = 0; first < p.n_all; first += step) {
+    for (long long first = 0; first < p.n_items; first += step) {
         p.first = (int)first;
-        const long long here = p.n_all - first < step ? p.n_all - first : step;
+        const long long here = p.n_items - first < step ? p.n_items - first : step;
         const dim3 grid((unsigned)((here + per_block - 1) / per_block));
         if (ir) hipLaunchKernelGGL((finalize_heads_kernel<PER_WAVE, true>), grid, dim3(kThreads), 0, st, p);
         else hipLaunchKernelGGL((finalize_heads_kernel<PER_WAVE, false>), grid, dim3(kThreads), 0, st, p);
@@ -372,8 +320,18 @@ hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, i
         while (p.H < heads && 2 * p.H * p.TP <= 64 && 64 / (2 * p.H * p.TP) * kBatch >= lay.partials) p.H <<= 1;
         while (p.G * 2 * p.H * p.TP <= 64 && p.G < lay.partials) p.G <<= 1;
     } else {
-        // lanes per row: enough to keep a workgroup's 256 threads busy, at most one per partial
-        while (p.G < 64 && p.G * Tq < kThreads && p.G < lay.partials) p.G <<= 1;
+        // lanes per row: runs of rows, each of batches of loads (three times a join's time) and of joins.  (As many lanes as fill the
+        // workgroup once: 77 rows, the layers above, 15.4 us in two runs of four lanes a row, 10.3 in one of two; 100 rows over 4000 keys
+        // of 24 layers 92.7 and 90.3 us a call.)
+        int best = 0;
+        for (int lg = 0; 1 << lg <= 64 && (lg == 0 || 1 << (lg - 1) < lay.partials); ++lg) {
+            const int runs = ((Tq << lg) + kThreads - 1) / kThreads, batches = (lay.partials + (kBatch << lg) - 1) >> lg >> 2;
+            const int cost = runs * (3 * batches + lg);
+            if (best == 0 || cost < best) {
+                best = cost;
+                p.G = 1 << lg;
+            }
+        }
     }
     p.groups = (heads + p.H - 1) / p.H;
     p.by_groups = Div::by((unsigned)p.groups);
@@ -381,7 +339,6 @@ hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, i
     p.by_pairs = Div::by((unsigned)L - 1);
     p.by_tile = Div::by(lay.variant == kGeneric ? 1u : (unsigned)(lay.wr * lay.rb * 32));
     p.n_items = B * (L - 1) * Hkv * p.groups;
-    p.n_all = p.n_items + (ir ? B * L * Hq : 0);
     if (per_wave) launch_heads<true>(p, ir != nullptr, st);
     else launch_heads<false>(p, ir != nullptr, st);
     const hipError_t e = hipGetLastError();
