@@ -182,9 +182,12 @@ MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bo
             if (c.tiles_per_split > 1 && f.kt <= 128) t_steps *= 1.2;
             if (chunks > 1) t_steps *= 1.25;   // (600 tokens over 700 keys: 247 us in two chunks, 241 in one)
         }
-        // (idle places draw no keys: the stream is up to 15 % slower)
+        // (idle places draw no keys: the stream is up to 15 % slower.  For up to 32 rows, which do little else than wait for it, also
+        // those of a last round -- one token over 6000 keys in three chunks of layers, 576 workgroups for 512 places, 104 us, in two
+        // 85, 3 of 5535 keys and 80 layers 629 and 532; not for more, which hide it: 57 tokens over 276 keys 62 us, 70 so.)
+        const double taken = Rk <= 32 ? n_wg / slots / ceil(n_wg / slots) : fmin(1.0, n_wg / slots);
         const double bytes = (double)(B * d * 2) * (double)(Hkv * S + s->n_q_heads * Tq) * layers_read;
-        const double t_stream = bytes / (f.short_stream[d > 64] * 1e6 * fmin(1.0, 0.85 + 0.15 * n_wg / slots)) + kWorkgroupStart;
+        const double t_stream = bytes / (f.short_stream[d > 64] * 1e6 * (0.85 + 0.15 * taken)) + kWorkgroupStart;
         // (slim tiles have next to nothing to do but wait for keys; the others' steps hide most of the stream)
         const double t = fmax(t_steps, t_stream) + record_time(record_bytes, chunk) + (Rk > 32 ? 0.1 * fmin(t_steps, t_stream) : 0.0);
         // The fastest within the limit on records; where none is, the one with the fewest.

@@ -21,6 +21,14 @@ def test_rounds_are_full(shape):
     assert kr.workspace_bytes(sh) <= (520 << 20)
 
 
+@pytest.mark.parametrize("shape", [(1, 32, 32, 8, 128, 6000, 1), (6, 32, 32, 8, 128, 916, 1), (3, 80, 64, 8, 128, 5535, 1), (1, 32, 32, 8, 128, 8253, 1),
+                                   (1, 80, 64, 8, 128, 1494, 1)], ids=lambda s: f"{s[0]}-over-{s[5]}")
+def test_no_nearly_empty_last_round_of_a_decode_step(shape):
+    p = kr.plan(kr.KrulShape(*shape, kr.KRUL_BF16, 0.0, kr.KRUL_FLAG_CAUSAL))
+    rounds = p["n_workgroups"] / (512 if p["form"] == 5 else 256)
+    assert rounds / math.ceil(rounds) >= 0.7, p
+
+
 def test_forms_are_told_apart():
     """Every long 16-bit call takes a matrix-core form, whatever its number: 0 is the kernel of float32 inputs and heads above 128."""
     for d in (8, 40, 64, 72, 96, 128):
