@@ -26,7 +26,7 @@ def test_rounds_are_full(shape):
 def test_no_nearly_empty_last_round_of_a_decode_step(shape):
     p = kr.plan(kr.KrulShape(*shape, kr.KRUL_BF16, 0.0, kr.KRUL_FLAG_CAUSAL))
     rounds = p["n_workgroups"] / (512 if p["form"] == 5 else 256)
-    assert rounds / math.ceil(rounds) >= 0.7, p
+    assert rounds <= 1 or rounds / math.ceil(rounds) >= 0.7, p
 
 
 def test_forms_are_told_apart():
