@@ -30,7 +30,7 @@ typedef enum {
     KRUL_OK = 0,
     KRUL_EINVAL = -1,       /* null pointer, non-positive extent, bad head grouping, misalignment */
     KRUL_EDTYPE = -2,       /* dtype is not a krul_dtype_t */
-    KRUL_EWORKSPACE = -3,   /* workspace missing, misaligned or shorter than the query says */
+    KRUL_EWORKSPACE = -3,   /* workspace missing, misaligned or too short (see krul_pair_similarity_workspace) */
     KRUL_ELAUNCH = -4,      /* the HIP runtime refused a launch */
     KRUL_EUNSUPPORTED = -5, /* valid request with no kernel (head_dim, n_layers limits) */
     KRUL_ESCRATCH = -6      /* krul_pair_similarity_static: the shape needs more than KRUL_STATIC_SCRATCH_BYTES */
@@ -75,6 +75,11 @@ typedef struct {
  * Bytes of device workspace krul_pair_similarity needs for this
  * shape (a multiple of 256).  Returns 0 if the shape is invalid or unsupported.
  * Host-only: touches no GPU.
+ *
+ * The size does not always grow with n_hist: it follows how the keys are split.  A caller that keeps one workspace
+ * while a history grows takes the largest of the sizes along the way.  A call with fewer bytes than this is
+ * also served where they hold the library's second, slower plan for the shape, or another plan for where the keys are
+ * (the results then agree to rounding); otherwise it is refused with KRUL_EWORKSPACE.
  */
 size_t krul_pair_similarity_workspace(const krul_shape_t *shape);
 

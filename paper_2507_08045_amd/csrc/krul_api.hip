@@ -121,7 +121,9 @@ long long record_bytes(const krul_shape_t *s, const MfmaForm &f, long long n_spl
 // lose by it (10 % on average, up to 1.8 times the time: 1042 tokens over 19743 keys of 32/8 heads 14.9 ms in 272
 // workgroups, one round and a sixteenth, 9.4 in 1768), and choose_long has the last word where its own choice is 7 % faster by
 // its estimate.
-MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static)
+//
+// fallback: the plan for a workspace that does not hold the fastest one, see make_plan.
+MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static, bool fallback = false)
 {
     const long long B = s->batch, L = s->n_layers, Hkv = s->n_kv_heads, S = s->n_hist, Tq = s->n_query;
     const long long Rk = s->n_q_heads / Hkv * Tq, d = s->head_dim;
@@ -185,7 +187,7 @@ MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bo
         // (idle places draw no keys: the stream is up to 15 % slower.  For up to 32 rows, which do little else than wait for it, also
         // those of a last round -- one token over 6000 keys in three chunks of layers, 576 workgroups for 512 places, 104 us, in two
         // 85, 3 of 5535 keys and 80 layers 629 and 532; not for more, which hide it: 57 tokens over 276 keys 62 us, 70 so.)
-        const double taken = Rk <= 32 ? n_wg / slots / ceil(n_wg / slots) : fmin(1.0, n_wg / slots);
+        const double taken = Rk <= 32 && !fallback ? n_wg / slots / ceil(n_wg / slots) : fmin(1.0, n_wg / slots);
         const double bytes = (double)(B * d * 2) * (double)(Hkv * S + s->n_q_heads * Tq) * layers_read;
         const double t_stream = bytes / (f.short_stream[d > 64] * 1e6 * (0.85 + 0.15 * taken)) + kWorkgroupStart;
         // (slim tiles have next to nothing to do but wait for keys; the others' steps hide most of the stream)
@@ -340,8 +342,9 @@ MfmaChoice choose_long(const krul_shape_t *s, bool want_ir, bool plain_keys, con
 // in_static: for krul_pair_similarity_static.  Its limit on records is the library's own area: the plan of the call with a
 // workspace where that fits, and otherwise choose_short's within the limit.  (What that does not fit is refused: large calls
 // with many query rows, which should bring a workspace.)
-MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static)
+MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static, bool fallback)
 {
+    if (fallback) return choose_short(s, want_ir, plain_keys, false, true);
     MfmaChoice c = choose_long(s, want_ir, plain_keys, choose_short(s, want_ir, plain_keys, false));
     // Heads up to 64, wide tiles, an even number of them in a split: half as many tiles of twice the keys.  What a layer step
     // costs beside its blocks -- merging, waiting -- is a third of it there (2 x 128 tokens over 16384 keys of 24 layers, 16/4
@@ -358,7 +361,7 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, boo
 
 }  // namespace
 
-int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bool in_static)
+int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bool in_static, bool fallback)
 {
     const int rc = check_shape(s);
     if (rc != KRUL_OK) return rc;
@@ -379,7 +382,7 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
     bool generic = (s->flags & KRUL_FLAG_GENERIC_KERNEL) != 0;
     long long n_wg = 0, records = 0;
     if (mfma) {
-        const MfmaChoice ch = choose_mfma(s, want_ir, plain_keys, in_static);
+        const MfmaChoice ch = choose_mfma(s, want_ir, plain_keys, in_static, fallback);
         const MfmaForm &f = *ch.form;
         y.variant = f.variant;
         y.wr = f.wr;
@@ -476,6 +479,16 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
     return KRUL_OK;
 }
 
+// Bytes that hold both the plan of a call and its fallback (0: unsupported).
+size_t plan_bytes(const krul_shape_t *s, bool want_ir, bool plain_keys)
+{
+    Plan pl, fallback;
+    if (make_plan(s, &pl, want_ir, plain_keys) != KRUL_OK) return 0;
+    if (pl.lay.variant == kGeneric || pl.lay.variant == kF32) return pl.total_bytes;   // (one plan for all)
+    if (make_plan(s, &fallback, want_ir, plain_keys, false, true) != KRUL_OK) return pl.total_bytes;
+    return pl.total_bytes > fallback.total_bytes ? pl.total_bytes : fallback.total_bytes;
+}
+
 int resolve_keys(const krul_shape_t *s, bool mfma, bool dense_2gib, const void *k, const krul_k_layout_t *kl,
                  const krul_k_pages_t *kp, KeyAddr *out)
 {
@@ -566,8 +579,12 @@ int run_similarity(const krul_shape_t *shape, const void *q, const void *k, floa
     if (((uintptr_t)pair_score | (uintptr_t)head_score | (uintptr_t)pair_dist | (uintptr_t)ir_mass) & 3)
         return KRUL_EINVAL;
     if (ir && (!(gamma >= 0.f) || !isfinite(gamma) || (!ir_mass && !eligible))) return KRUL_EINVAL;
-    if (!workspace || ((uintptr_t)workspace & (kAlign - 1)) || workspace_bytes < pl.total_bytes)
-        return KRUL_EWORKSPACE;
+    if (!workspace || ((uintptr_t)workspace & (kAlign - 1))) return KRUL_EWORKSPACE;
+    if (workspace_bytes < pl.total_bytes) {
+        if (in_static || make_plan(shape, &pl, ir, k != nullptr && !kl && !kp, false, true) != KRUL_OK ||
+            workspace_bytes < pl.total_bytes)
+            return KRUL_EWORKSPACE;
+    }
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     unsigned char *ws = static_cast<unsigned char *>(workspace);
@@ -665,9 +682,8 @@ int krul_pair_similarity_plan(const krul_shape_t *shape, int32_t *n_workgroups, 
 size_t krul_pair_similarity_workspace(const krul_shape_t *shape)
 {
     // enough for the call on dense keys and for the calls on keys read in place (their plans may differ)
-    Plan pl, pl_dense;
-    if (make_plan(shape, &pl) != KRUL_OK || make_plan(shape, &pl_dense, false, true) != KRUL_OK) return 0;
-    return pl.total_bytes > pl_dense.total_bytes ? pl.total_bytes : pl_dense.total_bytes;
+    const size_t in_place = plan_bytes(shape, false, false), dense = plan_bytes(shape, false, true);
+    return in_place == 0 || dense == 0 ? 0 : in_place > dense ? in_place : dense;
 }
 
 int krul_pair_similarity(const krul_shape_t *shape, const void *q, const void *k,
@@ -853,9 +869,7 @@ int krul_pair_scores_from_sums(const float *head_sum, const float *head_dist_sum
 
 size_t krul_pair_similarity_ir_workspace(const krul_shape_t *shape)
 {
-    Plan pl;
-    if (make_plan(shape, &pl, true) != KRUL_OK) return 0;
-    return pl.total_bytes;
+    return plan_bytes(shape, true, false);
 }
 
 int krul_pair_similarity_ir(const krul_shape_t *shape, const void *q, const void *k, float gamma,
