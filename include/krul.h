@@ -325,7 +325,10 @@ int krul_pair_similarity_select(const krul_shape_t *shape, const void *q, const 
  *                   largest batch that fits max_bytes (max_bytes 0: a default budget of 4 GiB; never
  *                   less than the bytes for the smallest batch, up to 256 rows of one kv head), or 0 if the
  *                   shape is not supported.  Any size from the smallest batch's up is accepted by the
- *                   call; more memory means fewer, larger launches.
+ *                   call; more memory means fewer, larger launches.  (max_bytes too small for any batch, e.g. 1,
+ *                   asks for the smallest batch's.  For some shapes of few rows, or of up to 16 heads in all
+ *                   conversations, somewhat less is accepted too; the results then agree to rounding.  The sizes do
+ *                   not always grow with n_hist.)
  * Limits: n_layers <= 128.  bf16 or f16 with head_dim up to 128 runs on the matrix cores; other inputs take a
  * portable, slow kernel.  Exponentials are rounded to fp16 (2^-11 relative) before the products.
  * Results are deterministic.  Errors as for krul_pair_similarity.

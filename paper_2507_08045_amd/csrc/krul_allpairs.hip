@@ -1354,7 +1354,7 @@ __global__ __launch_bounds__(kSelThreads) void select_all_many_kernel(
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct APPlan {
-    int NW, NRB, NRG, NKB, nsplit, kps, tpw, total_rg, nrg_batch, ksp, kb_per;
+    int NW, NRB, NRG, NKB, nsplit, kps, tpw, total_rg, nrg_batch, ksp, kb_per, classes;
     size_t head_cos_off, head_dist_off, dump_off, rowm_off, rowz_off, rowzt_off, gpart_off, row_cos_off, row_dist_off, e_off, total_bytes;
     bool mfma;
     bool direct;   // ap_direct_kernel: the exponentials stay in LDS
@@ -1362,11 +1362,13 @@ struct APPlan {
 
 constexpr int kGramTargetWorkgroups = 512;
 
-// Sizes for a batch of nrg row groups (NW, NRG, NKB, nsplit must be set).
-void ap_layout(const krul_shape_t *s, int nrg, APPlan *pl)
+// Sizes for a batch of nrg row groups (NW, NRG, NKB, nsplit must be set).  fallback: eight classes, and the fewest key splits
+// that give every CU a workgroup.
+void ap_layout(const krul_shape_t *s, int nrg, APPlan *pl, bool fallback)
 {
     const size_t L = s->n_layers, LL = L * L, NB = (L + 31) / 32, NACC = NB * (NB + 1) / 2;
-    const size_t heads = (size_t)s->batch * s->n_q_heads * class_count((long long)s->batch * s->n_q_heads) * LL * sizeof(float);
+    pl->classes = fallback ? kClasses : class_count((long long)s->batch * s->n_q_heads);
+    const size_t heads = (size_t)s->batch * s->n_q_heads * pl->classes * LL * sizeof(float);
     const size_t rows = (size_t)nrg * pl->NW * 32;
     // the Gram kernel splits the keys until it has enough workgroups, but keeps at least 16 key blocks
     // per workgroup so that the partial matrices stay small beside the weights
@@ -1383,7 +1385,8 @@ void ap_layout(const krul_shape_t *s, int nrg, APPlan *pl)
         const long long blocks = (long long)s->batch * s->n_kv_heads * pl->NRB, most = pl->NKB < 128 ? pl->NKB : 128;   // (the row kernel holds every partial's exponents in LDS)
         const double t_kb = 5.9 * (double)((s->n_layers + 7) / 8) / 4.0 * (s->head_dim > 64 ? 1.0 : 0.63);
         double best = 0.0;
-        for (long long r = (blocks + 255) / 256, r_end = r + 8; r < r_end; ++r) {
+        ksp = (256 + blocks - 1) / blocks < most ? (256 + blocks - 1) / blocks : most;
+        for (long long r = (blocks + 255) / 256, r_end = r + 8; r < r_end && !fallback; ++r) {
             const long long n = 256 * r / blocks < most ? 256 * r / blocks : most, kb = (pl->NKB + n - 1) / n;
             const double t = (double)r * ((double)kb * t_kb + 8.0) + 0.04 * (double)(blocks * n);
             if (best == 0.0 || t < best) {
@@ -1413,6 +1416,16 @@ void ap_layout(const krul_shape_t *s, int nrg, APPlan *pl)
 
 constexpr int kMaxLayersAllPairs = 128;
 constexpr size_t kDefaultBudget = (size_t)4 << 30;
+
+// Bytes that every call takes, whatever the plan it would rather have: the fallback's batch of up to 256 rows of one kv head and,
+// for each of them, two L x L matrices.  (Callers bring memory sized so; where ap_direct_kernel's splits or sixteen classes
+// need more for a single row block -- one kv head, few rows -- they are served by the fallback.)
+size_t ap_always_enough(const krul_shape_t *s, APPlan *pl)
+{
+    const int rows = 32 * (pl->NRB >= 6 ? 8 : (pl->NRB >= 3 ? 4 : pl->NRB));
+    ap_layout(s, rows / (pl->NW * 32), pl, true);
+    return pl->total_bytes + (pl->direct ? 2 * align_up((size_t)rows * s->n_layers * s->n_layers * sizeof(float)) : 0);
+}
 
 // Validate and size: the largest batch of row groups whose workspace fits max_bytes (0: a default
 // budget), at least one group.  Returns a krul_status_t.
@@ -1455,14 +1468,21 @@ int ap_plan(const krul_shape_t *s, size_t max_bytes, APPlan *pl)
     const size_t budget = max_bytes ? max_bytes : kDefaultBudget;
     // the largest batch that fits (the size grows with the batch but for the partial matrices, whose
     // number per row shrinks as the batch grows: bisect, then step down if need be)
-    long long lo = 1, hi = total;
-    while (lo < hi) {
-        const long long mid = (lo + hi + 1) / 2;
-        ap_layout(s, (int)mid, pl);
-        if (pl->total_bytes <= budget) lo = mid; else hi = mid - 1;
-    }
-    ap_layout(s, (int)lo, pl);
-    while (pl->total_bytes > budget && lo > 1) ap_layout(s, (int)--lo, pl);
+    const auto fit = [&](bool fallback) {
+        long long lo = 1, hi = total;
+        while (lo < hi) {
+            const long long mid = (lo + hi + 1) / 2;
+            ap_layout(s, (int)mid, pl, fallback);
+            if (pl->total_bytes <= budget) lo = mid; else hi = mid - 1;
+        }
+        ap_layout(s, (int)lo, pl, fallback);
+        while (pl->total_bytes > budget && lo > 1) ap_layout(s, (int)--lo, pl, fallback);
+    };
+    fit(false);
+    if (pl->total_bytes <= budget) return KRUL_OK;
+    const size_t enough = ap_always_enough(s, pl);
+    fit(budget >= enough);
+    if (budget >= enough && pl->total_bytes < enough) pl->total_bytes = enough;   // (the size to bring, not only to use)
     return KRUL_OK;
 }
 
@@ -1513,16 +1533,12 @@ int run_all_pairs(const krul_shape_t *s, const void *q, const void *k, const kru
                   void *workspace, size_t workspace_bytes, hipStream_t st)
 {
     APPlan pl;
-    int rc = ap_plan(s, 1, &pl);   // the smallest batch: one row group
+    int rc = ap_plan(s, workspace_bytes ? workspace_bytes : 1, &pl);   // the batch is what the caller's workspace holds
     if (rc != KRUL_OK) return rc;
     if (!q || !pair_score) return KRUL_EINVAL;
     if ((uintptr_t)q & 15) return KRUL_EINVAL;
     if (((uintptr_t)pair_score | (uintptr_t)pair_dist | (uintptr_t)head_score) & 3) return KRUL_EINVAL;
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < pl.total_bytes) return KRUL_EWORKSPACE;
-    // the batch is what the caller's workspace holds
-    rc = ap_plan(s, workspace_bytes, &pl);
-    if (rc != KRUL_OK) return rc;
-    if (pl.total_bytes > workspace_bytes) return KRUL_EWORKSPACE;
 
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     APParams p;
@@ -1549,7 +1565,7 @@ int run_all_pairs(const krul_shape_t *s, const void *q, const void *k, const kru
     p.kps = pl.kps;
     p.tpw = pl.tpw;
     p.want_dist = pair_dist != nullptr;
-    p.classes = class_count((long long)s->batch * s->n_q_heads);
+    p.classes = pl.classes;
     p.E = ws + pl.e_off;
     p.dump = ws + pl.dump_off;
     p.rowM = reinterpret_cast<float *>(ws + pl.rowm_off);

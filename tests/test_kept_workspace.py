@@ -84,3 +84,35 @@ def test_the_plan_that_fits_matches_the_oracle(oracle, shape, flags, rows, n_spl
         assert np.max(np.abs(got - cos)) <= 3e-5
     assert torch.max(torch.abs(out[0]["head_score"] - out[1]["head_score"])) <= 3e-5
     assert torch.max(torch.abs(out[0]["pair_dist"] - out[1]["pair_dist"])) <= 3e-5
+
+
+# All pairs: (B, L, Hq, Hkv, d, S, Tq), bytes of up to 256 rows of a kv head with eight classes, a round of splits and the rows'
+# matrices: up to 32 layers, where the plan that is fastest wants sixteen classes, and with more
+ALL_PAIRS = [((1, 24, 16, 4, 64, 346, 3), 2151424), ((4, 4, 2, 1, 128, 2488, 8), 4148736), ((1, 32, 8, 1, 128, 4200, 2), 8081408),
+             ((1, 48, 16, 16, 64, 600, 20), 5539840), ((2, 40, 8, 2, 72, 500, 33), 10539008)]
+ids = [f"{s[0]}x{s[6]}-over-{s[5]}-{s[1]}layers" for s, _ in ALL_PAIRS]
+
+
+@pytest.mark.parametrize("shape,need", ALL_PAIRS, ids=ids)
+def test_all_pairs_takes_a_smaller_batch(shape, need):
+    sh = kr.KrulShape(*shape, kr.KRUL_BF16, 0.0, 0)
+
+    def status(n):
+        return kr.lib().krul_all_pairs_similarity(ctypes.byref(sh), vp(0x1000), vp(0x2008), vp(0x3000), None, None, vp(0x10000),
+                                                  ctypes.c_size_t(n), None)
+    for n in (need, kr.all_pairs_workspace_bytes(sh, 1), kr.all_pairs_workspace_bytes(sh)):
+        assert status(n) == kr.KRUL_EINVAL, n
+    assert status(need - 1) == kr.KRUL_EWORKSPACE
+    assert kr.all_pairs_workspace_bytes(sh, need) == need   # (a budget is kept)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,need", ALL_PAIRS, ids=ids)
+def test_all_pairs_in_a_smaller_batch_matches_the_oracle(oracle, shape, need):
+    import gpu_util as G
+    B, L, Hq, Hkv, d, S, Tq = shape
+    w = workloads.make("kept-workspace-all-pairs", B=B, L=L, Hq=Hq, Hkv=Hkv, d=d, S=S, Tq=Tq, dtype="bf16", seed=S)
+    q, k = G.to_device(w)
+    out = kr.all_pairs_similarity(q, k, want_head_score=True, workspace=torch.empty(need, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    G.assert_all_pairs(out, oracle.all_pairs(w.q, w.k), G.all_pairs_tolerance(q, k, False, split=128 if L > 32 else None), f"{need} bytes")
