@@ -122,8 +122,8 @@ long long record_bytes(const krul_shape_t *s, const MfmaForm &f, long long n_spl
 // workgroups, one round and a sixteenth, 9.4 in 1768), and choose_long has the last word where its own choice is 7 % faster by
 // its estimate.
 //
-// fallback: the plan for a workspace that does not hold the fastest one, see make_plan.
-MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static, bool fallback = false)
+// fallback: set to the plan for a workspace that does not hold the fastest one, see Plan.
+MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static, MfmaChoice *fallback)
 {
     const long long B = s->batch, L = s->n_layers, Hkv = s->n_kv_heads, S = s->n_hist, Tq = s->n_query;
     const long long Rk = s->n_q_heads / Hkv * Tq, d = s->head_dim;
@@ -150,12 +150,14 @@ MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bo
         // (Not a prefill chunk on keys in place whose records at one tile per split stay small: see below.)
         const bool chunk = causal && !plain_keys && Tq > f.rows() && B * Hkv * nrt * tiles * L * f.rows() * 16 <= limit;
         if (big || (nrt % 8 == 0 && tiles >= 16 && want <= 4 && !chunk))
-            return splits(f, want < 4 && tiles >= 16 && nrt % 8 == 0 ? 4 : want, 1);
+            return *fallback = splits(f, want < 4 && tiles >= 16 && nrt % 8 == 0 ? 4 : want, 1);
     }
 
-    MfmaChoice best = {nullptr, 0, 0, 0};
-    double best_t = 0.0;
-    long long best_bytes = 0;
+    struct Best {
+        MfmaChoice c;
+        double t;
+        long long bytes;
+    } best = {}, best_whole = {};
     const auto consider = [&](const MfmaForm &f, long long want, long long chunks) {
         const MfmaChoice c = splits(f, want, chunks);
         if (chunks > 1 && c.tiles_per_split > 1) return;
@@ -187,17 +189,17 @@ MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bo
         // (idle places draw no keys: the stream is up to 15 % slower.  For up to 32 rows, which do little else than wait for it, also
         // those of a last round -- one token over 6000 keys in three chunks of layers, 576 workgroups for 512 places, 104 us, in two
         // 85, 3 of 5535 keys and 80 layers 629 and 532; not for more, which hide it: 57 tokens over 276 keys 62 us, 70 so.)
-        const double taken = Rk <= 32 && !fallback ? n_wg / slots / ceil(n_wg / slots) : fmin(1.0, n_wg / slots);
+        const bool last_round = Rk <= 32;
         const double bytes = (double)(B * d * 2) * (double)(Hkv * S + s->n_q_heads * Tq) * layers_read;
-        const double t_stream = bytes / (f.short_stream[d > 64] * 1e6 * (0.85 + 0.15 * taken)) + kWorkgroupStart;
-        // (slim tiles have next to nothing to do but wait for keys; the others' steps hide most of the stream)
-        const double t = fmax(t_steps, t_stream) + record_time(record_bytes, chunk) + (Rk > 32 ? 0.1 * fmin(t_steps, t_stream) : 0.0);
-        // The fastest within the limit on records; where none is, the one with the fewest.
-        if (!best.form || (record_bytes <= limit ? best_bytes > limit || t < best_t : best_bytes > limit && record_bytes < best_bytes)) {
-            best = c;
-            best_t = t;
-            best_bytes = record_bytes;
-        }
+        const auto take = [&](Best &b, double taken) {
+            const double t_stream = bytes / (f.short_stream[d > 64] * 1e6 * (0.85 + 0.15 * taken)) + kWorkgroupStart;
+            // (slim tiles have next to nothing to do but wait for keys; the others' steps hide most of the stream)
+            const double t = fmax(t_steps, t_stream) + record_time(record_bytes, chunk) + (Rk > 32 ? 0.1 * fmin(t_steps, t_stream) : 0.0);
+            // The fastest within the limit on records; where none is, the one with the fewest.
+            if (!b.c.form || (record_bytes <= limit ? b.bytes > limit || t < b.t : b.bytes > limit && record_bytes < b.bytes)) b = {c, t, record_bytes};
+        };
+        take(best, last_round ? n_wg / slots / ceil(n_wg / slots) : fmin(1.0, n_wg / slots));
+        if (Rk <= 32) take(best_whole, fmin(1.0, n_wg / slots));
     };
     const auto consider_form = [&](const MfmaForm &f) {
         const long long tiles = ceil_div(S, f.kt), nrt = ceil_div(Rk, f.rows()), units = B * Hkv * nrt;
@@ -232,7 +234,8 @@ MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bo
         consider_form(kMidForm);
         consider_form(kMidShortForm);
     }
-    return best;
+    *fallback = Rk <= 32 ? best_whole.c : best.c;
+    return best.c;
 }
 
 // o: the plan of choose_short, which stays unless there is one that takes 7 % less.
@@ -342,10 +345,9 @@ MfmaChoice choose_long(const krul_shape_t *s, bool want_ir, bool plain_keys, con
 // in_static: for krul_pair_similarity_static.  Its limit on records is the library's own area: the plan of the call with a
 // workspace where that fits, and otherwise choose_short's within the limit.  (What that does not fit is refused: large calls
 // with many query rows, which should bring a workspace.)
-MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static, bool fallback)
+MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, bool in_static, MfmaChoice *fallback)
 {
-    if (fallback) return choose_short(s, want_ir, plain_keys, false, true);
-    MfmaChoice c = choose_long(s, want_ir, plain_keys, choose_short(s, want_ir, plain_keys, false));
+    MfmaChoice c = choose_long(s, want_ir, plain_keys, choose_short(s, want_ir, plain_keys, false, fallback));
     // Heads up to 64, wide tiles, an even number of them in a split: half as many tiles of twice the keys.  What a layer step
     // costs beside its blocks -- merging, waiting -- is a third of it there (2 x 128 tokens over 16384 keys of 24 layers, 16/4
     // heads, 467 us in tiles of 256 keys, 426 so; 256 over 16384 with strides 470 and 448).  With two of 256 it depends: 64 over
@@ -355,13 +357,13 @@ MfmaChoice choose_mfma(const krul_shape_t *s, bool want_ir, bool plain_keys, boo
         c = MfmaChoice{&kWideDeepForm, c.n_split, c.tiles_per_split / 2, 1};
     if (!in_static) return c;
     const auto fits = [&](const MfmaChoice &m) { return record_bytes(s, *m.form, m.n_split) <= static_limit(s); };
-    const MfmaChoice o = choose_short(s, want_ir, plain_keys, true);
+    const MfmaChoice o = choose_short(s, want_ir, plain_keys, true, fallback);
     return fits(o) && fits(c) ? c : o;
 }
 
 }  // namespace
 
-int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bool in_static, bool fallback)
+int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bool in_static, bool take_fallback)
 {
     const int rc = check_shape(s);
     if (rc != KRUL_OK) return rc;
@@ -380,9 +382,12 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
     const bool mfma = (s->dtype == KRUL_BF16 || s->dtype == KRUL_F16) && s->head_dim <= 128 &&
                       !(s->flags & KRUL_FLAG_GENERIC_KERNEL);
     bool generic = (s->flags & KRUL_FLAG_GENERIC_KERNEL) != 0;
-    long long n_wg = 0, records = 0;
+    long long n_wg = 0, records = 0, fallback_records = 0;
     if (mfma) {
-        const MfmaChoice ch = choose_mfma(s, want_ir, plain_keys, in_static, fallback);
+        MfmaChoice fallback;
+        MfmaChoice ch = choose_mfma(s, want_ir, plain_keys, in_static, &fallback);
+        if (take_fallback) ch = fallback;
+        fallback_records = record_bytes(s, *fallback.form, fallback.n_split) / 16;
         const MfmaForm &f = *ch.form;
         y.variant = f.variant;
         y.wr = f.wr;
@@ -465,28 +470,22 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
     }
     if (n_wg > INT32_MAX) return KRUL_EUNSUPPORTED;
     pl->n_workgroups = (int)n_wg;
-    pl->state_bytes = round_up((size_t)records * sizeof(float4), kAlign);
     const size_t head_bytes = round_up((size_t)(B * (L - 1) * Hq) * sizeof(float), kAlign);
-    pl->head_cos_off = pl->state_bytes;
-    pl->head_dist_off = pl->head_cos_off + head_bytes;
-    pl->total_bytes = pl->head_dist_off + head_bytes;
-    pl->state_ir_off = pl->head_ir_off = 0;
-    if (want_ir) {
-        pl->state_ir_off = pl->total_bytes;
-        pl->head_ir_off = pl->state_ir_off + round_up((size_t)records * sizeof(float), kAlign);
-        pl->total_bytes = pl->head_ir_off + round_up((size_t)(B * L * Hq) * sizeof(float), kAlign);
-    }
+    const auto layout = [&](size_t n) {   // of n records
+        pl->head_cos_off = pl->state_bytes = round_up(n * sizeof(float4), kAlign);
+        pl->head_dist_off = pl->head_cos_off + head_bytes;
+        pl->total_bytes = pl->head_dist_off + head_bytes;
+        pl->state_ir_off = pl->head_ir_off = 0;
+        if (want_ir) {
+            pl->state_ir_off = pl->total_bytes;
+            pl->head_ir_off = pl->state_ir_off + round_up(n * sizeof(float), kAlign);
+            pl->total_bytes = pl->head_ir_off + round_up((size_t)(B * L * Hq) * sizeof(float), kAlign);
+        }
+        return pl->total_bytes;
+    };
+    pl->fallback_bytes = layout((size_t)(fallback_records ? fallback_records : records));
+    layout((size_t)records);
     return KRUL_OK;
-}
-
-// Bytes that hold both the plan of a call and its fallback (0: unsupported).
-size_t plan_bytes(const krul_shape_t *s, bool want_ir, bool plain_keys)
-{
-    Plan pl, fallback;
-    if (make_plan(s, &pl, want_ir, plain_keys) != KRUL_OK) return 0;
-    if (pl.lay.variant == kGeneric || pl.lay.variant == kF32) return pl.total_bytes;   // (one plan for all)
-    if (make_plan(s, &fallback, want_ir, plain_keys, false, true) != KRUL_OK) return pl.total_bytes;
-    return pl.total_bytes > fallback.total_bytes ? pl.total_bytes : fallback.total_bytes;
 }
 
 int resolve_keys(const krul_shape_t *s, bool mfma, bool dense_2gib, const void *k, const krul_k_layout_t *kl,
@@ -581,8 +580,8 @@ int run_similarity(const krul_shape_t *shape, const void *q, const void *k, floa
     if (ir && (!(gamma >= 0.f) || !isfinite(gamma) || (!ir_mass && !eligible))) return KRUL_EINVAL;
     if (!workspace || ((uintptr_t)workspace & (kAlign - 1))) return KRUL_EWORKSPACE;
     if (workspace_bytes < pl.total_bytes) {
-        if (in_static || make_plan(shape, &pl, ir, k != nullptr && !kl && !kp, false, true) != KRUL_OK ||
-            workspace_bytes < pl.total_bytes)
+        if (in_static || workspace_bytes < pl.fallback_bytes ||
+            make_plan(shape, &pl, ir, k != nullptr && !kl && !kp, false, true) != KRUL_OK)
             return KRUL_EWORKSPACE;
     }
 
@@ -681,9 +680,15 @@ int krul_pair_similarity_plan(const krul_shape_t *shape, int32_t *n_workgroups, 
 
 size_t krul_pair_similarity_workspace(const krul_shape_t *shape)
 {
-    // enough for the call on dense keys and for the calls on keys read in place (their plans may differ)
-    const size_t in_place = plan_bytes(shape, false, false), dense = plan_bytes(shape, false, true);
-    return in_place == 0 || dense == 0 ? 0 : in_place > dense ? in_place : dense;
+    // enough for the call on dense keys and for the calls on keys read in place (their plans may differ for more than 64 rows),
+    // each with its fallback
+    Plan pl;
+    if (make_plan(shape, &pl) != KRUL_OK) return 0;
+    size_t need = pl.total_bytes > pl.fallback_bytes ? pl.total_bytes : pl.fallback_bytes;
+    if (pl.lay.variant == kGeneric || pl.lay.variant == kF32 || pl.lay.rows_per_unit <= 64) return need;
+    if (make_plan(shape, &pl, false, true) != KRUL_OK) return 0;
+    if (need < pl.total_bytes) need = pl.total_bytes;
+    return need > pl.fallback_bytes ? need : pl.fallback_bytes;
 }
 
 int krul_pair_similarity(const krul_shape_t *shape, const void *q, const void *k,
@@ -869,7 +874,9 @@ int krul_pair_scores_from_sums(const float *head_sum, const float *head_dist_sum
 
 size_t krul_pair_similarity_ir_workspace(const krul_shape_t *shape)
 {
-    return plan_bytes(shape, true, false);
+    Plan pl;
+    if (make_plan(shape, &pl, true) != KRUL_OK) return 0;
+    return pl.total_bytes > pl.fallback_bytes ? pl.total_bytes : pl.fallback_bytes;
 }
 
 int krul_pair_similarity_ir(const krul_shape_t *shape, const void *q, const void *k, float gamma,

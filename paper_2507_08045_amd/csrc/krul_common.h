@@ -63,6 +63,11 @@ struct Plan {
     float c;             // scale * log2(e)
     size_t state_bytes;  // merged partial records (float4), read by the finalize kernel
     size_t head_cos_off, head_dist_off, total_bytes;
+    // Workspace of the plan for callers whose memory does not hold this one: choose_short's, with rounds counted whole for the
+    // stream of keys too.  Memory that holds either is taken, and the size query names the larger, so that memory sized for the
+    // fallback serves a growing history although the fastest plans jump (8 x 172 tokens of 32/8 heads over 1024 to 32768 keys:
+    // 48 MB at every length, where the fastest take 48 to 504).
+    size_t fallback_bytes;
     // Initial-Recent layer test only: one float per record beside state, head means
     size_t state_ir_off, head_ir_off;
 };
@@ -72,11 +77,8 @@ struct Plan {
 // plain_keys: the keys are dense and no mask or Initial-Recent test is asked for -- what the many-query kernel
 // (kMfmaBig) takes; the plan (and so the workspace) may differ with it.
 // in_static: a plan for the scratch area of krul_pair_similarity_static, if there is one that fits it.
-// fallback: the plan for a workspace that does not hold the fastest one: choose_short's, with rounds counted whole for the stream
-// of keys too.  A workspace that holds either is taken, and the size query names the larger, so that memory sized for the
-// fallback serves a growing history although the fastest plans jump (8 x 172 tokens of 32/8 heads over 1024 to 32768 keys:
-// 48 MB at every length, where the fastest take 48 to 504).
-int make_plan(const krul_shape_t *s, Plan *plan, bool want_ir = false, bool plain_keys = false, bool in_static = false, bool fallback = false);
+// take_fallback: the plan that Plan::fallback_bytes belongs to.
+int make_plan(const krul_shape_t *s, Plan *plan, bool want_ir = false, bool plain_keys = false, bool in_static = false, bool take_fallback = false);
 
 struct SimParams {
     const void *q;
