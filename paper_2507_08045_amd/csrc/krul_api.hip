@@ -188,8 +188,10 @@ MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bo
         }
         // (idle places draw no keys: the stream is up to 15 % slower.  For up to 32 rows, which do little else than wait for it, also
         // those of a last round -- one token over 6000 keys in three chunks of layers, 576 workgroups for 512 places, 104 us, in two
-        // 85, 3 of 5535 keys and 80 layers 629 and 532; not for more, which hide it: 57 tokens over 276 keys 62 us, 70 so.)
-        const bool last_round = Rk <= 32;
+        // 85, 3 of 5535 keys and 80 layers 629 and 532; not for more, which hide it: 57 tokens over 276 keys 62 us, 70 so; nor for heads
+        // up to 64 where it makes one chunk, whose workgroups do not fill the places once, look better than several: 13 tokens of
+        // 1652 keys and 24 layers in one chunk 69.6 us, in two 61.3, 2 of 11145 keys 70.4 and 62.9.)
+        const bool last_round = Rk <= 32 && !(d <= 64 && chunks > 1 && n_splits_all < (long long)slots);
         const double bytes = (double)(B * d * 2) * (double)(Hkv * S + s->n_q_heads * Tq) * layers_read;
         const auto take = [&](Best &b, double taken) {
             const double t_stream = bytes / (f.short_stream[d > 64] * 1e6 * (0.85 + 0.15 * taken)) + kWorkgroupStart;

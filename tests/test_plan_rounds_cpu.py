@@ -29,6 +29,12 @@ def test_no_nearly_empty_last_round_of_a_decode_step(shape):
     assert rounds <= 1 or rounds / math.ceil(rounds) >= 0.7, p
 
 
+@pytest.mark.parametrize("shape", [(2, 24, 16, 4, 64, 11145, 1), (13, 24, 16, 4, 64, 1652, 1), (2, 24, 16, 4, 64, 10944, 5)], ids=lambda s: f"{s[0]}x{s[6]}-over-{s[5]}")
+def test_small_heads_cut_the_layers_rather_than_leave_one_workgroup_a_cu(shape):
+    p = kr.plan(kr.KrulShape(*shape, kr.KRUL_BF16, 0.0, kr.KRUL_FLAG_CAUSAL))
+    assert p["form"] == 5 and p["n_workgroups"] > 512, p
+
+
 def test_forms_are_told_apart():
     """Every long 16-bit call takes a matrix-core form, whatever its number: 0 is the kernel of float32 inputs and heads above 128."""
     for d in (8, 40, 64, 72, 96, 128):
