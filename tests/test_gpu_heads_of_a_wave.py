@@ -33,9 +33,10 @@ def test_scores_and_running_sums(G, oracle, case):
     kr.pair_similarity_accumulate(q, k, head_sum, dist_sum)
     torch.cuda.synchronize()
     head, dist = out["head_score"].cpu().numpy(), out["pair_dist"].cpu().numpy()
-    # an exponential is known to 1e-6 (logits to 2^-21), a lane adds at most 128 of them (128 * 2^-24 = 8e-6), and a cosine is made of three such sums
-    assert np.max(np.abs(head - want["head_score"])) <= 3e-5
-    assert np.max(np.abs(dist - want["pair_dist"])) <= 3e-5
+    # an exponential is known to 7e-7 (logits below 16 to 2^-20); a cosine or a distance of one row of tens of keys moves by about as much
+    e = [np.max(np.abs(head - want["head_score"])), np.max(np.abs(dist - want["pair_dist"]))]
+    print(f"[{g} heads, {Tq} tokens, {S} keys] cos {e[0]:.1e} dist {e[1]:.1e}", flush=True)
+    assert max(e) <= 2e-6
     # sums of up to 560 are rounded to 2^-15
     assert np.max(np.abs((head_sum - start).cpu().numpy() - Tq * head)) <= 2.0 ** -14 + Tq * 1e-6
     assert np.max(np.abs((dist_sum - start).cpu().numpy().mean(-1) - Tq * dist)) <= 2.0 ** -14 + Tq * 1e-6

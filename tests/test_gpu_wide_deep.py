@@ -31,12 +31,12 @@ def test_matches_other_tiles(case, dtype):
         assert kr.plan(kr.make_shape(q, k, 0.125, flags))["form"] == 10
         assert kr.plan(kr.make_shape(*padded, 0.125, flags))["form"] != 10
         got, want = (kr.pair_similarity(*t, scale=0.125, flags=flags) for t in ((q, k), padded))
-        # the logits are the same bits; sums of float32 in another order, at most 256 terms a lane before they are joined: 256 * 2^-24
-        assert torch.max(torch.abs(got["head_score"] - want["head_score"])) <= 1.6e-5
-        assert torch.max(torch.abs(got["pair_dist"] - want["pair_dist"])) <= 1.6e-5
+        # the logits are the same bits and the sums of float32 are in another order: terms that round at random (7e-8 is seen), means of thousands
+        assert torch.max(torch.abs(got["head_score"] - want["head_score"])) <= 1e-6
+        assert torch.max(torch.abs(got["pair_dist"] - want["pair_dist"])) <= 1e-6
         for keys in in_place:
             cos, dist = (torch.zeros((B, L - 1, Hq), device="cuda") for _ in range(2))
             kr.pair_similarity_accumulate_in_place(q, keys, cos, dist, scale=0.125, flags=flags)
-            # (and a sum of Tq of them, divided by Tq)
-            assert torch.max(torch.abs(cos / Tq - want["head_score"])) <= 3.2e-5
-            assert torch.max(torch.abs((dist / Tq).mean(-1) - want["pair_dist"])) <= 3.2e-5
+            # (and a sum of Tq of them, rounded to 2^-24 of itself in each of its dozen joins, divided by Tq)
+            assert torch.max(torch.abs(cos / Tq - want["head_score"])) <= 2e-6
+            assert torch.max(torch.abs((dist / Tq).mean(-1) - want["pair_dist"])) <= 2e-6

@@ -80,10 +80,10 @@ def test_the_plan_that_fits_matches_the_oracle(oracle, shape, flags, rows, n_spl
     torch.cuda.synchronize()
     for o in out:
         got = np.array([float(o["head_score"][u]) for u in units])
-        # exponentials known to 1e-6 (logits to 2^-21); a lane adds at most 128 of a tile's before they are joined, three such sums to a cosine
-        assert np.max(np.abs(got - cos)) <= 3e-5
-    assert torch.max(torch.abs(out[0]["head_score"] - out[1]["head_score"])) <= 3e-5
-    assert torch.max(torch.abs(out[0]["pair_dist"] - out[1]["pair_dist"])) <= 3e-5
+        # exponentials known to 7e-7 (logits below 16 to 2^-20), means of rows of thousands of keys
+        assert np.max(np.abs(got - cos)) <= 1e-6
+    assert torch.max(torch.abs(out[0]["head_score"] - out[1]["head_score"])) <= 1e-6
+    assert torch.max(torch.abs(out[0]["pair_dist"] - out[1]["pair_dist"])) <= 1e-6
 
 
 # All pairs: (B, L, Hq, Hkv, d, S, Tq), bytes of up to 256 rows of a kv head with eight classes, a round of splits and the rows'
