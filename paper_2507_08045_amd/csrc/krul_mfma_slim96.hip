@@ -9,7 +9,7 @@ hipError_t launch_sim_mfma_slim128(const SimParams &p, int n_workgroups, hipStre
 
 hipError_t launch_sim_mfma_slim96(const SimParams &p, int n_workgroups, hipStream_t st)
 {
-    // (the 32 x 512 form, for problems of hundreds of gigabytes at these sizes, runs as for 128)
+    // (the 32 x 512 form, which a plan takes at these sizes from some 38 GB of keys on, runs as for 128)
     if (p.lay.variant != kMfmaSlimShort) return launch_sim_mfma_slim128(p, n_workgroups, st);
     //                 D  WR WK KBW NC KS
     return launch_cfg<Cfg<128, 1, 4, 1, 2, 6>>(p, n_workgroups, st);   //  32 x 256, 4 waves, ring 2 x 128 keys: two workgroups per CU

@@ -22,9 +22,9 @@ __global__ __launch_bounds__(kSelThreads) void select_pairs_kernel(
 }
 
 // Averages over the heads and the greedy choice of one conversation per workgroup: two steps whose launches cost more
-// than the work in them.  Bound by latency: a half-wave per pair reads its head values and adds them by shuffles (the
-// same bits as finalize_pairs_kernel), so that one load and five shuffles stand between the launch and the scores.
-// (Staged in LDS and added by a thread per pair, head after head: 9.4 us for 31 pairs of 32 heads, 5.6 us now.)
+// than the work in them.  Bound by latency: a half-wave per pair reads its head values and adds them by DPP and
+// permlane swaps (the same bits as finalize_pairs_kernel), so that one load and five such adds stand between the launch and the
+// scores.  (Staged in LDS and added by a thread per pair, head after head: 9.4 us for 31 pairs of 32 heads, 4.8 us now.)
 constexpr int kPsThreads = 1024;
 
 __global__ __launch_bounds__(kPsThreads) void pairs_select_kernel(PairsSelectArgs a)
