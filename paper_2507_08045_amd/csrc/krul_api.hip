@@ -102,6 +102,16 @@ long long record_bytes(const krul_shape_t *s, const MfmaForm &f, long long n_spl
     return (long long)s->batch * s->n_kv_heads * ceil_div(rows, f.rows()) * f.rows() * n_split * s->n_layers * 16;
 }
 
+// The calls that 256 x 256 tiles may take: the rows fill 256-row tiles well and there are two rounds of workgroups or more.  One factor
+// of their cross terms is held in binary16 (cosines of 49 rows over 14839 keys off by 2e-6, 4e-8 in the other shapes), so
+// that no others are given to them, also where they would be faster.
+bool many_query(const krul_shape_t *s, bool want_ir, bool plain_keys)
+{
+    const long long Rk = (long long)s->n_q_heads / s->n_kv_heads * s->n_query, nrt = ceil_div(Rk, 256), tiles = ceil_div(s->n_hist, 256);
+    return plain_keys && !want_ir && !(s->flags & KRUL_FLAG_CAUSAL) && s->head_dim == 128 && Rk > 64 && nrt * 256 * 7 <= Rk * 8 &&
+           (long long)s->batch * s->n_kv_heads * nrt * tiles >= 512;
+}
+
 // Which tile shape, how many key splits and how many layer chunks.
 //
 // A workgroup walks (tiles of its key split) x (layers of its chunk) steps one after the other, and workgroups run in
@@ -138,10 +148,8 @@ MfmaChoice choose_short(const krul_shape_t *s, bool want_ir, bool plain_keys, bo
     if (Rk > 64) {
         // Many query rows on a large problem: 256 x 256 tiles (two 32-row blocks per wave, the previous layer's
         // exponentials kept as binary16 pairs) move a third fewer bytes per logit and read half the operands.
-        // Taken when the rows fill 256-row tiles well and there are two rounds of workgroups or more.
-        const long long nrt_big = ceil_div(Rk, 256), tiles = ceil_div(S, 256);
-        const bool big = plain_keys && !want_ir && !causal && d == 128 && nrt_big * 256 * 7 <= Rk * 8 &&
-                         B * Hkv * nrt_big * tiles >= 512;
+        const long long tiles = ceil_div(S, 256);
+        const bool big = many_query(s, want_ir, plain_keys);
         // Here, and where the 128-row tile has as many row tiles, four key splits (or the round's worth, if that is
         // more) per row tile: the workgroups running side by side on an XCD then form patches of 8 row tiles x 4 key
         // splits (patch_rows()) and share both their query rows and their keys through the L2.
@@ -336,7 +344,7 @@ MfmaChoice choose_long(const krul_shape_t *s, bool want_ir, bool plain_keys, con
         if (Rk > 64) {
             consider_form(kWideForm);
             consider_form(kWideShortForm);
-            if (plain_keys && !want_ir && !causal && d == 128 && Rk > 128) consider_form(kBigForm);
+            if (many_query(s, want_ir, plain_keys)) consider_form(kBigForm);
         }
         consider_form(kMidForm);
         consider_form(kMidShortForm);

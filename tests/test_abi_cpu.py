@@ -292,7 +292,7 @@ def test_plan_for_the_benchmark_shapes(kr):
         a.update(over)
         return kr.plan(kr.KrulShape(a["B"], a["L"], a["Hq"], a["Hkv"], a["d"], a["S"], a["Tq"], dtype, 0.0, a["flags"]))
 
-    assert plan("C1")["form"] == 0                                   # fp32: the portable kernel
+    assert plan("C1")["form"] == 0                                   # float32 kernel
     c2 = plan("C2")
     assert c2["form"] == 1 and c2["n_workgroups"] == 256 and c2["n_key_splits"] == 16
     assert plan("C3")["form"] == 2                                   # 64 rows per kv head: the 64 x 512 tile

@@ -22,7 +22,7 @@ def G():
 CASES = [
     ("sel-wide", 1, 12, 8, 2, 128, 1500, 40, "bf16", 4, False),        # several key splits, one conversation
     ("sel-batch", 3, 9, 4, 2, 64, 700, 6, "bf16", 3, True),            # three conversations, a workgroup each
-    ("sel-f32", 2, 6, 4, 2, 64, 300, 5, "f32", 2, True),               # portable similarity kernel
+    ("sel-f32", 2, 6, 4, 2, 64, 300, 5, "f32", 2, True),               # float32 kernel
     ("sel-two-layers", 1, 2, 2, 1, 64, 40, 1, "bf16", 1, False),
     ("sel-none", 2, 5, 4, 4, 128, 90, 2, "f16", 0, False),             # n_select = 0
     ("sel-many-heads", 2, 130, 128, 8, 64, 100, 1, "bf16", 10, True),    # 129*128 = 16512 head values a conversation: separate kernels

@@ -62,7 +62,7 @@ def test_one_workspace_over_a_growing_history(entry, model, n_split):
 
 # (B, L, Hq, Hkv, d, S, Tq), flags, rows of a tile, key splits of the plan of whole rounds
 PLANS = [((3, 8, 16, 8, 128, 1681, 213), 0, 64, 3), ((2, 4, 16, 4, 96, 19406, 66), kr.KRUL_FLAG_CAUSAL, 64, 19),
-         ((2, 8, 16, 4, 128, 14839, 49), 0, 64, 15), ((1, 8, 32, 8, 128, 13637, 52), 0, 64, 14)]
+         ((2, 4, 16, 8, 64, 19822, 72), 0, 64, 10), ((3, 8, 16, 8, 72, 2080, 231), kr.KRUL_FLAG_CAUSAL, 64, 5)]
 
 
 @pytest.mark.gpu
@@ -79,11 +79,12 @@ def test_the_plan_that_fits_matches_the_oracle(oracle, shape, flags, rows, n_spl
     out = [kr.pair_similarity(q, k, flags=flags, want_head_score=True, workspace=torch.empty(n, dtype=torch.uint8, device="cuda")) for n in (size, need)]
     torch.cuda.synchronize()
     for o in out:
-        got = np.array([float(o["head_score"][u]) for u in units])
-        # exponentials known to 7e-7 (logits below 16 to 2^-20), means of rows of thousands of keys
-        assert np.max(np.abs(got - cos)) <= 1e-6
-    assert torch.max(torch.abs(out[0]["head_score"] - out[1]["head_score"])) <= 1e-6
-    assert torch.max(torch.abs(out[0]["pair_dist"] - out[1]["pair_dist"])) <= 1e-6
+        err = np.max(np.abs(np.array([float(o["head_score"][u]) for u in units]) - cos))
+        print(f"[{shape}] {err:.2e}", flush=True)
+        # exponentials known to 7e-7 (logits below 16 to 2^-20), means of rows of thousands of keys to a fraction of that
+        assert err <= 1e-6
+    for n in ("head_score", "pair_dist"):
+        assert torch.max(torch.abs(out[0][n] - out[1][n])) <= 2e-6
 
 
 # All pairs: (B, L, Hq, Hkv, d, S, Tq), bytes of up to 256 rows of a kv head with eight classes, a round of splits and the rows'

@@ -35,6 +35,17 @@ def test_small_heads_cut_the_layers_rather_than_leave_one_workgroup_a_cu(shape):
     assert p["form"] == 5 and p["n_workgroups"] > 512, p
 
 
+# calls for which 256 x 256 tiles are estimated to be the fastest, though their rows fill them badly or they are small
+@pytest.mark.parametrize("shape", [(2, 8, 16, 4, 128, 14839, 49), (1, 8, 32, 8, 128, 13637, 52), (5, 32, 32, 8, 128, 12524, 50), (3, 80, 64, 8, 128, 1116, 51)],
+                         ids=lambda s: f"{s[0]}x{s[6]}-over-{s[5]}")
+def test_no_more_calls_take_the_tiles_that_keep_exponentials_in_binary16(shape):
+    B, L, Hq, Hkv, d, S, Tq = shape
+    rows, tiles = Hq // Hkv * Tq, -(-S // 256)
+    row_tiles = -(-rows // 256)
+    assert row_tiles * 256 * 7 > rows * 8 or B * Hkv * row_tiles * tiles < 512
+    assert kr.plan(kr.KrulShape(*shape, kr.KRUL_BF16, 0.0, 0))["form"] != 8
+
+
 def test_forms_are_told_apart():
     """Every long 16-bit call takes a matrix-core form, whatever its number: 0 is the kernel of float32 inputs and heads above 128."""
     for d in (8, 40, 64, 72, 96, 128):

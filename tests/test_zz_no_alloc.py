@@ -23,7 +23,7 @@ def test_static_scratch_matches_workspace_call(oracle):
     cases = [
         workloads.make("na-1", B=2, L=6, Hq=8, Hkv=2, d=128, S=3000, Tq=40, dtype="bf16", rho_k=0.8, seed=71),
         workloads.make("na-2", B=1, L=4, Hq=8, Hkv=2, d=128, S=700, Tq=5, dtype="bf16", rho_k=0.6, seed=72),   # smaller
-        workloads.make("na-3", B=1, L=3, Hq=2, Hkv=2, d=64, S=300, Tq=9, dtype="f32", rho_k=0.7, seed=73),     # portable kernel
+        workloads.make("na-3", B=1, L=3, Hq=2, Hkv=2, d=64, S=300, Tq=9, dtype="f32", rho_k=0.7, seed=73),     # float32 kernel
     ]
     dev = [G.to_device(w) for w in cases]
     want = [kr.pair_similarity(q, k) for q, k in dev]
