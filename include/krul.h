@@ -145,7 +145,8 @@ int krul_pair_similarity_static(const krul_shape_t *shape, const void *q, const 
  *   gamma       threshold, finite and >= 0
  *   ir_mass     [B][L] float   device, may be NULL
  *   eligible    [B][L] uint8   device, may be NULL (not both NULL)
- *   workspace   at least krul_pair_similarity_ir_workspace() bytes (more than the plain call needs)
+ *   workspace   at least krul_pair_similarity_ir_workspace() bytes (a size of its own: the plain call, which may split the
+ *               keys otherwise, can need more or less)
  * Everything else, and the error behaviour, is as for krul_pair_similarity.
  */
 size_t krul_pair_similarity_ir_workspace(const krul_shape_t *shape);
