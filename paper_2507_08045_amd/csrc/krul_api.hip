@@ -645,14 +645,10 @@ int run_similarity(const krul_shape_t *shape, const void *q, const void *k, floa
         return KRUL_ELAUNCH;
     float *head_cos = head_score ? head_score : reinterpret_cast<float *>(ws + pl.head_cos_off);
     float *head_dist = accumulate ? pair_dist : reinterpret_cast<float *>(ws + pl.head_dist_off);
-    if (sel && pairs_select_fits(p.L, p.Hq)) {   // head scores, then pairs and selection in one small launch
-        e = launch_finalize(pl.lay, p.state, p.B, p.L, p.Hq, p.Hkv, p.Tq, head_cos, head_dist, nullptr,
-                            pair_dist, false, nullptr, st);
-        if (e == hipSuccess) {
-            const PairsSelectArgs a = {head_cos, pair_dist ? head_dist : nullptr, pair_score, pair_dist, sel->eligible,
-                                       p.B, p.L, p.Hq, sel->n_select, sel->out_pairs, sel->out_count};
-            e = launch_pairs_select(a, st);
-        }
+    if (sel && pairs_select_fits(p.L, p.Hq)) {   // head scores, pairs and selection in one small launch or two
+        const PairsSelectArgs a = {head_cos, pair_dist ? head_dist : nullptr, pair_score, pair_dist, sel->eligible,
+                                   p.B, p.L, p.Hq, sel->n_select, sel->out_pairs, sel->out_count};
+        e = launch_finalize_select(pl.lay, p.state, p.Hkv, p.Tq, head_score, head_cos, head_dist, a, st);
         return e == hipSuccess ? KRUL_OK : KRUL_ELAUNCH;
     }
     const IrArgs ir_args = {p.state_ir, reinterpret_cast<float *>(ws + pl.head_ir_off), gamma, ir_mass, eligible};

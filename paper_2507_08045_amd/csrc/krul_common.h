@@ -171,6 +171,10 @@ struct IrArgs {
 hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, int L, int Hq, int Hkv,
                            int Tq, float *head_cos, float *head_dist, float *pair_cos,
                            float *pair_dist, bool accumulate, const IrArgs *ir, hipStream_t st);
+// Head scores, pair scores and the selection of a launch of scores (head_out: where the head scores are wanted, or null; head_cos, head_dist:
+// memory for them all the same), in one kernel or two.
+hipError_t launch_finalize_select(const StateLayout &lay, const float4 *state, int Hkv, int Tq, float *head_out,
+                                  float *head_cos, float *head_dist, const PairsSelectArgs &a, hipStream_t st);
 // Pair scores from head scores and the selection, one workgroup per conversation
 // (pairs_select_fits says whether a conversation's head values fit one).
 bool pairs_select_fits(int L, int Hq);

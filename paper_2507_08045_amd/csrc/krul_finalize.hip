@@ -7,6 +7,7 @@
 // (from the a^2 + b^2 - 2ab expansion of Sec. 7) the Euclidean distance of the two
 // attention rows, and the sum over rows is taken in a fixed tree order.
 // finalize_pairs: 32 lanes per (conversation, pair) average the heads (pair_average).
+// heads_select: both, and the greedy choice, for models whose heads one workgroup takes at once.
 //
 // These kernels are bound by the latency of one chain of steps, unless there are thousands of rows: which rows, their
 // records, the merges, the sums.  So the rows are found without a division, a lane asks for the records of four partials at once (one
@@ -126,6 +127,51 @@ __device__ inline float sum_over(float v, int n)
     return v;
 }
 
+// A row's records of layers l and l + 1, merged by the lanes that share it (row: there is one), the same in each of them.
+template <bool IR>
+__device__ inline RowAcc merged_row(const HeadsArgs &p, bool row, int u, int r, int l, int g, int RW, bool last)
+{
+    const int P = p.lay.partials;
+    RowAcc acc = {kMInit, 0.f, 0.f, kMInit, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (row) {
+        const RowRecords q = row_records(p.lay, p.by_tile, u, r, l);
+        for (int p0 = g; p0 < P; p0 += kBatch * p.G) {
+            float4 a[kBatch], c[kBatch];
+            float ia[kBatch], ib[kBatch];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                const size_t at = q.at + (size_t)min(p0 + i * p.G, P - 1) * q.step;
+                a[i] = p.state[at];
+                c[i] = p.state[at + q.next_layer];
+                ia[i] = IR ? p.state_ir[at] : 0.f;
+                ib[i] = last ? p.state_ir[at + q.next_layer] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i)
+                if (p0 + i * p.G < P)
+                    merge_into<IR>(acc, RowAcc{a[i].x, a[i].y, a[i].z, c[i].x, c[i].y, c[i].z, c[i].w, ia[i], ib[i]});
+        }
+    }
+    if (RW <= 32) join<32, IR>(acc);
+    if (RW <= 16) join<16, IR>(acc);
+    if (RW <= 8) join<8, IR>(acc);
+    if (RW <= 4) join<4, IR>(acc);
+    if (RW <= 2) join<2, IR>(acc);
+    if (RW <= 1) join<1, IR>(acc);
+    return acc;
+}
+
+// ... and what the row adds to its head's sums.
+__device__ inline void add_row(const RowAcc &acc, int want_dist, float &cs, float &ds)
+{
+    cs += acc.C * rsqrtf(acc.Na * acc.Nb);
+    if (want_dist) {   // (Z is only accumulated when the distance is asked for)
+        const float ia = 1.f / acc.Za, ib = 1.f / acc.Zb;
+        const float d2 = acc.Na * ia * ia + acc.Nb * ib * ib - 2.f * acc.C * ia * ib;
+        ds += sqrtf(fmaxf(d2, 0.f));
+    }
+}
+
 // IR: also the Initial-Recent layer test (Sec. 4.2; Alg. 1 first loop): per (conversation, layer, head) the
 // mean over query rows of Zir / Z -- the attention mass on T_initial and T_recent -- from the same records: a pair's first
 // layer's, the last pair's second layer's too.  (As items of their own, which read every record once more: 17.9 us for 2 x
@@ -137,7 +183,6 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int item = p.first + (PER_WAVE ? blockIdx.x * (kThreads / 64) + wave : blockIdx.x);
     if (PER_WAVE && item >= p.n_items) return;   // (a whole wave: no barrier follows in this form)
-    const int P = p.lay.partials;
 
     // (conversation b, pair l, kv head, group of heads): each is the remainder of a division
     const int t1 = p.groups > 1 ? (int)p.by_groups(item) : item, group = item - t1 * p.groups;
@@ -156,40 +201,10 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
     const bool last = IR && l == p.L - 2;
     float cs = 0.f, ds = 0.f, mass_a = 0.f, mass_b = 0.f;
     for (int t = t_first; t - t_first < p.Tq; t += PER_WAVE ? 64 : kThreads / 64 * RW) {   // (PER_WAVE: once)
-        RowAcc acc = {kMInit, 0.f, 0.f, kMInit, 0.f, 0.f, 0.f, 0.f, 0.f};
         const bool row = t < p.Tq && head < heads;
-        if (row) {
-            const RowRecords q = row_records(p.lay, p.by_tile, u, head * p.Tq + t, l);
-            for (int p0 = g; p0 < P; p0 += kBatch * p.G) {
-                float4 a[kBatch], c[kBatch];
-                float ia[kBatch], ib[kBatch];
-#pragma unroll
-                for (int i = 0; i < kBatch; ++i) {
-                    const size_t at = q.at + (size_t)min(p0 + i * p.G, P - 1) * q.step;
-                    a[i] = p.state[at];
-                    c[i] = p.state[at + q.next_layer];
-                    ia[i] = IR ? p.state_ir[at] : 0.f;
-                    ib[i] = last ? p.state_ir[at + q.next_layer] : 0.f;
-                }
-#pragma unroll
-                for (int i = 0; i < kBatch; ++i)
-                    if (p0 + i * p.G < P)
-                        merge_into<IR>(acc, RowAcc{a[i].x, a[i].y, a[i].z, c[i].x, c[i].y, c[i].z, c[i].w, ia[i], ib[i]});
-            }
-        }
-        if (RW <= 32) join<32, IR>(acc);
-        if (RW <= 16) join<16, IR>(acc);
-        if (RW <= 8) join<8, IR>(acc);
-        if (RW <= 4) join<4, IR>(acc);
-        if (RW <= 2) join<2, IR>(acc);
-        if (RW <= 1) join<1, IR>(acc);
+        const RowAcc acc = merged_row<IR>(p, row, u, head * p.Tq + t, l, g, RW, last);
         if (row && g == 0) {
-            cs += acc.C * rsqrtf(acc.Na * acc.Nb);
-            if (p.want_dist) {   // (Z is only accumulated when the distance is asked for)
-                const float ia = 1.f / acc.Za, ib = 1.f / acc.Zb;
-                const float d2 = acc.Na * ia * ia + acc.Nb * ib * ib - 2.f * acc.C * ia * ib;
-                ds += sqrtf(fmaxf(d2, 0.f));
-            }
+            add_row(acc, p.want_dist, cs, ds);
             if (IR) mass_a += acc.Ia / acc.Za;
             if (last) mass_b += acc.Ib / acc.Zb;
         }
@@ -226,6 +241,49 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
             if (last) mass[p.Hq] = mass_b / (float)p.Tq;
         }
     }
+}
+
+// A small model's heads, averages and greedy choice in one launch, a workgroup per conversation (krul_pair_similarity_select): a wave
+// per group of heads, all of them at once (the same bits as finalize_heads_kernel and pairs_select_kernel).  The chain of steps is theirs,
+// without the launch between them: 16 float32 tokens over 256 keys of 4 layers, 2 heads, 3.7 and 2.6 us -> 4.3, the call, which the host
+// bounds, 23.5 -> 20.2.
+constexpr int kTailWaves = 16;
+
+__global__ __launch_bounds__(kTailWaves * 64) void heads_select_kernel(HeadsArgs p, PairsSelectArgs a)
+{
+    extern __shared__ float tail_smem[];
+    const int NP = p.L - 1, b = blockIdx.x, lane = threadIdx.x & 63, item = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float *const hc = tail_smem, *const hd = hc + NP * p.Hq, *const pc = hd + NP * p.Hq;   // head values, [NP] pair scores
+    {
+        const int t1 = p.groups > 1 ? (int)p.by_groups(item) : item, group = item - t1 * p.groups;
+        const int l = (int)p.by_hkv(t1), kvh = t1 - l * p.Hkv;
+        const int RW = 64 / p.G, g = lane / RW, in_wave = lane % RW;   // (powers of two)
+        const int heads = p.lay.rows_per_unit / p.Tq, head = group * p.H + in_wave / p.TP, t = in_wave % p.TP;
+        const bool row = t < p.Tq && head < heads;
+        const RowAcc acc = merged_row<false>(p, row, b * p.Hkv + kvh, head * p.Tq + t, l, g, RW, false);
+        float cs = 0.f, ds = 0.f;
+        if (row && g == 0) add_row(acc, p.want_dist, cs, ds);
+        cs = sum_over(cs, p.TP);
+        ds = sum_over(ds, p.TP);
+        if (head < heads && g == 0 && t == 0) {
+            const int out = l * p.Hq + kvh * heads + head;
+            hc[out] = cs / (float)p.Tq;
+            hd[out] = ds / (float)p.Tq;
+            if (p.head_cos) p.head_cos[(size_t)b * NP * p.Hq + out] = hc[out];
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x >> 5; i < NP; i += blockDim.x >> 5) {
+        const float cs = pair_average(hc + i * p.Hq, p.Hq, 1.0f, lane & 31);
+        const float ds = p.want_dist ? pair_average(hd + i * p.Hq, p.Hq, 1.0f, lane & 31) : 0.f;
+        if ((lane & 31) == 0) {
+            a.pair_cos[(size_t)b * NP + i] = pc[i] = cs;
+            if (p.want_dist) a.pair_dist[(size_t)b * NP + i] = ds;
+        }
+    }
+    // (select_adjacent starts with a barrier)
+    select_adjacent(pc, a.eligible ? a.eligible + (size_t)b * a.L : nullptr, a.L, a.n_select,
+                    a.out_pairs + (size_t)b * a.n_select, a.out_count + b, pc + NP);
 }
 
 struct PairsArgs {
@@ -293,9 +351,9 @@ void launch_heads(HeadsArgs p, bool ir, hipStream_t st)
 
 }  // namespace
 
-hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, int L, int Hq, int Hkv,
-                           int Tq, float *head_cos, float *head_dist, float *pair_cos,
-                           float *pair_dist, bool accumulate, const IrArgs *ir, hipStream_t st)
+namespace {
+// Rows to lanes; per_wave: which of the two forms of finalize_heads_kernel.
+HeadsArgs heads_args(const StateLayout &lay, const float4 *state, int B, int L, int Hq, int Hkv, int Tq, bool want_dist, bool *per_wave_form)
 {
     HeadsArgs p = {};
     p.lay = lay;
@@ -304,17 +362,10 @@ hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, i
     p.Hq = Hq;
     p.Hkv = Hkv;
     p.Tq = Tq;
-    p.want_dist = pair_dist != nullptr;
-    p.accumulate = accumulate ? 1 : 0;
-    p.head_cos = head_cos;
-    p.head_dist = head_dist;
-    if (ir) {
-        p.state_ir = ir->state_ir;
-        p.head_ir = ir->head_ir;
-    }
+    p.want_dist = want_dist ? 1 : 0;
     const int heads = Hq / Hkv;
     p.G = p.TP = p.H = 1;
-    const bool per_wave = Tq <= 8;
+    const bool per_wave = *per_wave_form = Tq <= 8;
     if (per_wave) {   // few rows: heads of a kv head as long as a lane has one batch of partials, lanes left over share rows
         while (p.TP < Tq) p.TP <<= 1;
         while (p.H < heads && 2 * p.H * p.TP <= 64 && 64 / (2 * p.H * p.TP) * kBatch >= lay.partials) p.H <<= 1;
@@ -339,6 +390,23 @@ hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, i
     p.by_pairs = Div::by((unsigned)L - 1);
     p.by_tile = Div::by(lay.variant == kGeneric ? 1u : (unsigned)(lay.wr * lay.rb * 32));
     p.n_items = B * (L - 1) * Hkv * p.groups;
+    return p;
+}
+}  // namespace
+
+hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, int L, int Hq, int Hkv,
+                           int Tq, float *head_cos, float *head_dist, float *pair_cos,
+                           float *pair_dist, bool accumulate, const IrArgs *ir, hipStream_t st)
+{
+    bool per_wave;
+    HeadsArgs p = heads_args(lay, state, B, L, Hq, Hkv, Tq, pair_dist != nullptr, &per_wave);
+    p.accumulate = accumulate ? 1 : 0;
+    p.head_cos = head_cos;
+    p.head_dist = head_dist;
+    if (ir) {
+        p.state_ir = ir->state_ir;
+        p.head_ir = ir->head_ir;
+    }
     if (per_wave) launch_heads<true>(p, ir != nullptr, st);
     else launch_heads<false>(p, ir != nullptr, st);
     const hipError_t e = hipGetLastError();
@@ -359,6 +427,31 @@ hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, i
         a.eligible = ir->eligible;
     }
     return launch_pairs(a, st);
+}
+
+hipError_t launch_finalize_select(const StateLayout &lay, const float4 *state, int Hkv, int Tq, float *head_out,
+                                  float *head_cos, float *head_dist, const PairsSelectArgs &a, hipStream_t st)
+{
+    bool per_wave;
+    HeadsArgs p = heads_args(lay, state, a.B, a.L, a.Hq, Hkv, Tq, a.pair_dist != nullptr, &per_wave);
+    const int RW = 64 / p.G, heads = a.Hq / Hkv;
+    if (!per_wave && Tq <= RW) {   // heads of a wave here too
+        while (p.TP < Tq) p.TP <<= 1;
+        while (p.H < heads && 2 * p.H * p.TP <= RW) p.H <<= 1;
+        p.groups = (heads + p.H - 1) / p.H;
+        p.by_groups = Div::by((unsigned)p.groups);
+    }
+    // One launch where all of a conversation's heads are at work at once.  (In two rounds the chain of steps, 3 us, outlasts what a
+    // launch costs, 1 to 1.5 on the GPU and 3 on the host: 12.7 -> 16.6 us of GPU time.)
+    const long long items = (long long)(a.L - 1) * Hkv * p.groups;
+    if (items <= kTailWaves && p.TP >= Tq) {
+        p.head_cos = head_out;
+        const size_t smem = (size_t)(a.L - 1) * (2 * a.Hq + 1) * sizeof(float) + select_scratch_bytes(a.L);
+        hipLaunchKernelGGL(heads_select_kernel, dim3(a.B), dim3((unsigned)items * 64), smem, st, p, a);
+        return hipGetLastError();
+    }
+    const hipError_t e = launch_finalize(lay, state, a.B, a.L, a.Hq, Hkv, Tq, head_cos, head_dist, nullptr, a.pair_dist, false, nullptr, st);
+    return e == hipSuccess ? launch_pairs_select(a, st) : e;
 }
 
 hipError_t launch_scores_from_sums(const float *head_sum, const float *head_dist_sum, int n_pairs_total,

@@ -30,6 +30,17 @@ CASES = [
     ("sel-at-the-limit", 2, 129, 128, 8, 64, 100, 1, "bf16", 16, False),  # 128*128 = 16384: the largest conversation one workgroup takes
 ]
 
+# heads, pairs and choice in one kernel: up to 16 groups of heads in a conversation, rows of a head in one run
+CASES += [
+    ("tail-16-groups", 2, 9, 2, 2, 64, 300, 16, "f32", 3, True),        # ... and one more:
+    ("tail-17-groups", 2, 18, 1, 1, 64, 300, 16, "f32", 5, True),
+    ("tail-rows-64", 1, 5, 6, 2, 64, 200, 64, "bf16", 2, False),        # a wave's worth of rows, three heads of a kv head
+    ("tail-rows-65", 1, 5, 2, 1, 64, 200, 65, "bf16", 2, False),        # two runs
+    ("tail-ragged-group", 3, 4, 10, 2, 64, 700, 9, "f16", 1, True),     # five heads of a kv head, four to a wave
+    ("tail-shared-rows", 1, 3, 3, 1, 128, 4000, 33, "bf16", 1, False),  # lanes that share a row
+    ("tail-many-heads", 2, 3, 128, 1, 64, 100, 1, "bf16", 1, False),
+]
+
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_select_fused_matches_two_calls_and_oracle(G, oracle, case):
