@@ -411,25 +411,34 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
         n_wg = n_splits_all * ch.n_chunks;
         records = n_splits_all * L * f.rows();
     } else if (!generic) {
-        // float32 inputs and larger heads: tiles of 32 or 64 rows x 128 keys
+        // float32 inputs and larger heads: tiles of 32 or 64 rows x 128 keys, two workgroups a CU, or of 96 rows x 256 keys, one
         y.variant = kF32;
         y.wr = y.wk = y.rb = 1;
-        const long long tiles = ceil_div(S, 128), ks = ceil_div(s->head_dim, 16);
+        const long long ks = ceil_div(s->head_dim, 16);
         const int rb_most = Rk > 32 && s->head_dim <= 128 ? 2 : 1;
         const long long limit = in_static ? static_limit(s) : record_limit(s, B * Hkv * ceil_div(Rk, 32 * rb_most) * 32 * rb_most);
         long long best_ns = 1, best_nl = 1, best_bytes = 0;
         double best_t = 0.0;
-        for (int rb = 1; rb <= rb_most; ++rb) {
-            const long long nrt = ceil_div(Rk, 32 * rb), units = B * Hkv * nrt;
+        // 96-row tiles, which split the keys once for 96 rows: for heads above 64 (below, within 5 % either way but for one call of 60) and more
+        // rows than one of the others has, on memory that the others' plan takes too.  Their step is entered longer than it was best
+        // fitted (7.0), so that a close call stays with the others: 24 tokens over 1021 keys 78.5 -> 67.3 us; of 50 drawn calls of 65 to
+        // 1024 rows three 1.25 to 1.33 times as fast, one (159 rows over 227 keys) 216 -> 230, the rest within 6 %.  Short calls are not asked:
+        // the candidates take the host 1 us, and such calls wait for it.
+        for (int rb = 1; rb <= rb_most || (rb == 3 && Rk > 64 && s->head_dim > 64 && s->head_dim <= 128 && best_t >= 40.0); ++rb) {
+            const long long nrt = ceil_div(Rk, 32 * rb), units = B * Hkv * nrt, tiles = ceil_div(S, rb == 3 ? 256 : 128);
+            const long long resident = rb == 3 ? 1 : 2;
             // us per step for one workgroup a CU and for two, measured at head_dim 128
-            const double step1 = rb == 1 ? 2.2 : 3.2, step2 = (rb == 1 ? 2.9 : 4.4) * (0.3 + 0.7 * (double)ks / 8.0);
+            const double step1 = rb == 1 ? 2.2 : rb == 2 ? 3.2 : 7.8;
+            const double step2 = rb == 3 ? 7.8 * (0.5 + 0.5 * (double)ks / 8.0) : (rb == 1 ? 2.9 : 4.4) * (0.3 + 0.7 * (double)ks / 8.0);
+            const long long cap = rb == 3 ? best_bytes : INT64_MAX;
             const auto consider = [&](long long ns, long long nl) {
                 const long long tps = ceil_div(tiles, ns);
                 if ((s->flags & KRUL_FLAG_SINGLE_SPLIT) && ns > 1) return;
                 const double n = (double)(units * ceil_div(tiles, tps) * nl), steps = (double)(tps * (ceil_div(L - 1, nl) + 1));
                 const long long bytes = units * ceil_div(tiles, tps) * L * 32 * rb * 16;
-                const double t = (n <= kCUs ? steps * fmin(step1, step2) + 4.0 : ceil(n / (2 * kCUs)) * (steps * step2 + 4.0)) +
+                const double t = (n <= kCUs ? steps * fmin(step1, step2) + 4.0 : ceil(n / (double)(resident * kCUs)) * (steps * step2 + 4.0)) +
                                  record_time(bytes, false);
+                if (bytes > cap) return;
                 if (best_t == 0.0 || (bytes <= limit ? best_bytes > limit || t < best_t : best_bytes > limit && bytes < best_bytes)) {   // (as in choose_mfma)
                     y.rb = rb;
                     best_ns = ceil_div(tiles, tps);
@@ -440,7 +449,7 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
             };
             for (long long nl = 1; nl <= L - 1 && nl <= 31; ++nl) {   // (more, with 80 layers: 5 tokens over 300 keys 48.0 -> 49.5 us, one over 1000 78.5 -> 79.4)
                 for (int r = 1; r <= 3; ++r) {   // a round of workgroups, two or three; one tile per split
-                    const long long ns = 2 * kCUs * r / (units * nl);
+                    const long long ns = resident * kCUs * r / (units * nl);
                     if (ns >= 1 && ns < tiles) consider(ns, nl);
                 }
                 consider(1, nl);
@@ -452,7 +461,8 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
         y.n_row_tiles = (int)ceil_div(Rk, 32 * y.rb);
         y.n_split = y.partials = (int)best_ns;
         y.n_layer_chunks = (int)best_nl;
-        pl->keys_per_split = (int)(ceil_div(tiles, best_ns) * 128);
+        const long long kt = y.rb == 3 ? 256 : 128;
+        pl->keys_per_split = (int)(ceil_div(ceil_div(S, kt), best_ns) * kt);
         n_wg = units * best_ns;
         records = n_wg * L * 32 * y.rb;
         n_wg *= best_nl;

@@ -13,18 +13,20 @@
 // What bounds it.  32 keys x 32 rows at head_dim 128 are 48 MFMAs of 32 cycles; splitting the keys takes 352 vector
 // instructions per 32 keys of a wave, the exponentials, the share in the query rows' split and the sums some 250 per
 // row block, in part beside the MFMAs.  So the vector units are the bound, and with more than 32 rows a wave takes two
-// row blocks on one split of the keys.
+// row blocks on one split of the keys, with more than 64 three in workgroups of eight waves (one to a CU: 24 query tokens over 1021 keys, 96
+// rows, this kernel 73 -> 55 us; without its MFMAs 76 -> 78 a call, without the exponentials and merges -8 us, without loads of keys -8, without
+// the keys' split -5, without the query rows' -5).
 //
-// A workgroup of four waves owns 32 * RB query rows of a unit (conversation, kv head), a key split and a chunk of
-// layers.  It walks the split in tiles of 128 keys (32 per wave) and, inside a tile, the layers of the chunk in order,
+// A workgroup of four (eight) waves owns 32 * RB query rows of a unit (conversation, kv head), a key split and a chunk of
+// layers.  It walks the split in tiles of 128 (256) keys (32 per wave) and, inside a tile, the layers of the chunk in order,
 // so that the previous layer's exponentials are in registers when the cross term is taken (as in sim_mfma_kernel).
 // Keys go from memory to the registers of the one wave that uses them, a layer ahead; query rows are split once per
 // workgroup and handed round in LDS.  In the MFMA result a lane owns one query row and 16 keys; the row's eight
-// partials (two half-waves, four waves) and its running record over the tiles before (its row record, stored after
-// every tile) are merged one step late, every wave taking eight rows of a block.
+// partials (two half-waves of each wave) and its running record over the tiles before (its row record, stored after
+// every tile) are merged one step late, every wave taking a share of a block's rows.
 //
-// Measured (one conversation, 32 layers, 32 query / 8 kv heads of 128, the whole call): 24 query tokens over 1021 keys 3080 -> 85 us
-// (this kernel 77), 64 over 4096 31400 -> 499 us, against one wave per query row on the vector units, every row fetching the keys
+// Measured (one conversation, 32 layers, 32 query / 8 kv heads of 128, the whole call): 24 query tokens over 1021 keys 3080 -> 67 us
+// (this kernel 55), 64 over 4096 31400 -> 499 us, against one wave per query row on the vector units, every row fetching the keys
 // anew (float32 MFMAs in this kernel's place: 115 and 740 us).  Errors against a float64 evaluation, geometric means over 12 calls drawn
 // over the float32 sizes: cosines 4.1e-8, distances 4.7e-8 of themselves (the vector units' float32 products: 5.6e-8 and 6.3e-8).
 #include "krul_common.h"
@@ -39,7 +41,6 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
-constexpr int kWaves = 4, kThreads = kWaves * 64, kTileKeys = kWaves * 32;
 
 // Eight consecutive elements as they lie in memory, and as MFMA operands: three bfloat16 planes, or the 16-bit
 // elements themselves.
@@ -103,12 +104,14 @@ __device__ inline void lds_barrier()
     asm volatile("" ::: "memory");
 }
 
-// Over the eight lanes that share lane % 8, by vector instructions (shuffles go through LDS and take ten times as long):
-// op applied as a butterfly over 8, 16 and 32, the same in each of them.
-template <class Op>
-__device__ inline float over_eighths(float v, Op op)
+// Over the P = 8 or 16 lanes that share lane % (64 / P), by vector instructions (shuffles go through LDS and take ten times as long):
+// op applied as a butterfly over (4,) 8, 16 and 32, the same in each of them.
+template <int P, class Op>
+__device__ inline float over_partials(float v, Op op)
 {
+    static_assert(P == 8 || P == 16, "partials of a row");
     v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x128, 0xF, 0xF, true)));   // row_ror 8
+    if constexpr (P == 16) v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x124, 0xF, 0xF, true)));   // row_ror 4
     const unsigned u = __float_as_uint(v);
     const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
     v = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
@@ -116,17 +119,22 @@ __device__ inline float over_eighths(float v, Op op)
     const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
     return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
-__device__ inline float eighths_max(float v) { return over_eighths(v, [](float a, float b) { return fmaxf(a, b); }); }
-__device__ inline float eighths_sum(float v) { return over_eighths(v, [](float a, float b) { return a + b; }); }
+template <int P> __device__ inline float partials_max(float v) { return over_partials<P>(v, [](float a, float b) { return fmaxf(a, b); }); }
+template <int P> __device__ inline float partials_sum(float v) { return over_partials<P>(v, [](float a, float b) { return a + b; }); }
 
 constexpr int q_pitch(int ks) { return ks * 32 + 16; }   // bytes of a query row's plane in LDS: 16 rows' 16-byte reads fall into different banks
 
 // KS: MFMA steps of 16 elements that cover the head (head_dim up to 16 * KS; what is past it counts as zero); RB: 32-row blocks per wave; IR: the
-// Initial-Recent test too.
+// Initial-Recent test too.  Three row blocks take eight waves.
 template <typename T, int KS, int RB, bool IR>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 16 && Elem8<T>::kPlanes == 3 ? 1 : 2, 2))) void sim_f32_kernel(SimParams p)
+__global__ __launch_bounds__(RB == 3 ? 512 : 256) __attribute__((amdgpu_waves_per_eu(KS == 16 && Elem8<T>::kPlanes == 3 ? 1 : 2, 2))) void sim_f32_kernel(SimParams p)
 {
-    constexpr int PL = Elem8<T>::kPlanes, R_WG = 32 * RB, PITCH = q_pitch(KS), QG = (KS + 3) / 4;   // QG: groups of 8 elements that a thread stages per row
+    constexpr int PL = Elem8<T>::kPlanes, R_WG = 32 * RB, PITCH = q_pitch(KS);
+    constexpr int kWaves = RB == 3 ? 8 : 4, kThreads = kWaves * 64, kTileKeys = kWaves * 32;
+    constexpr int TPR = kThreads / 32, QG = (2 * KS + TPR - 1) / TPR;   // threads that stage a query row, and groups of 8 elements for each
+    constexpr int P = 2 * kWaves, RPM = 64 / P;                         // partials of a row; rows of a block that a wave merges
+    // keys in registers, ahead: a layer's, or half (three row blocks leave no more)
+    constexpr int KR = RB == 3 ? KS / 2 : KS;
     typedef __attribute__((address_space(1))) f32x4 *global_f32x4;
     typedef __attribute__((address_space(1))) float *global_f32;
     typedef __attribute__((address_space(3))) f32x4 *lds_f32x4;
@@ -182,10 +190,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
     // is zeroed or masked where it is used -- so that the compiler can count them: a wait for the keys of this step
     // then leaves the loads behind them in flight.
 
-    // ---- query rows of a layer: thread (row tid / 8, groups tid % 8, + 8, ...) -> registers -> split -> LDS.  (Rows
+    // ---- query rows of a layer: thread (row tid / TPR, groups tid % TPR, + TPR, ...) -> registers -> split -> LDS.  (Rows
     // past the last are copies of it; their results are never read.  Elements past the head size are zeros, written
     // once below, so that whatever the keys have there does not count.)
-    const int qrow = tid >> 3, qc = tid & 7;
+    const int qrow = tid / TPR, qc = tid % TPR;
     const T *Q[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
@@ -197,20 +205,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-            for (int i = 0; i < QG; ++i) load8(qs[rb][i], (uintptr_t)(Q[rb] + (size_t)l * q_layer + (i < DMIN / 64 ? (qc + 8 * i) * 8 : min((qc + 8 * i) * 8, d - 8))));
+            for (int i = 0; i < QG; ++i) load8(qs[rb][i], (uintptr_t)(Q[rb] + (size_t)l * q_layer + ((i + 1) * TPR * 8 <= DMIN ? (qc + TPR * i) * 8 : min((qc + TPR * i) * 8, d - 8))));
     };
     auto store_q = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int i = 0; i < QG; ++i) {
-                if (i >= DMIN / 64 && (qc + 8 * i) * 8 >= d) continue;
+                if ((i + 1) * TPR * 8 > DMIN && (qc + TPR * i) * 8 >= d) continue;
                 u32x4 o[PL];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) qs[rb][i].split_pair(e, o);
 #pragma unroll
                 for (int pl = 0; pl < PL; ++pl)
-                    *reinterpret_cast<u32x4 *>(qlds + ((rb * PL + pl) * 32 + qrow) * PITCH + (qc + 8 * i) * 16) = o[pl];
+                    *reinterpret_cast<u32x4 *>(qlds + ((rb * PL + pl) * 32 + qrow) * PITCH + (qc + TPR * i) * 16) = o[pl];
             }
     };
 
@@ -231,11 +239,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
                                         : (uintptr_t)(static_cast<const T *>(p.k) + (size_t)(l_first + l) * p.k_stride_l);
         return layer + koff * sizeof(T);
     };
-    Elem8<T> kr[KS];
+    Elem8<T> kr[KR];
     auto load_k = [&](uintptr_t key, int ks) __attribute__((always_inline)) {
         // (key: the lane's half is in it already where no clamp to the head size is needed)
-        if (ks * 16 + 16 <= DMIN) load8(kr[ks], key + ks * 16 * sizeof(T));
-        else load8(kr[ks], key + (size_t)(min(ks * 16 + half * 8, d - 8) - half * 8) * sizeof(T));
+        if (ks * 16 + 16 <= DMIN) load8(kr[ks % KR], key + ks * 16 * sizeof(T));
+        else load8(kr[ks % KR], key + (size_t)(min(ks * 16 + half * 8, d - 8) - half * 8) * sizeof(T));
     };
 
     float ep[RB][16];   // the previous layer's exponentials of this lane's keys
@@ -244,8 +252,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
 #pragma unroll
         for (int v = 0; v < 16; ++v) ep[rb][v] = 0.f;
 
-    // ---- merge of the rows' partials, one step late: wave w takes rows 8w .. 8w + 7 of a block, lane (i, r) partial i
-    // of row 8w + r; the eight partials are joined by a butterfly.  f_prev took this lane's partial onto the merged
+    // ---- merge of the rows' partials, one step late: wave w takes RPM rows of a block from RPM * w on, lane (i, r) partial i
+    // of row RPM * w + r; the P partials are joined by a butterfly.  f_prev took this lane's partial onto the merged
     // exponent of the previous layer, f_run the row's running record over the tiles before.
     float f_prev[RB], f_run[RB];
 #pragma unroll
@@ -254,9 +262,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
         const bool foreign = l == 0 && l_first > 0;   // the layer's records belong to the chunk before
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const int mrow = wave * 8 + (lane & 7), pw = lane >> 4, pl = ((lane >> 3) & 1) * 32 + mrow;
+            const int mrow = wave * RPM + lane % RPM, pw = lane / RPM >> 1, pl = (lane / RPM & 1) * 32 + mrow;
             const f32x4 v = part[rb][pw][pl];
-            float M = eighths_max(v.x);
+            float M = partials_max<P>(v.x);
             const int rrow = rb * 32 + mrow;
             const size_t rec = rec0 + (size_t)l * R_WG + rrow;
             // (pointers that say which memory they lead to: chosen between at run time they would be generic, and a
@@ -274,13 +282,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
                 M = fmaxf(M, rr.x);
             }
             const float f = __builtin_amdgcn_exp2f(v.x - M), fr = __builtin_amdgcn_exp2f(rr.x - M);
-            const float zs = eighths_sum(v.y * f), ns = eighths_sum(v.z * (f * f)), cc = eighths_sum(v.w * (f * f_prev[rb]));
-            float zi = IR ? eighths_sum(part_ir[rb][pw][pl] * f) : 0.f;
+            const float zs = partials_sum<P>(v.y * f), ns = partials_sum<P>(v.z * (f * f)), cc = partials_sum<P>(v.w * (f * f_prev[rb]));
+            float zi = IR ? partials_sum<P>(part_ir[rb][pw][pl] * f) : 0.f;
             const f32x4 out = {M, fmaf(rr.y, fr, zs), fmaf(rr.z, fr * fr, ns), fmaf(rr.w, fr * f_run[rb], cc)};
             if (IR) zi = fmaf(ri, fr, zi);
             f_prev[rb] = f;
             f_run[rb] = fr;
-            if (lane < 8) {
+            if (lane < RPM) {
                 if (foreign) {
                     *(lds_f32x4)(run0 + rrow) = out;
                     if (IR) *(lds_f32)(run0_ir + rrow) = zi;
@@ -298,11 +306,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
     }
     load_q(0);
     find_key(0);
-    {
-        const uintptr_t key = key_ptr(0);
+    uintptr_t key = key_ptr(0);   // of the layer at hand, and of the next
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) load_k(key, ks);
-    }
+    for (int ks = 0; ks < KR; ++ks) load_k(key, ks);
     store_q();
 
     const float c = p.c;
@@ -316,7 +322,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
         if (step > 0) merge(l_before, tile_before);
         const int key0 = key_begin + tile * kTileKeys + wave * 32;
         if (tn != tile) find_key(tn);
-        const uintptr_t key = key_ptr(ln);
+        const uintptr_t key_now = key;
+        key = key_ptr(ln);
+        // the keys KR steps after step ks, this layer's or the next one's, take the registers' place
+        auto load_after = [&](int ks) __attribute__((always_inline)) { load_k(ks + KR < KS ? key_now : key, (ks + KR) % KS); };
 
         // ---- logits
         f32x16 acc[RB], low;   // (with two row blocks their chains run side by side, and there are no registers for a second pair)
@@ -330,38 +339,55 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KS == 
         u32x4 ko[2][PL];   // the keys' operands of MFMA step ks, and of ks + 1
 #pragma unroll
         for (int e = 0; e < 4; ++e) kr[0].split_pair(e, ko[0]);
-        load_k(key, 0);   // the next step's keys take the registers' place
+        load_after(0);
         asm volatile("" ::: "memory");   // (now: the compiler would put these loads, of no use before the next step, last)
+        // Three row blocks: the query rows' operands of a step are read a plane at a time, for the next step, as soon as the plane's last product is on
+        // its way, so that no product waits for LDS and no further registers are taken.  (One block or two, with a second workgroup on
+        // the CU: all planes before the step; a plane at a time 63 tokens over 1150 keys took 188 us, 181 so.)
+        constexpr bool AHEAD = RB == 3;
+        u32x4 qo[RB][PL];
+        auto read_plane = [&](int pl, int ks) __attribute__((always_inline)) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) qo[rb][pl] = *reinterpret_cast<const u32x4 *>(qr + (rb * PL + pl) * 32 * PITCH + ks * 32);
+        };
+        if constexpr (AHEAD) read_plane(1, 0), read_plane(2, 0), read_plane(0, 0);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            u32x4 qo[RB][PL];
+            if constexpr (!AHEAD) {
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
+                for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                for (int pl = 0; pl < PL; ++pl)
-                    qo[rb][pl] = *reinterpret_cast<const u32x4 *>(qr + (rb * PL + pl) * 32 * PITCH + ks * 32);
+                    for (int pl = 0; pl < PL; ++pl)
+                        qo[rb][pl] = *reinterpret_cast<const u32x4 *>(qr + (rb * PL + pl) * 32 * PITCH + ks * 32);
+            }
             const auto &kc = ko[ks & 1];
             auto &kn = ko[(ks + 1) & 1];
             // The six products in turn -- the chains of two row blocks, or of the large and the small terms, side by
             // side -- and between them, pinned by the empty statements, the split of the next step's keys two elements
             // at a time: matrix and vector units then work at once.
-            constexpr int kTerms[6][2] = {{1, 1}, {0, 2}, {0, 0}, {2, 0}, {0, 1}, {1, 0}};
+            constexpr int kTerms[2][6][2] = {{{1, 1}, {0, 2}, {0, 0}, {2, 0}, {0, 1}, {1, 0}}, {{1, 1}, {0, 1}, {0, 2}, {2, 0}, {1, 0}, {0, 0}}};   // (planes of the keys, of the query rows)
 #pragma unroll
             for (int t = 0; t < (PL == 3 ? 6 : 1); ++t) {
                 if (ks + 1 < KS && t < 4) {
 #pragma unroll
                     for (int e = (PL == 3 ? t : 0); e < (PL == 3 ? t + 1 : 4); ++e) {
-                        kr[ks + 1 < KS ? ks + 1 : 0].split_pair(e, kn);
+                        kr[(ks + 1) % KR].split_pair(e, kn);
                         if constexpr (PL == 3) asm volatile("" : "+v"(kn[0][e]), "+v"(kn[1][e]), "+v"(kn[2][e]));
                     }
-                    if (t == 3 || PL == 1) load_k(key, ks + 1);
+                    if (t == 3 || PL == 1) load_after(ks + 1);
                 }
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
-                    const int ka = PL == 3 ? kTerms[t][0] : 0, qa = PL == 3 ? kTerms[t][1] : 0;
+                    const int ka = PL == 3 ? kTerms[AHEAD][t][0] : 0, qa = PL == 3 ? kTerms[AHEAD][t][1] : 0;
                     f32x16 &to = PL == 3 && RB == 1 && t != 2 ? low : acc[rb];
                     to = mfma8<T>(kc[ka], qo[rb][qa], to);
                     asm volatile("" : "+v"(to));
+                }
+                if (AHEAD && ks + 1 < KS) {
+                    asm volatile("" ::: "memory");
+                    if (t == 1) read_plane(1, ks + 1);
+                    if (t == 2) read_plane(2, ks + 1);
+                    if (t == 5) read_plane(0, ks + 1);
                 }
             }
             asm volatile("" ::: "memory");
@@ -415,9 +441,9 @@ template <typename T, int KS, int RB>
 hipError_t launch(const SimParams &p, int n_workgroups, hipStream_t st)
 {
     if (p.want_ir)
-        hipLaunchKernelGGL((sim_f32_kernel<T, KS, RB, true>), dim3(n_workgroups), dim3(kThreads), 0, st, p);
+        hipLaunchKernelGGL((sim_f32_kernel<T, KS, RB, true>), dim3(n_workgroups), dim3(RB == 3 ? 512 : 256), 0, st, p);
     else
-        hipLaunchKernelGGL((sim_f32_kernel<T, KS, RB, false>), dim3(n_workgroups), dim3(kThreads), 0, st, p);
+        hipLaunchKernelGGL((sim_f32_kernel<T, KS, RB, false>), dim3(n_workgroups), dim3(RB == 3 ? 512 : 256), 0, st, p);
     return hipGetLastError();
 }
 
@@ -426,7 +452,8 @@ hipError_t launch_rows(const SimParams &p, int n_workgroups, hipStream_t st)
 {
     if (p.d > 96) return launch<float, 8, RB>(p, n_workgroups, st);
     if (p.d > 64) return launch<float, 6, RB>(p, n_workgroups, st);
-    return launch<float, 4, RB>(p, n_workgroups, st);
+    if constexpr (RB < 3) return launch<float, 4, RB>(p, n_workgroups, st);
+    return hipErrorInvalidValue;   // (three row blocks: heads above 64)
 }
 
 }  // namespace
@@ -437,7 +464,7 @@ hipError_t launch_sim_f32(const SimParams &p, int dtype, int n_workgroups, hipSt
     if (dtype == KRUL_F16) return launch<_Float16, 16, 1>(p, n_workgroups, st);
     if (p.d > 192) return launch<float, 16, 1>(p, n_workgroups, st);
     if (p.d > 128) return launch<float, 12, 1>(p, n_workgroups, st);
-    return p.lay.rb == 2 ? launch_rows<2>(p, n_workgroups, st) : launch_rows<1>(p, n_workgroups, st);
+    return p.lay.rb == 3 ? launch_rows<3>(p, n_workgroups, st) : p.lay.rb == 2 ? launch_rows<2>(p, n_workgroups, st) : launch_rows<1>(p, n_workgroups, st);
 }
 
 }  // namespace krul

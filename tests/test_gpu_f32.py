@@ -21,6 +21,11 @@ CASES = [
     ("d128-rows200", 1, 9, 8, 2, 128, 1500, 50, "f32"),
     ("d136", 1, 3, 4, 2, 136, 520, 9, "f32"),
     ("d256", 1, 3, 4, 2, 256, 300, 7, "f32"),
+    # three row blocks on eight waves, 256-key tiles: the least rows and the most of one tile, two tiles, keys of one tile, a ragged second one
+    ("three-blocks-rows65", 8, 17, 32, 32, 96, 200, 65, "f32"),
+    ("three-blocks-rows80", 16, 16, 16, 4, 128, 511, 20, "f32"),
+    ("three-blocks-rows96", 1, 32, 32, 8, 128, 1021, 24, "f32"),
+    ("three-blocks-rows186", 1, 9, 32, 32, 128, 300, 186, "f32"),
     ("bf16-d136", 1, 4, 4, 2, 136, 300, 20, "bf16"),
     ("f16-d256", 1, 3, 4, 2, 256, 200, 40, "f16"),
 ]
