@@ -54,6 +54,11 @@ IR_CASES = [
     ("ir-slim", 1, 5, 4, 1, 128, 2500, 3),       # 250 and 2250: several tiles
     ("ir-short", 1, 3, 4, 2, 128, 9, 40),        # floor(0.9) = 0 initial keys, recent = key 8 only
     ("ir-one-key", 1, 2, 2, 2, 64, 1, 2),        # S = 1: the one key is recent, mass 1
+    # tiles of which all keys, none or some are initial or recent
+    ("ir-between-tiles", 1, 3, 4, 1, 128, 2560, 40),   # boundaries at 256 and 2304: ends of 256-key tiles
+    ("ir-a-key-over", 1, 3, 4, 1, 96, 2570, 40),       # 257 and 2313: a key of the second tile, nine of the last but one
+    ("ir-between-blocks", 2, 3, 8, 2, 128, 1600, 20),  # 160 and 1440: ends of 32-key blocks inside tiles
+    ("ir-both-in-one", 1, 4, 4, 1, 64, 200, 33),       # 20 and 180: both inside a tile
 ]
 
 
