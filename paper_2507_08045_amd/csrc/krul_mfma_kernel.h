@@ -550,8 +550,9 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
                 const unsigned char *nslot = slot_ptr((c + 1) % NC);
 
                 // (this branch and the one to a second pass are said to be rare: their code lies behind the loop, and a chunk runs on
-                // without a jump.  2 x 77 tokens over 5003 keys 429 -> 425 us, 64 over 4096 119.8 -> 118.6, 512 over 3575 767 -> 761)
-                if (__builtin_expect(ragged, 0)) {
+                // without a jump.  2 x 77 tokens over 5003 keys 429 -> 425 us, 64 over 4096 119.8 -> 118.6, 512 over 3575 767 -> 761.  Shapes of fewer wave
+                // rows wait for their keys, and in pages they lost by it: 8 decode steps over 4096 keys 367 -> 374.)
+                if (C::WR == 4 ? __builtin_expect(ragged, 0) : (long)ragged) {
                     // keys at or past key_end: element v of a lane is key kb0 + 8*(v/4) + v%4
 #pragma unroll
                     for (int kb = 0; kb < KBW; ++kb) {
@@ -618,7 +619,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
                     }
                     acc[(c + 1) & 1][kb] = nx;
                     asm volatile("" : "+v"(bz), "+v"(bn), "+v"(bd));   // the sums are taken here, beside the MFMAs
-                    if (__builtin_expect(__any(!(bn <= kBig)) != 0, 0)) {
+                    if (C::WR == 4 ? __builtin_expect(__any(!(bn <= kBig)) != 0, 0) : (long)(__any(!(bn <= kBig)) != 0)) {
                         float tmax = x[0];
 #pragma unroll
                         for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, x[v]);
