@@ -246,7 +246,7 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
 // A small model's heads, averages and greedy choice in one launch, a workgroup per conversation (krul_pair_similarity_select): a wave
 // per group of heads, all of them at once (the same bits as finalize_heads_kernel and pairs_select_kernel).  The chain of steps is theirs,
 // without the launch between them: 16 float32 tokens over 256 keys of 4 layers, 2 heads, 3.7 and 2.6 us -> 4.3, the call, which the host
-// bounds, 23.5 -> 20.2.
+// bounds, 22.3 -> 18.9.
 constexpr int kTailWaves = 16;
 
 __global__ __launch_bounds__(kTailWaves * 64) void heads_select_kernel(HeadsArgs p, PairsSelectArgs a)
