@@ -421,6 +421,20 @@ int krul_calibration_block(int32_t row_blocks, int32_t parts, int32_t iters, flo
  */
 int krul_pair_similarity_plan(const krul_shape_t *shape, int32_t *n_workgroups, int32_t *n_key_splits);
 
+/*
+ * Measurement aid, host-only: more of that plan, or (in_static not 0) of the one krul_pair_similarity_static takes (KRUL_ESCRATCH where
+ * there is none).
+ */
+typedef struct krul_plan {
+    int32_t form;            /* as krul_pair_similarity_plan numbers it                       */
+    int32_t rows_per_tile;   /* query rows of a workgroup (1: the portable kernel)            */
+    int32_t keys_per_split;  /* one key tile or several                                       */
+    int32_t n_key_splits;
+    int32_t n_layer_chunks;  /* pieces of the chain of layers that run side by side           */
+    int32_t n_workgroups;
+} krul_plan_t;
+int krul_pair_similarity_plan_of(const krul_shape_t *shape, int32_t in_static, krul_plan_t *plan);
+
 
 #ifdef __cplusplus
 }

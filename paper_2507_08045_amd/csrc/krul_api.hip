@@ -417,7 +417,7 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
         const long long ks = ceil_div(s->head_dim, 16);
         const int rb_most = Rk > 32 && s->head_dim <= 128 ? 2 : 1;
         const long long limit = in_static ? static_limit(s) : record_limit(s, B * Hkv * ceil_div(Rk, 32 * rb_most) * 32 * rb_most);
-        long long best_ns = 1, best_nl = 1, best_bytes = 0;
+        long long best_ns = 1, best_nl = 1, best_bytes = 0, others_bytes = 0;   // others_bytes: of the best plan without 96-row tiles
         double best_t = 0.0;
         // 96-row tiles, which split the keys once for 96 rows: for heads above 64 (below, within 5 % either way but for one call of 60) and more
         // rows than one of the others has, on memory that the others' plan takes too.  Their step is entered longer than it was best
@@ -430,7 +430,7 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
             // us per step for one workgroup a CU and for two, measured at head_dim 128
             const double step1 = rb == 1 ? 2.2 : rb == 2 ? 3.2 : 7.8;
             const double step2 = rb == 3 ? 7.8 * (0.5 + 0.5 * (double)ks / 8.0) : (rb == 1 ? 2.9 : 4.4) * (0.3 + 0.7 * (double)ks / 8.0);
-            const long long cap = rb == 3 ? best_bytes : INT64_MAX;
+            const long long cap = rb == 3 ? others_bytes : INT64_MAX;
             const auto consider = [&](long long ns, long long nl) {
                 const long long tps = ceil_div(tiles, ns);
                 if ((s->flags & KRUL_FLAG_SINGLE_SPLIT) && ns > 1) return;
@@ -456,11 +456,13 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
                 if (tiles <= 1024) consider(tiles, nl);
                 if (units * nl >= 6 * kCUs) break;
             }
+            if (rb < 3) others_bytes = best_bytes;
         }
         const long long units = B * Hkv * ceil_div(Rk, 32 * y.rb);
         y.n_row_tiles = (int)ceil_div(Rk, 32 * y.rb);
         y.n_split = y.partials = (int)best_ns;
         y.n_layer_chunks = (int)best_nl;
+        fallback_records = others_bytes / 16;
         const long long kt = y.rb == 3 ? 256 : 128;
         pl->keys_per_split = (int)(ceil_div(ceil_div(S, kt), best_ns) * kt);
         n_wg = units * best_ns;
@@ -471,6 +473,7 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
         generic = in_static && best_bytes > limit;
     }
     if (generic) {
+        fallback_records = 0;
         y.variant = kGeneric;
         y.wr = y.wk = y.rb = 1;
         y.n_row_tiles = 1;
@@ -684,14 +687,27 @@ int krul_calibration_copy(const void *src, void *dst, size_t bytes, void *stream
     return hipGetLastError() == hipSuccess ? KRUL_OK : KRUL_ELAUNCH;
 }
 
+int krul_pair_similarity_plan_of(const krul_shape_t *shape, int32_t in_static, krul_plan_t *plan)
+{
+    if (!plan) return KRUL_EINVAL;
+    Plan pl;
+    const int rc = make_plan(shape, &pl, false, true, in_static != 0);
+    if (rc != KRUL_OK) return rc;
+    if (in_static && pl.total_bytes > (size_t)KRUL_STATIC_SCRATCH_BYTES) return KRUL_ESCRATCH;
+    const StateLayout &y = pl.lay;
+    *plan = krul_plan_t{y.variant == kF32 ? 0 : y.variant, y.variant == kGeneric ? 1 : y.wr * y.rb * 32, pl.keys_per_split, y.n_split, y.n_layer_chunks,
+                        pl.n_workgroups};
+    return KRUL_OK;
+}
+
 int krul_pair_similarity_plan(const krul_shape_t *shape, int32_t *n_workgroups, int32_t *n_key_splits)
 {
-    Plan pl;
-    const int rc = make_plan(shape, &pl, false, true);
+    krul_plan_t pl;
+    const int rc = krul_pair_similarity_plan_of(shape, 0, &pl);
     if (rc != KRUL_OK) return rc;
     if (n_workgroups) *n_workgroups = pl.n_workgroups;
-    if (n_key_splits) *n_key_splits = pl.lay.n_split;
-    return pl.lay.variant == kF32 ? 0 : pl.lay.variant;
+    if (n_key_splits) *n_key_splits = pl.n_key_splits;
+    return pl.form;
 }
 
 size_t krul_pair_similarity_workspace(const krul_shape_t *shape)

@@ -66,7 +66,9 @@ struct Plan {
     // Workspace of the plan for callers whose memory does not hold this one: choose_short's, with rounds counted whole for the
     // stream of keys too.  Memory that holds either is taken, and the size query names the larger, so that memory sized for the
     // fallback serves a growing history although the fastest plans jump (8 x 172 tokens of 32/8 heads over 1024 to 32768 keys:
-    // 48 MB at every length, where the fastest take 48 to 504).
+    // 48 MB at every length, where the fastest take 48 to 504).  Float32: the plan without 96-row tiles, which take as much or less.  Named by the size
+    // query, it keeps what memory sized for one history serves of the shorter ones (named by its own size, 347 of 40000 random shorter calls
+    // were refused), and where it fits krul_pair_similarity_static's area both calls choose from the same plans.
     size_t fallback_bytes;
     // Initial-Recent layer test only: one float per record beside state, head means
     size_t state_ir_off, head_ir_off;
