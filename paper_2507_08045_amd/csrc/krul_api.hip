@@ -419,12 +419,14 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
         const long long limit = in_static ? static_limit(s) : record_limit(s, B * Hkv * ceil_div(Rk, 32 * rb_most) * 32 * rb_most);
         long long best_ns = 1, best_nl = 1, best_bytes = 0, others_bytes = 0;   // others_bytes: of the best plan without 96-row tiles
         double best_t = 0.0;
-        // 96-row tiles, which split the keys once for 96 rows: for heads above 64 (below, within 5 % either way but for one call of 60) and more
-        // rows than one of the others has, on memory that the others' plan takes too.  Their step is entered longer than it was best
-        // fitted (7.0), so that a close call stays with the others: 24 tokens over 1021 keys 78.5 -> 67.3 us; of 50 drawn calls of 65 to
-        // 1024 rows three 1.25 to 1.33 times as fast, one (159 rows over 227 keys) 216 -> 230, the rest within 6 %.  Short calls are not asked:
-        // the candidates take the host 1 us, and such calls wait for it.
-        for (int rb = 1; rb <= rb_most || (rb == 3 && Rk > 64 && s->head_dim > 64 && s->head_dim <= 128 && best_t >= 40.0); ++rb) {
+        // 96-row tiles, which split the keys once for 96 rows, stand in for 64-row ones only: a wave with one row block keeps the small terms of its products in a
+        // sum of their own, one with two or three has no registers for it (modelled over 128 unit-normal elements: 6.8e-7, 1.5e-6 and 1.4e-6
+        // root mean square of a logit).  For heads above 64 (below, within 5 % either way but for one call of 60), on memory that the others'
+        // plan takes too.  Their step is entered longer than it was best fitted (7.0), so that a close call stays with the others: 24
+        // tokens over 1021 keys 84 -> 68 us; 70 drawn calls that take them are 1.13 to 1.50 times as fast (65 to 96 rows most of them, 128 padded
+        // ones in the others), 110 that do not would be 0.59 to 1.17 times as fast in them.  Short calls are not asked: the
+        // candidates take the host 1 us, and such calls wait for it.
+        for (int rb = 1; rb <= rb_most || (rb == 3 && y.rb == 2 && Rk > 64 && s->head_dim > 64 && best_t >= 40.0); ++rb) {
             const long long nrt = ceil_div(Rk, 32 * rb), units = B * Hkv * nrt, tiles = ceil_div(S, rb == 3 ? 256 : 128);
             const long long resident = rb == 3 ? 1 : 2;
             // us per step for one workgroup a CU and for two, measured at head_dim 128

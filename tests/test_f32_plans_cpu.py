@@ -54,3 +54,11 @@ def test_memory_for_a_history_serves_a_shorter_one(model, longer, shorter):
     assert kr.plan(sh)["rows_per_tile"] == 96
     assert status(sh, kr.workspace_bytes(sh)) == kr.KRUL_EINVAL
     assert status(shape(B, L, Hq, Hkv, d, shorter, Tq), kr.workspace_bytes(sh)) == kr.KRUL_EINVAL
+
+
+# calls that 32-row tiles are estimated to be fastest for among 32 and 64 rows, and 96-row tiles faster still
+@pytest.mark.parametrize("size", [(1, 32, 32, 8, 128, 7260, 17), (4, 24, 16, 16, 128, 2224, 70), (6, 28, 24, 8, 96, 166, 22), (2, 80, 64, 8, 128, 786, 9),
+                                  (8, 24, 16, 16, 128, 1081, 84), (3, 24, 16, 16, 128, 131, 83)], ids=lambda s: f"{s[0]}x{s[6]}-over-{s[5]}")
+def test_one_row_block_is_not_given_up_for_three(size):
+    """A wave with one row block sums the small terms of its products apart from the large ones, one with two or three does not."""
+    assert kr.plan(shape(*size))["rows_per_tile"] == 32
