@@ -768,8 +768,7 @@ __global__ __launch_bounds__(kDirectWaves * 64, 2) void ap_direct_kernel(APParam
                         x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qf[i][ks], x, 0, 0, 0);
                 }
                 // lane (n, half): row n, keys 8*(v/4) + 4*half + v%4 of the block
-                // (the rare branches' code lies behind the loop: 64 tokens over 4096 keys 194.4 -> 192.1 us)
-                if (__builtin_expect(masked, 0)) {
+                if (masked) {
                     const int lim = row_end - kb * 32 - 4 * half;
 #pragma unroll
                     for (int v = 0; v < 16; ++v)
@@ -790,7 +789,7 @@ __global__ __launch_bounds__(kDirectWaves * 64, 2) void ap_direct_kernel(APParam
                     }
                 };
                 exponentials();
-                if (__builtin_expect(__any(!(zb <= kDirectLimit)) != 0, 0)) {   // (rare) some lane's exponentials are too large: raise m, take the block again
+                if (__any(!(zb <= kDirectLimit))) {   // (rare) some lane's exponentials are too large: raise m, take the block again
                     float mx = x[0];
 #pragma unroll
                     for (int v = 1; v < 16; ++v) mx = fmaxf(mx, x[v]);
@@ -827,7 +826,7 @@ __global__ __launch_bounds__(kDirectWaves * 64, 2) void ap_direct_kernel(APParam
                 // lane = (layer l16 or 16 + l16, 16-byte piece kq); 16 + l16 lies 1 KB further on
                 const int eo = row * 2048 + (((l16 * 4) ^ ((l16 >> 2) & 3) ^ kq ^ (row & 15)) << 4);
                 const f16x8 o0 = *reinterpret_cast<const f16x8 *>(et + eo), o1 = *reinterpret_cast<const f16x8 *>(et + (eo + 1024));
-                if (__builtin_expect(rescale, 0)) {   // (rare) element v of block (bi, bj): layers 16*bi + 4*kq + v and 16*bj + l16
+                if (rescale) {   // (rare) element v of block (bi, bj): layers 16*bi + 4*kq + v and 16*bj + l16
                     auto f = [&](int l) { return __builtin_amdgcn_exp2f(m_gram[row * 33 + l] - m_new[row * 33 + l]); };
                     const float c0 = f(l16), c1 = f(16 + l16);
 #pragma unroll
