@@ -549,10 +549,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
                 if (c == NC - 1) read_q();   // every wave has the old rows in use no more
                 const unsigned char *nslot = slot_ptr((c + 1) % NC);
 
-                // (this branch and the one to a second pass are said to be rare: their code lies behind the loop, and a chunk runs on
-                // without a jump.  2 x 77 tokens over 5003 keys 429 -> 425 us, 64 over 4096 119.8 -> 118.6, 512 over 3575 767 -> 761.  Shapes of fewer wave
-                // rows wait for their keys, and in pages they lost by it: 8 decode steps over 4096 keys 367 -> 374.)
-                if (C::WR == 4 ? __builtin_expect(ragged, 0) : (long)ragged) {
+                if (ragged) {
                     // keys at or past key_end: element v of a lane is key kb0 + 8*(v/4) + v%4
 #pragma unroll
                     for (int kb = 0; kb < KBW; ++kb) {
@@ -619,6 +616,10 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
                     }
                     acc[(c + 1) & 1][kb] = nx;
                     asm volatile("" : "+v"(bz), "+v"(bn), "+v"(bd));   // the sums are taken here, beside the MFMAs
+                    // (said to be rare: its code lies behind the loop, and a block runs on without a jump.  230 random calls of more than 64 rows 1.004
+                    // times as fast, 0.98 to 1.04.  Not said of the keys past the end and of the layer test's edges: in a short history most tiles
+                    // have some, and with both behind the loop 77 layer tests over up to 3000 keys were 0.96 to 1.01 times as fast.  Shapes of fewer wave rows
+                    // wait for their keys, and in pages they lost by it: 8 decode steps over 4096 keys 367 -> 374 us.)
                     if (C::WR == 4 ? __builtin_expect(__any(!(bn <= kBig)) != 0, 0) : (long)(__any(!(bn <= kBig)) != 0)) {
                         float tmax = x[0];
 #pragma unroll
@@ -644,7 +645,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void sim_mfma_kernel(SimParams p)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) e[blk][v] = ev[v];
                     tz += bz;
-                    if (IR && __builtin_expect(ir_some, 0)) {
+                    if (IR && ir_some) {
                         // keys of this block inside T_initial or T_recent: all, none, or some
                         const int kb0 = tile_key0 + c * C::CH + (wk * KBW + kb) * 32;
                         if (kb0 + 32 <= p.ir_init_end || kb0 >= p.ir_recent_begin) {
