@@ -432,6 +432,7 @@ typedef struct krul_plan {
     int32_t n_key_splits;
     int32_t n_layer_chunks;  /* pieces of the chain of layers that run side by side           */
     int32_t n_workgroups;
+    int32_t select_kernels;  /* behind it in krul_pair_similarity_select: 1 (heads, averages and choice in one), 2 or 3 */
 } krul_plan_t;
 int krul_pair_similarity_plan_of(const krul_shape_t *shape, int32_t in_static, krul_plan_t *plan);
 

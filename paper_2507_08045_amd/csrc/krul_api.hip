@@ -698,7 +698,9 @@ int krul_pair_similarity_plan_of(const krul_shape_t *shape, int32_t in_static, k
     if (in_static && pl.total_bytes > (size_t)KRUL_STATIC_SCRATCH_BYTES) return KRUL_ESCRATCH;
     const StateLayout &y = pl.lay;
     *plan = krul_plan_t{y.variant == kF32 ? 0 : y.variant, y.variant == kGeneric ? 1 : y.wr * y.rb * 32, pl.keys_per_split, y.n_split, y.n_layer_chunks,
-                        pl.n_workgroups};
+                        pl.n_workgroups, 3};
+    if (pairs_select_fits(shape->n_layers, shape->n_q_heads))
+        plan->select_kernels = select_in_one_launch(y, shape->batch, shape->n_layers, shape->n_q_heads, shape->n_kv_heads, shape->n_query) ? 1 : 2;
     return KRUL_OK;
 }
 

@@ -177,6 +177,8 @@ hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, i
 // memory for them all the same), in one kernel or two.
 hipError_t launch_finalize_select(const StateLayout &lay, const float4 *state, int Hkv, int Tq, float *head_out,
                                   float *head_cos, float *head_dist, const PairsSelectArgs &a, hipStream_t st);
+// (host logic) whether it is one.
+bool select_in_one_launch(const StateLayout &lay, int B, int L, int Hq, int Hkv, int Tq);
 // Pair scores from head scores and the selection, one workgroup per conversation
 // (pairs_select_fits says whether a conversation's head values fit one).
 bool pairs_select_fits(int L, int Hq);

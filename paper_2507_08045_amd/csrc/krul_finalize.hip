@@ -429,25 +429,44 @@ hipError_t launch_finalize(const StateLayout &lay, const float4 *state, int B, i
     return launch_pairs(a, st);
 }
 
-hipError_t launch_finalize_select(const StateLayout &lay, const float4 *state, int Hkv, int Tq, float *head_out,
-                                  float *head_cos, float *head_dist, const PairsSelectArgs &a, hipStream_t st)
+namespace {
+// Rows to the lanes of heads_select_kernel; false where it does not take the call.
+// One launch where all of a conversation's heads are at work at once.  (In two rounds the chain of steps, 3 us, outlasts what a
+// launch costs, 1 to 1.5 on the GPU and 3 on the host: 12.7 -> 16.6 us of GPU time.)
+bool heads_select_args(const StateLayout &lay, const float4 *state, int B, int L, int Hq, int Hkv, int Tq, bool want_dist, HeadsArgs *out, int *waves)
 {
     bool per_wave;
-    HeadsArgs p = heads_args(lay, state, a.B, a.L, a.Hq, Hkv, Tq, a.pair_dist != nullptr, &per_wave);
-    const int RW = 64 / p.G, heads = a.Hq / Hkv;
+    HeadsArgs p = heads_args(lay, state, B, L, Hq, Hkv, Tq, want_dist, &per_wave);
+    const int RW = 64 / p.G, heads = Hq / Hkv;
     if (!per_wave && Tq <= RW) {   // heads of a wave here too
         while (p.TP < Tq) p.TP <<= 1;
         while (p.H < heads && 2 * p.H * p.TP <= RW) p.H <<= 1;
         p.groups = (heads + p.H - 1) / p.H;
         p.by_groups = Div::by((unsigned)p.groups);
     }
-    // One launch where all of a conversation's heads are at work at once.  (In two rounds the chain of steps, 3 us, outlasts what a
-    // launch costs, 1 to 1.5 on the GPU and 3 on the host: 12.7 -> 16.6 us of GPU time.)
-    const long long items = (long long)(a.L - 1) * Hkv * p.groups;
-    if (items <= kTailWaves && p.TP >= Tq) {
+    const long long items = (long long)(L - 1) * Hkv * p.groups;
+    *out = p;
+    *waves = (int)items;
+    return items <= kTailWaves && p.TP >= Tq;
+}
+}  // namespace
+
+bool select_in_one_launch(const StateLayout &lay, int B, int L, int Hq, int Hkv, int Tq)
+{
+    HeadsArgs p;
+    int waves;
+    return heads_select_args(lay, nullptr, B, L, Hq, Hkv, Tq, true, &p, &waves);
+}
+
+hipError_t launch_finalize_select(const StateLayout &lay, const float4 *state, int Hkv, int Tq, float *head_out,
+                                  float *head_cos, float *head_dist, const PairsSelectArgs &a, hipStream_t st)
+{
+    HeadsArgs p;
+    int waves;
+    if (heads_select_args(lay, state, a.B, a.L, a.Hq, Hkv, Tq, a.pair_dist != nullptr, &p, &waves)) {
         p.head_cos = head_out;
         const size_t smem = (size_t)(a.L - 1) * (2 * a.Hq + 1) * sizeof(float) + select_scratch_bytes(a.L);
-        hipLaunchKernelGGL(heads_select_kernel, dim3(a.B), dim3((unsigned)items * 64), smem, st, p, a);
+        hipLaunchKernelGGL(heads_select_kernel, dim3(a.B), dim3((unsigned)waves * 64), smem, st, p, a);
         return hipGetLastError();
     }
     const hipError_t e = launch_finalize(lay, state, a.B, a.L, a.Hq, Hkv, Tq, head_cos, head_dist, nullptr, a.pair_dist, false, nullptr, st);

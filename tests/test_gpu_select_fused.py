@@ -30,16 +30,26 @@ CASES = [
     ("sel-at-the-limit", 2, 129, 128, 8, 64, 100, 1, "bf16", 16, False),  # 128*128 = 16384: the largest conversation one workgroup takes
 ]
 
-# heads, pairs and choice in one kernel: up to 16 groups of heads in a conversation, rows of a head in one run
-CASES += [
-    ("tail-16-groups", 2, 9, 2, 2, 64, 300, 16, "f32", 3, True),        # ... and one more:
-    ("tail-17-groups", 2, 18, 1, 1, 64, 300, 16, "f32", 5, True),
-    ("tail-rows-64", 1, 5, 6, 2, 64, 200, 64, "bf16", 2, False),        # a wave's worth of rows, three heads of a kv head
-    ("tail-rows-65", 1, 5, 2, 1, 64, 200, 65, "bf16", 2, False),        # two runs
-    ("tail-ragged-group", 3, 4, 10, 2, 64, 700, 9, "f16", 1, True),     # five heads of a kv head, four to a wave
-    ("tail-shared-rows", 1, 3, 3, 1, 128, 4000, 33, "bf16", 1, False),  # lanes that share a row
-    ("tail-many-heads", 2, 3, 128, 1, 64, 100, 1, "bf16", 1, False),
+# heads, pairs and choice in one kernel (1): up to 16 waves, each a group of heads, rows of a head in one run; two kernels (2) past either
+TAIL = [
+    (1, ("tail-16-groups", 2, 9, 2, 2, 64, 300, 16, "f32", 3, True)),        # ... and one more:
+    (2, ("tail-17-groups", 2, 18, 1, 1, 64, 300, 16, "f32", 5, True)),
+    (1, ("tail-three-waves", 1, 2, 3, 1, 64, 64, 33, "f32", 1, False)),         # three waves of one head each
+    (1, ("tail-rows-64-three-layers", 1, 3, 6, 2, 64, 200, 64, "bf16", 1, False)),   # a wave's worth of rows, three heads of a kv head
+    (2, ("tail-rows-64", 1, 5, 6, 2, 64, 200, 64, "bf16", 2, False)),        # ... 24 groups
+    (2, ("tail-rows-65", 1, 5, 2, 1, 64, 200, 65, "bf16", 2, False)),        # two runs
+    (1, ("tail-ragged-four", 3, 4, 10, 2, 64, 200, 9, "f16", 1, True)),      # five heads of a kv head, four to a wave
+    (1, ("tail-ragged-two", 3, 3, 10, 2, 64, 700, 9, "f16", 1, True)),       # ... two lanes a row, two heads to a wave
+    (2, ("tail-ragged-group", 3, 4, 10, 2, 64, 700, 9, "f16", 1, True)),     # ... 18 groups
+    (1, ("tail-two-lanes-a-row", 1, 3, 3, 1, 64, 700, 29, "f16", 1, False)),
+    (1, ("tail-four-lanes-a-row", 1, 3, 3, 1, 128, 2000, 16, "bf16", 1, False)),
+    (1, ("tail-four-lanes-ragged", 1, 3, 3, 1, 128, 1200, 13, "f32", 1, False)),
+    (2, ("tail-shared-rows", 1, 3, 3, 1, 128, 4000, 33, "bf16", 1, False)),  # more rows than the lanes that share them take at once
+    (1, ("tail-few-rows-shared", 2, 3, 5, 1, 128, 4000, 3, "f32", 1, True)), # eight lanes a row, two heads to a wave, the last wave one
+    (1, ("tail-many-heads", 2, 3, 128, 1, 64, 100, 1, "bf16", 1, False)),
 ]
+CASES += [c for _, c in TAIL]
+KERNELS = {c[0]: n for n, c in TAIL}
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
@@ -50,6 +60,8 @@ def test_select_fused_matches_two_calls_and_oracle(G, oracle, case):
     rho = rng.uniform(0.3, 0.95, size=(B, L - 1, Hkv))
     w = workloads.make(name, B=B, L=L, Hq=Hq, Hkv=Hkv, d=d, S=S, Tq=Tq, dtype=dtype, rho_k=rho, seed=131)
     q, k = G.to_device(w)
+    if name in KERNELS:
+        assert kr.plan(kr.make_shape(q, k))["select_kernels"] == KERNELS[name]
     el = (rng.random((B, L)) > 0.2).astype(np.uint8) if with_el else None
     el_gpu = torch.from_numpy(el).cuda() if with_el else None
 
