@@ -31,6 +31,26 @@ CASES = [
 ]
 
 
+def rows_per_tile(q, k, flags):
+    import paper_2507_08045_amd as kr
+    return kr.plan(kr.make_shape(q, k, flags=flags))["rows_per_tile"]
+
+
+def in_pages(k):
+    """The keys [B, L, Hkv, S, d] in pages of 16 tokens: pools of the layers, block table."""
+    B, L, Hkv, S, d = k.shape
+    blocks = -(-S // 16)
+    table = torch.randperm(B * blocks, device="cuda").view(B, blocks)
+    pools = []
+    for l in range(L):
+        pool = torch.zeros((B * blocks, 16, Hkv, d), dtype=k.dtype, device="cuda")
+        padded = torch.zeros((B, blocks * 16, Hkv, d), dtype=k.dtype, device="cuda")
+        padded[:, :S] = k[:, l].permute(0, 2, 1, 3)
+        pool[table.view(-1)] = padded.view(B * blocks, 16, Hkv, d)
+        pools.append(pool)
+    return pools, table.to(torch.int32)
+
+
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_f32_kernel_matches_oracle(oracle, case):
     import gpu_util as G
@@ -39,6 +59,8 @@ def test_f32_kernel_matches_oracle(oracle, case):
     w = workloads.make(name, B=B, L=L, Hq=Hq, Hkv=Hkv, d=d, S=S, Tq=Tq, dtype=dtype, seed=411,
                        rho_k=np.random.default_rng(6).uniform(0.4, 0.95, size=(B, L - 1, Hkv)))
     q, k = G.to_device(w)
+    if name.startswith("three-blocks"):
+        assert rows_per_tile(q, k, 0) == 96
     want = oracle.pair_similarity(w.q, w.k)
     for flags in (0, kr.KRUL_FLAG_SINGLE_SPLIT):   # the second: one workgroup along the keys walks all tiles
         got = G.gpu_scores(q, k, flags=flags)
@@ -51,19 +73,49 @@ def test_f32_kernel_matches_oracle(oracle, case):
         gc, wc = G.gpu_scores(q, k, flags=kr.KRUL_FLAG_CAUSAL), oracle.pair_similarity(w.q, w.k, causal=True)
         G.assert_close(gc["head_score"], wc["head_score"], TOL32, f"{name} causal head_score")
     # keys in pages give the dense call's bits
-    blocks = -(-S // 16)
-    table = torch.randperm(B * blocks, device="cuda").view(B, blocks)
-    pools = []
-    for l in range(L):
-        pool = torch.zeros((B * blocks, 16, Hkv, d), dtype=k.dtype, device="cuda")
-        padded = torch.zeros((B, blocks * 16, Hkv, d), dtype=k.dtype, device="cuda")
-        padded[:, :S] = k[:, l].permute(0, 2, 1, 3)
-        pool[table.view(-1)] = padded.view(B * blocks, 16, Hkv, d)
-        pools.append(pool)
-    paged = kr.pair_similarity_paged(q, pools, table.to(torch.int32), S)
+    paged = kr.pair_similarity_paged(q, *in_pages(k), S)
     dense = kr.pair_similarity(q, k)
     torch.cuda.synchronize()
     assert torch.equal(paged["head_score"], dense["head_score"]), name
+
+
+# (name, B, L, Hq, Hkv, d, S, Tq, all keys in one split, keys of a split, pieces of the layers): 96-row tiles, heads that fill the steps of 16 elements
+# or not, splits of several tiles, whose running records (the layer test's too) then come from memory or, of another piece's layer, from LDS
+THREE_BLOCKS = [
+    ("d72", 1, 33, 16, 16, 72, 511, 65, True, 512, 16),
+    ("d88-rows-end-in-both-tiles", 2, 5, 24, 24, 88, 390, 186, True, 512, 2),
+    ("d96-chain", 8, 3, 24, 24, 96, 511, 65, True, 512, 1),
+    ("d104", 1, 33, 16, 16, 104, 511, 65, True, 512, 16),
+    ("d120-rows-end-in-both-tiles", 2, 5, 24, 24, 120, 390, 186, True, 512, 2),
+    ("d120-one-tile", 1, 17, 32, 32, 120, 300, 65, False, 256, 4),
+    ("d128-two-splits", 4, 3, 24, 24, 128, 1000, 65, False, 512, 1),
+    ("d128-grouped", 1, 32, 32, 8, 128, 3000, 24, False, 768, 8),
+]
+
+
+@pytest.mark.parametrize("case", THREE_BLOCKS, ids=[c[0] for c in THREE_BLOCKS])
+def test_three_row_blocks(oracle, case):
+    import gpu_util as G
+    import paper_2507_08045_amd as kr
+    name, B, L, Hq, Hkv, d, S, Tq, single, keys_per_split, pieces = case
+    flags = kr.KRUL_FLAG_SINGLE_SPLIT if single else 0
+    w = workloads.make(name, B=B, L=L, Hq=Hq, Hkv=Hkv, d=d, S=S, Tq=Tq, dtype="f32", seed=413,
+                       rho_k=np.random.default_rng(7).uniform(0.4, 0.95, size=(B, L - 1, Hkv)))
+    q, k = G.to_device(w)
+    for f in (flags, flags | kr.KRUL_FLAG_CAUSAL):
+        plan = kr.plan(kr.make_shape(q, k, flags=f))
+        assert (plan["rows_per_tile"], plan["keys_per_split"], plan["n_layer_chunks"]) == (96, keys_per_split, pieces), plan
+    got, want = G.gpu_scores(q, k, flags=flags), oracle.pair_similarity(w.q, w.k)
+    for n in ("head_score", "pair_score", "pair_dist"):
+        G.assert_close(got[n], want[n], TOL32, f"{name} {n}")
+    ir = kr.pair_similarity_ir(q, k, 0.2, flags=flags)
+    paged = kr.pair_similarity_paged(q, *in_pages(k), S, flags=flags)
+    torch.cuda.synchronize()
+    G.assert_close(ir["ir_mass"].cpu().numpy(), oracle.ir_mass(w.q, w.k, 0.2)[0], TOL32, f"{name} ir_mass")
+    np.testing.assert_array_equal(paged["head_score"].cpu().numpy(), got["head_score"])
+    gc, wc = G.gpu_scores(q, k, flags=flags | kr.KRUL_FLAG_CAUSAL), oracle.pair_similarity(w.q, w.k, causal=True)
+    for n in ("head_score", "pair_dist"):
+        G.assert_close(gc[n], wc[n], TOL32, f"{name} causal {n}")
 
 
 def test_causal_whole_prompt_f32(oracle):
