@@ -423,7 +423,7 @@ int make_plan(const krul_shape_t *s, Plan *pl, bool want_ir, bool plain_keys, bo
         // sum of their own, one with two or three has no registers for it (modelled over 128 unit-normal elements: 6.8e-7, 1.5e-6 and 1.4e-6
         // root mean square of a logit).  For heads above 64 (below, within 5 % either way but for one call of 60), on memory that the others'
         // plan takes too.  Their step is entered longer than it was best fitted (7.0), so that a close call stays with the others: 24
-        // tokens over 1021 keys 84 -> 68 us; 70 drawn calls that take them are 1.13 to 1.50 times as fast (65 to 96 rows most of them, 128 padded
+        // tokens over 1021 keys 84 -> 68 us; 140 drawn calls that take them are 1.10 to 1.50 times as fast (65 to 96 rows most of them, 128 padded
         // ones in the others), 110 that do not would be 0.59 to 1.17 times as fast in them.  Short calls are not asked: the
         // candidates take the host 1 us, and such calls wait for it.
         for (int rb = 1; rb <= rb_most || (rb == 3 && y.rb == 2 && Rk > 64 && s->head_dim > 64 && best_t >= 40.0); ++rb) {

@@ -38,7 +38,7 @@ enum Variant : int {
     kMfmaMidShort = 6,   // bf16 MFMA,  64 rows x 128 keys (2x2 waves)
     kMfmaWideShort = 7,  // bf16 MFMA, 128 rows x 128 keys (4x2 waves)
     kMfmaBig = 8,        // bf16 MFMA, 256 rows x 256 keys (4x2 waves, two 32-row blocks per wave): krul_mfma_big.hip
-    kF32 = 9,       // float32 inputs and heads above 128: 32 or 64 rows x 128 keys per workgroup tile (4 waves): krul_f32.hip
+    kF32 = 9,       // float32 inputs and heads above 128: 32 or 64 rows x 128 keys per workgroup tile (4 waves), 96 x 256 (8): krul_f32.hip
     kMfmaWideDeep = 10,  // bf16 MFMA, 128 rows x 512 keys (4x2 waves), heads up to 64, without the layer test
 };
 

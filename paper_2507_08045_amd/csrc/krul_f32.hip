@@ -12,23 +12,25 @@
 //
 // What bounds it.  32 keys x 32 rows at head_dim 128 are 48 MFMAs of 32 cycles; splitting the keys takes 352 vector
 // instructions per 32 keys of a wave, the exponentials, the share in the query rows' split and the sums some 250 per
-// row block, in part beside the MFMAs.  So the vector units are the bound, and with more than 32 rows a wave takes two
-// row blocks on one split of the keys, with more than 64 three in workgroups of eight waves (one to a CU: 24 query tokens over 1021 keys, 96
-// rows, this kernel 73 -> 55 us; without its MFMAs 76 -> 78 a call, without the exponentials and merges -8 us, without loads of keys -8, without
-// the keys' split -5, without the query rows' -5).
+// row block, in part beside the MFMAs.  So with more than 32 rows a wave takes two row blocks on one split of the keys, with more than 64 three
+// in workgroups of eight waves, one to a CU (24 query tokens over 1021 keys, 96 rows in place of 128 padded ones: this kernel 75 -> 56 us; 1.2 of
+// that factor are the rows, less the layers that more pieces of the chain read twice).  No one part bounds the kernel of three row blocks: of a call of 58.5 us without selection a
+// build without its MFMAs takes 49.9, without exponentials and sums 52.5, without loads of keys 54.1, without merges 56.4, without the query rows'
+// loads 57.1 or their split 57.1, without the keys' split, which hides beside the MFMAs, 59.0.
 //
 // A workgroup of four (eight) waves owns 32 * RB query rows of a unit (conversation, kv head), a key split and a chunk of
 // layers.  It walks the split in tiles of 128 (256) keys (32 per wave) and, inside a tile, the layers of the chunk in order,
 // so that the previous layer's exponentials are in registers when the cross term is taken (as in sim_mfma_kernel).
-// Keys go from memory to the registers of the one wave that uses them, a layer ahead; query rows are split once per
-// workgroup and handed round in LDS.  In the MFMA result a lane owns one query row and 16 keys; the row's eight
+// Keys go from memory to the registers of the one wave that uses them, a layer ahead, with three row blocks half a layer; query rows
+// are split once per workgroup and handed round in LDS.  In the MFMA result a lane owns one query row and 16 keys; the row's eight (sixteen)
 // partials (two half-waves of each wave) and its running record over the tiles before (its row record, stored after
 // every tile) are merged one step late, every wave taking a share of a block's rows.
 //
 // Measured (one conversation, 32 layers, 32 query / 8 kv heads of 128, the whole call): 24 query tokens over 1021 keys 3080 -> 67 us
-// (this kernel 55), 64 over 4096 31400 -> 499 us, against one wave per query row on the vector units, every row fetching the keys
+// (this kernel 56), 64 over 4096 31400 -> 499 us, against one wave per query row on the vector units, every row fetching the keys
 // anew (float32 MFMAs in this kernel's place: 115 and 740 us).  Errors against a float64 evaluation, geometric means over 12 calls drawn
-// over the float32 sizes: cosines 4.1e-8, distances 4.7e-8 of themselves (the vector units' float32 products: 5.6e-8 and 6.3e-8).
+// over the float32 sizes: cosines 4.1e-8, distances 4.7e-8 of themselves (the vector units' float32 products: 5.6e-8 and 6.3e-8); over 700 calls
+// in 96-row tiles 4.95e-8 and 4.85e-8, the same calls in 64-row tiles 4.97e-8 and 4.82e-8.
 #include "krul_common.h"
 
 namespace krul {

@@ -245,8 +245,8 @@ __global__ __launch_bounds__(kThreads) void finalize_heads_kernel(HeadsArgs p)
 
 // A small model's heads, averages and greedy choice in one launch, a workgroup per conversation (krul_pair_similarity_select): a wave
 // per group of heads, all of them at once (the same bits as finalize_heads_kernel and pairs_select_kernel).  The chain of steps is theirs,
-// without the launch between them: 16 float32 tokens over 256 keys of 4 layers, 2 heads, 3.7 and 2.6 us -> 4.3, the call, which the host
-// bounds, 22.3 -> 18.9.
+// without the launch between them: 16 float32 tokens over 256 keys of 4 layers, 2 heads, 3.6 and 2.6 us -> 4.2, the call, which the host
+// bounds, 20.8 -> 18.6.
 constexpr int kTailWaves = 16;
 
 __global__ __launch_bounds__(kTailWaves * 64) void heads_select_kernel(HeadsArgs p, PairsSelectArgs a)
